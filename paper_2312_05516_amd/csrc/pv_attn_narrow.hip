@@ -255,7 +255,11 @@ __global__ __launch_bounds__(256, 2) void attn_narrow_kernel(
 }
 
 // Merge of split-KV partial results: out = sum_s 2^(m_s - M) O_s / sum_s 2^(m_s - M) l_s.
-// One workgroup = 8 rows of one split item (32 threads per row, D/32 output elements each).
+// One workgroup = eight groups of 32 threads; combine_groups() of them share a row, each taking every
+// so-manyth part (D/32 output elements per thread), and add up through LDS.  The parts of a row are
+// megabytes apart from any other access, so what bounds this kernel is the number of dependent round
+// trips to memory: the 32 threads read all (max, sum) pairs of the row at once, and the partial
+// outputs of a thread are independent loads.
 template <typename T, int D>
 __global__ __launch_bounds__(256) void attn_combine_kernel(
     const CombineChunk *__restrict__ chunks, const CombineItem *__restrict__ items,
@@ -263,34 +267,53 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(
     int32_t group, uint16_t *__restrict__ out)
 {
     constexpr int PER = D / 32;
+    typedef float vecf __attribute__((ext_vector_type(PER)));
+    __shared__ vecf sm_acc[8][32];
     const CombineChunk ch = chunks[blockIdx.x];
     const CombineItem it = items[ch.item];
-    const int r = ch.row0 + ((int)threadIdx.x >> 5);
-    if (r >= it.row_count) return;
-    const int d0 = ((int)threadIdx.x & 31) * PER;
+    const int groups = combine_groups(it.split_count);
+    const int t = (int)threadIdx.x & 31;
+    const int grp = (int)threadIdx.x >> 5;
+    const int part = grp % groups;
+    const int r = ch.row0 + grp / groups;
+    const bool valid = r < it.row_count;
+    const int64_t slot0 = (int64_t)it.partial_base + (valid ? r : 0);
+
     float M = -INFINITY;
-    for (int s = 0; s < it.split_count; ++s) {
-        const int64_t slot = (int64_t)it.partial_base + (int64_t)s * it.row_count + r;
-        M = fmaxf(M, ws_ml[2 * slot]);
-    }
+    for (int s = t; s < it.split_count; s += 32)
+        M = fmaxf(M, ws_ml[2 * (slot0 + (int64_t)s * it.row_count)]);
+#pragma unroll
+    for (int x = 16; x >= 1; x >>= 1) M = fmaxf(M, __shfl_xor(M, x));
     const float M_safe = M == -INFINITY ? 0.f : M;
     float L = 0.f;
-    float acc[PER];
+    for (int s = t; s < it.split_count; s += 32) {
+        const int64_t slot = slot0 + (int64_t)s * it.row_count;
+        L += fast_exp2(ws_ml[2 * slot] - M_safe) * ws_ml[2 * slot + 1];
+    }
+#pragma unroll
+    for (int x = 16; x >= 1; x >>= 1) L += __shfl_xor(L, x);
+
+    vecf acc;
 #pragma unroll
     for (int e = 0; e < PER; ++e) acc[e] = 0.f;
-    for (int s = 0; s < it.split_count; ++s) {
-        const int64_t slot = (int64_t)it.partial_base + (int64_t)s * it.row_count + r;
-        const float wgt = fast_exp2(ws_ml[2 * slot] - M_safe);
-        L += wgt * ws_ml[2 * slot + 1];
-        const float *po = ws_o + slot * D + d0;
-#pragma unroll
-        for (int e = 0; e < PER; ++e) acc[e] += wgt * po[e];
+#pragma unroll 4
+    for (int s = part; s < it.split_count; s += groups) {
+        const int64_t slot = slot0 + (int64_t)s * it.row_count;
+        acc += fast_exp2(ws_ml[2 * slot] - M_safe) *
+               *reinterpret_cast<const vecf *>(ws_o + slot * D + t * PER);
     }
+    if (groups > 1) {  // the same for the whole workgroup
+        sm_acc[grp][t] = acc;
+        __syncthreads();
+        if (part != 0) return;
+        for (int i = 1; i < groups; ++i) acc += sm_acc[grp + i][t];
+    }
+    if (!valid) return;
     const float inv = 1.f / L;
     const int orow = it.row_begin + r;
     const int otok = orow / group;
     const int ohq = it.kv_head * group + orow % group;
-    uint16_t *dst = out + ((int64_t)(it.q_row0 + otok) * num_q_heads + ohq) * D + d0;
+    uint16_t *dst = out + ((int64_t)(it.q_row0 + otok) * num_q_heads + ohq) * D + t * PER;
     if constexpr (PER == 4) {
         *reinterpret_cast<u32x2 *>(dst) =
             u32x2{T::pack2(acc[0] * inv, acc[1] * inv), T::pack2(acc[2] * inv, acc[3] * inv)};

@@ -432,7 +432,8 @@ pv_status build_plan(const pv_pool_desc *pool, int32_t num_q_heads, const int32_
     order_items(plan->tile256, kTileRows, tune.xcds);
     plan->partial_slots = slots;
     for (size_t i = 0; i < plan->combine.size(); ++i)
-        for (int32_t r0 = 0; r0 < plan->combine[i].row_count; r0 += 8)
+        for (int32_t r0 = 0; r0 < plan->combine[i].row_count;
+             r0 += 8 / combine_groups(plan->combine[i].split_count))
             plan->combine_chunks.push_back(CombineChunk{(int32_t)i, r0});
     // workspace: fp32 partial outputs [slots][D], then (running max, running sum) [slots][2]
     plan->workspace_bytes = (size_t)slots * (size_t)(pool->head_dim + 2) * sizeof(float);

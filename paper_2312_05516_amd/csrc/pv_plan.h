@@ -40,7 +40,15 @@ struct CombineItem {
 };
 static_assert(sizeof(CombineItem) == 32, "CombineItem is read by the kernels as 8 int32");
 
-// Eight rows of one combine item: the unit of work of one merge workgroup.
+// How many of a merge workgroup's eight thread groups share one row, by the number of parts to add:
+// with few parts one group reads them all, with many the reads are spread over the groups, so that
+// nobody reads more than four parts after one another up to 32 of them.
+constexpr int combine_groups(int split_count)
+{
+    return split_count >= 16 ? 8 : split_count >= 8 ? 4 : split_count >= 4 ? 2 : 1;
+}
+
+// 8 / combine_groups() rows of one combine item: the unit of work of one merge workgroup.
 struct CombineChunk {
     int32_t item;  // index into the combine list
     int32_t row0;  // first row (relative to the item) of the chunk
