@@ -41,7 +41,9 @@ static int32_t env_int(const char *name, int32_t fallback)
 Tuning default_tuning()
 {
     Tuning t;
-    t.split_target = env_int("PV_SPLIT_TARGET", 1024);
+    t.split_target = env_int("PV_SPLIT_TARGET", 0);
+    t.split_by_hand = t.split_target > 0;
+    if (!t.split_by_hand) t.split_target = 1024;
     t.min_split_keys = env_int("PV_MIN_SPLIT_KEYS", 256);
     t.wide_min_rows = env_int("PV_WIDE_MIN_ROWS", 33);
     t.xcds = env_int("PV_XCDS", 8);
@@ -70,40 +72,73 @@ static int64_t item_cost(const WorkItem &w, int rows_per_step)
     return (int64_t)(w.kv_end - w.kv_begin) * steps;
 }
 
-// Cut long items into parts of the KV range.  With `chunk` = the KV length that would give about
-// split_target equal items (never below min_split_keys):
-//  * a list too short to fill the GPU (fewer than split_target items) is cut everywhere, every
-//    item longer than `chunk` into parts of about that length;
-//  * in a longer list only the outliers are cut, items more than twice as long as `chunk`, because
-//    one workgroup walking such an item alone would outlast everything else.
-//  * whatever the list, no part is longer than max_len keys (0 = no such limit).
+// Cut long items into parts of the KV range.  A cut is not free: every part pays the set-up of an
+// item, writes its rows in fp32, and the merge reads them back.  `slots` = workgroups of the kernel
+// that the GPU holds at once.
+//  * A list of fewer than kFewItems is cut everywhere, into parts of the shortest length (never below
+//    min_split_keys) at which all of them still run at once: one part more than there are slots
+//    starts when the others are nearly done and doubles the time.
+//  * In a longer list only the outliers are cut, items more than a quarter longer than `chunk` = the
+//    KV length of kFewItems equal items, because one workgroup walking such an item alone would
+//    outlast everything else.
+//  * Whatever the list, no part is longer than max_len keys (0 = no such limit).
+//  * Nothing is cut where the merge costs more than the shorter longest item gives: the merge is a
+//    launch of about 7 us, and moves 8 bytes per partial row element at about 4 TB/s; an item takes
+//    key_ns per key.
+// Measured, whole step, against a rule that cut every list of fewer than 1024 items into about 1024
+// parts: 28 requests, 752 items of the 128-row kernel (64/8 heads) 114 -> 82 us; 16 requests, 570
+// items (40/10 heads) 82 -> 54; 4 generation steps over 0.7-9 K keys, 64/8 heads 30 -> 27; 96 of them
+// 97 -> 93.  With 768 in place of kFewItems the first two stay at 102 and 80.  The cost of the merge:
+// 3 first prompts of 191-755 tokens, 64/8 heads (472 items of 24 blocks of 32 keys) 46 -> 39 us.
+// `slots` = 0, or a target set by hand: lists shorter than split_target are cut into about that
+// many parts, and longer ones at items more than twice as long as the target's share.
+constexpr int32_t kFewItems = 512;
+
 static void split_items(std::vector<WorkItem> &items, std::vector<CombineItem> &combine,
-                        int64_t &slots, const Tuning &tune, int64_t max_len = 0)
+                        int64_t &slots_out, const Tuning &tune, int32_t slots, int32_t key_ns,
+                        int32_t head_dim, int64_t max_len = 0)
 {
     if (items.empty()) return;
+    if (tune.split_by_hand) slots = 0;
+    const int32_t target = slots ? kFewItems : tune.split_target;
     int64_t total_keys = 0;
     for (const WorkItem &w : items) total_keys += w.kv_end - w.kv_begin;
-    int64_t chunk = (total_keys + tune.split_target - 1) / tune.split_target;
+    int64_t chunk = (total_keys + target - 1) / target;
+    const bool outliers_only = (int64_t)items.size() >= target;
+    if (slots && !outliers_only) chunk = (total_keys + slots - 1) / slots;
     chunk = std::max<int64_t>(chunk, tune.min_split_keys);
     chunk = (chunk + kKvBlock - 1) / kKvBlock * kKvBlock;
-    const bool outliers_only = (int64_t)items.size() >= tune.split_target;
+    while (slots && !outliers_only) {
+        int64_t parts = 0;
+        for (const WorkItem &w : items) parts += (w.kv_end - w.kv_begin + chunk - 1) / chunk;
+        if (parts <= slots) break;
+        chunk += (chunk / 32 + kKvBlock - 1) / kKvBlock * kKvBlock;
+    }
+    const int64_t longest_whole = !outliers_only ? chunk : slots ? chunk + chunk / 4 : 2 * chunk;
     auto too_long = [&](int64_t len) { return max_len > 0 && len > max_len; };
     auto wants_split = [&](const WorkItem &w) {
         const int64_t len = w.kv_end - w.kv_begin;
-        return too_long(len) || (len > chunk && len >= 2 * (int64_t)tune.min_split_keys &&
-                                 !(outliers_only && len <= 2 * chunk));
+        return too_long(len) || (len > longest_whole && len >= 2 * (int64_t)tune.min_split_keys);
     };
     bool any = false;
-    for (const WorkItem &w : items) any = any || wants_split(w);
+    int64_t longest = 0, part_rows = 0;
+    for (const WorkItem &w : items) {
+        if (!wants_split(w)) continue;
+        any = true;
+        const int64_t len = w.kv_end - w.kv_begin;
+        longest = std::max(longest, len);
+        part_rows += w.row_count * ((len + chunk - 1) / chunk);
+    }
     if (!any) return;  // the common case of a long list: nothing is copied
+    if (slots && !too_long(longest) &&
+        (longest - longest_whole) * key_ns < 7000 + part_rows * head_dim * 8 / 4000)
+        return;
     std::vector<WorkItem> result;
     result.reserve(items.size() * 2);
     for (const WorkItem &w : items) {
         const int64_t len = w.kv_end - w.kv_begin;
         int64_t parts = (len + chunk - 1) / chunk;
-        if (parts <= 1 || len < 2 * (int64_t)tune.min_split_keys ||
-            (outliers_only && len <= 2 * chunk))
-            parts = 1;
+        if (len <= longest_whole || len < 2 * (int64_t)tune.min_split_keys) parts = 1;
         if (too_long(len)) parts = std::max(parts, (len + max_len - 1) / max_len);
         if (parts <= 1) {
             result.push_back(w);
@@ -121,7 +156,7 @@ static void split_items(std::vector<WorkItem> &items, std::vector<CombineItem> &
         c.kv_head = w.kv_head;
         c.row_begin = w.row_begin;
         c.row_count = w.row_count;
-        c.partial_base = (int32_t)slots;
+        c.partial_base = (int32_t)slots_out;
         c.split_count = (int32_t)parts;
         c.q_row0 = w.q_row0;
         c.reserved = 0;
@@ -132,10 +167,10 @@ static void split_items(std::vector<WorkItem> &items, std::vector<CombineItem> &
             part.kv_end = (int32_t)std::min<int64_t>(w.kv_end, w.kv_begin + (s + 1) * part_len);
             part.split_index = (int32_t)s;
             part.split_count = (int32_t)parts;
-            part.partial_base = (int32_t)(slots + s * w.row_count);
+            part.partial_base = (int32_t)(slots_out + s * w.row_count);
             result.push_back(part);
         }
-        slots += parts * w.row_count;
+        slots_out += parts * w.row_count;
     }
     items.swap(result);
 }
@@ -419,9 +454,10 @@ pv_status build_plan(const pv_pool_desc *pool, int32_t num_q_heads, const int32_
         }
     }
     int64_t slots = 0;
-    split_items(plan->narrow, plan->combine, slots, tune);
-    split_items(plan->wide, plan->combine, slots, tune);
-    split_items(plan->tile256, plan->combine, slots, tune,
+    split_items(plan->narrow, plan->combine, slots, tune, kNarrowSlots, kNarrowKeyNs,
+                pool->head_dim);
+    split_items(plan->wide, plan->combine, slots, tune, kWideSlots, kWideKeyNs, pool->head_dim);
+    split_items(plan->tile256, plan->combine, slots, tune, 0, 0, pool->head_dim,
                 (int64_t)kTileMaxPages * pool->page_size - kKvBlock);
     if (slots > INT32_MAX / 2) {
         delete plan;

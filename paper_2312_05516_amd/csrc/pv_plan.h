@@ -68,6 +68,10 @@ static_assert(sizeof(AppendGroup) == 16, "AppendGroup is read by the kernel as 4
 constexpr int kNarrowRows = 16;  // rows per item of the bandwidth-oriented kernel
 constexpr int kWideRows = 128;   // rows per item of the matrix-core kernel (4 waves x 32 rows)
 constexpr int kTileRows = 256;   // rows per item of the 256-row matrix-core kernel (4 waves x 64)
+constexpr int kNarrowSlots = 512;  // workgroups that run at once: 256 CUs x 2 (256 registers a lane)
+constexpr int kWideSlots = 768;    // 256 CUs x 3 (168 registers a lane, 48 KiB of LDS)
+constexpr int kNarrowKeyNs = 16;   // time of an item per key while the GPU is not full, measured
+constexpr int kWideKeyNs = 31;
 constexpr int kKvBlock = 32;     // keys per inner step (two pages)
 constexpr int kTileMaxPages = 8192;  // page ids an item of the 256-row kernel may span (it keeps
                                      // them in LDS): its KV range is at most 16 times that
@@ -85,7 +89,9 @@ struct DeviceLists {
 };
 
 struct Tuning {
-    int32_t split_target;    // aim for at least this many work items per kernel
+    int32_t split_target;    // cut a list that is shorter into about this many work items (the
+                             // 256-row kernel, and every kernel when it is set by hand)
+    bool split_by_hand;
     int32_t min_split_keys;  // never make a KV part shorter than this
     int32_t wide_min_rows;   // (request, KV head) units with n*G >= this use the matrix-core
                              // kernel; smaller ones are cut into 16-row items of the narrow kernel

@@ -172,6 +172,41 @@ def test_plan_cuts_outliers_of_a_long_list(pv):
     plan.destroy()
 
 
+@pytest.mark.parametrize("ctx,qn,hq,hkv,kind,slots", [
+    ([700, 3000, 9000, 5000], [1] * 4, 64, 8, 0, 512),       # generation steps, 32 units
+    ([30000] * 48 + [60000], [1] * 49, 80, 10, 0, 512),      # 490 items: little room for parts
+    ([25000 + 100 * i for i in range(10)], [40] * 10, 10, 10, 1, 768),
+    ([9000, 200], [150, 90], 40, 40, 1, 768),
+])
+def test_plan_cuts_a_short_list_into_parts_that_run_at_once(pv, ctx, qn, hq, hkv, kind, slots):
+    """Fewer than 512 items: parts of one length that all fit the GPU at once, covering every unit's
+    KV range without gaps; no part below the shortest length unless it is a last one."""
+    plan = pv.plan_create(pv.pool_desc(1 << 17, hkv, 128, "f16"), hq, ctx, qn, 4096)
+    items = _items(pv, plan, kind)
+    assert pv.plan_num_work_items(plan, 2) > 0
+    assert len(items) <= slots
+    by_unit = {}
+    for it in items:
+        by_unit.setdefault((int(it[0]), int(it[1]), int(it[2])), []).append(it)
+    for (req, _, row0), parts in by_unit.items():
+        parts.sort(key=lambda it: int(it[6]))
+        assert [int(p[6]) for p in parts] == list(range(int(parts[0][7])))
+        assert int(parts[0][4]) == 0
+        assert all(int(a[5]) == int(b[4]) for a, b in zip(parts, parts[1:]))
+        group = hq // hkv
+        assert int(parts[-1][5]) == ctx[req] + (row0 + int(parts[0][3]) - 1) // group + 1
+        assert all(int(p[5] - p[4]) >= 128 for p in parts[:-1])
+    plan.destroy()
+
+
+def test_plan_leaves_a_short_list_whole_when_the_merge_costs_more(pv):
+    """Prompts of a few hundred tokens over 8 KV heads: 24 blocks at most, and 128-row partial results
+    would be written and read back for less than what the cut saves."""
+    plan = pv.plan_create(pv.pool_desc(4096, 8, 128, "bf16"), 64, [0] * 3, [191, 400, 755], 64)
+    assert pv.plan_num_work_items(plan, 1) > 0 and pv.plan_num_work_items(plan, 2) == 0
+    plan.destroy()
+
+
 def test_rope_table_matches_the_definition(pv, oracle):
     """The library's host table generator against the oracle's (independent code, same formula):
     equal up to one unit in the last place of a float."""

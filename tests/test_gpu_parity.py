@@ -135,6 +135,23 @@ def test_split_kv_and_combine(oracle, monkeypatch):
     check_case(oracle, H.make_case(b2, fill="nan"))
 
 
+@pytest.mark.parametrize("parts", [2, 3, 4, 7, 8, 15, 16, 17, 32, 33, 70])
+@pytest.mark.parametrize("head_dim", [64, 128])
+def test_merge_of_any_number_of_parts(oracle, monkeypatch, parts, head_dim):
+    """The merge spreads the parts of a row over one to eight thread groups: counts on both sides of
+    each step, more parts than a group has threads, rows that do not fill a workgroup."""
+    from paper_2312_05516_amd import binding as pv
+    monkeypatch.setenv("PV_MIN_SPLIT_KEYS", "32")
+    monkeypatch.setenv("PV_SPLIT_TARGET", str(parts))
+    b = wl.custom([32 * parts - 3], [3], num_q_heads=3, num_kv_heads=1, head_dim=head_dim,
+                  dtype="bf16" if parts % 2 else "f16", seed=480 + parts)
+    desc = pv.pool_desc(b.num_pages, b.num_kv_heads, b.head_dim, b.dtype)
+    plan = pv.plan_create(desc, b.num_q_heads, b.ctx_lens, b.q_lens, b.max_pages_per_req)
+    assert pv.plan_num_work_items(plan, 0) == parts and pv.plan_num_work_items(plan, 2) == 1
+    plan.destroy()
+    check_case(oracle, H.make_case(b, fill="nan"))
+
+
 def test_workspace_is_checked():
     import torch
     from paper_2312_05516_amd import binding as pv
