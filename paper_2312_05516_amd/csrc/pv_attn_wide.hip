@@ -7,7 +7,7 @@
 // never materialised.
 //
 // Mapping to gfx950.  One workgroup = 4 wavefronts = one item; wavefront w owns rows 32w..32w+31.
-// The K/V page tiles of a 32-key block (two pages) are copied from HBM straight into LDS
+// The K/V page tiles of a block (two pages; four for head size 64) are copied from HBM straight into LDS
 // (global_load_lds, 16 bytes per lane, fully coalesced because a (page, head) tile is contiguous
 // in the pool; no register staging, no ds_write) into a ring of three stages, two blocks ahead of
 // their use, and every wavefront reads its matrix-core operands from there, so a tile is fetched
@@ -16,7 +16,7 @@
 // consecutive bytes (no bank conflicts, no padding, no transposes).  Scores are produced
 // transposed, S^T = K Q^T (v_mfma_f32_32x32x16), so each lane owns one query row (softmax without
 // cross-lane traffic except one exchange for the maximum) and the probabilities are already the B
-// operand of O^T += V^T P^T.  About 160 VGPRs and 48 KiB of LDS let three workgroups share a CU, whose
+// operand of O^T += V^T P^T.  About 160 VGPRs (145 for head size 64) and 48 KiB of LDS let three workgroups share a CU, whose
 // wavefronts overlap each other's matrix-core, vector-ALU and LDS phases.  One raw s_barrier per
 // block, preceded by a wait that leaves only the newest loads in flight.  Blocks that touch the
 // causal boundary or the end of the sequence take a separate, masked instantiation so the
@@ -36,11 +36,17 @@ __global__ __launch_bounds__(256, 3) void attn_wide_kernel(
     int32_t num_kv_heads, int32_t group, float scale_log2e, uint32_t q_sign,
     uint16_t *__restrict__ out, float *__restrict__ ws_o, float *__restrict__ ws_ml)
 {
-    constexpr int BK = 32;                      // keys per block
+    // Keys per block: 32 for head size 128; 64 for head size 64, where 32 keys are only 8 matrix-core
+    // instructions of a wavefront against about 70 of the vector ALU, a barrier, a test for the
+    // maximum and two LDS round trips.  48 requests over 0.1-3 K tokens, 32/8 heads: 108.8 -> 104.1 us
+    // whole step.  (Head size 128 would need 231 registers a lane for 64 keys, two workgroups per CU.)
+    constexpr int PAGES = D == 128 ? 2 : 4;
+    constexpr int BK = 16 * PAGES;
+    constexpr int NT = BK / 32;                 // 32-key score tiles of a block
     constexpr int KS = D / 16;                  // k-steps of S^T = K Q^T
     constexpr int NB = D / 32;                  // 32-wide blocks of d in O^T
     constexpr int TILE_BYTES = 16 * D * 2;      // one (page, head) tile
-    constexpr int HALF_BYTES = 2 * TILE_BYTES;  // K (or V) part of a stage: two pages
+    constexpr int HALF_BYTES = PAGES * TILE_BYTES;  // K (or V) part of a stage
     constexpr int PASSES = HALF_BYTES / 4096;   // 16-byte copies per lane for K (same for V)
     constexpr int STAGES = 3;
     typedef typename T::vec8 vec8;
@@ -56,7 +62,9 @@ __global__ __launch_bounds__(256, 3) void attn_wide_kernel(
     const bool valid = 32 * w + q32 < it.row_count;
     const int tok = valid ? row / group : 0;
     const int hq = it.kv_head * group + (valid ? row % group : 0);
-    const int vis_end = valid ? it.ctx + tok + 1 : it.kv_end;
+    // one past the last key of the item this row may see (a part of a KV range need not end at the
+    // end of a block)
+    const int vis_end = valid ? min(it.ctx + tok + 1, it.kv_end) : it.kv_end;
     // wavefront-uniform limits: below unmasked_end nothing is masked for this wavefront's rows
     // (and no slot is past the end); at or beyond wave_end nothing is visible to them
     const int wave_rows = it.row_count - 32 * w;  // may be <= 0
@@ -96,20 +104,22 @@ __global__ __launch_bounds__(256, 3) void attn_wide_kernel(
     const int64_t page_stride = (int64_t)num_kv_heads * (16 * D);
 
     const uint32_t lane_bytes = (uint32_t)lane * 16u;
-    // page ids of a block (two pages; a page past the end is never used, so any valid id will do)
+    // asynchronous copies move bytes [w*1024, w*1024+1024) of every 4 KiB pass over the K (V) part:
+    // ids of the pages that this wavefront's pieces of a block lie in (a page past the end is never
+    // used, so any valid id will do)
+    static_assert(PASSES == 2, "two pieces of K and two of V per wavefront and block");
     auto page_ids = [&](int b, int &id0, int &id1) {
-        const int pg = pg0 + 2 * b;
+        const int pg = pg0 + PAGES * b + w * 1024 / TILE_BYTES;
         id0 = pt[pg <= last_pg ? pg : last_pg];
-        id1 = pt[pg + 1 <= last_pg ? pg + 1 : last_pg];
+        id1 = pt[pg + PAGES / 2 <= last_pg ? pg + PAGES / 2 : last_pg];
     };
-    // asynchronous copy of block b into stage b % 3: wavefront w moves bytes [w*1024, w*1024+1024)
-    // of every 4 KiB pass, lane l the 16 bytes at 16*l of those (scalar base + lane offset)
+    // block b into stage b % 3, lane l the 16 bytes at 16*l of a piece (scalar base + lane offset)
     auto dma_block = [&](int b, int id0, int id1) {
         unsigned char *stage = smem[b % STAGES];
 #pragma unroll
         for (int p = 0; p < PASSES; ++p) {
             const int off = p * 4096 + w * 1024;  // wavefront-uniform
-            const int page = off / TILE_BYTES ? id1 : id0;
+            const int page = p ? id1 : id0;
             const int64_t elem = (int64_t)page * page_stride + head_off + (off % TILE_BYTES) / 2;
             lds_dma16(k_pages + elem, lane_bytes, stage + off);
             lds_dma16(v_pages + elem, lane_bytes, stage + HALF_BYTES + off);
@@ -127,29 +137,38 @@ __global__ __launch_bounds__(256, 3) void attn_wide_kernel(
 
     auto compute_block = [&](const unsigned char *sb, int kb0, auto masked_tag) {
         constexpr bool MASKED = decltype(masked_tag)::value;
-        f32x16 s;
+        f32x16 s[NT];
 #pragma unroll
-        for (int v = 0; v < 16; ++v) s[v] = 0.f;
+        for (int t = 0; t < NT; ++t)
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            const u32x4 kf = *reinterpret_cast<const u32x4 *>(sb + k_lds + ks * 512);
-            s = T::mfma32(as_vec8<T>(kf), qf[ks], s);
-        }
-        // register v = 8*page + j  <->  key kb0 + 16*page + 8*h + j
-        bool vis[16];
+            for (int v = 0; v < 16; ++v) s[t][v] = 0.f;
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) {
+                const u32x4 kf = *reinterpret_cast<const u32x4 *>(sb + k_lds + t * 2 * TILE_BYTES +
+                                                                  ks * 512);
+                s[t] = T::mfma32(as_vec8<T>(kf), qf[ks], s[t]);
+            }
+        // register v = 8*page + j of tile t  <->  key kb0 + 32*t + 16*page + 8*h + j
+        bool vis[NT][16];
         if constexpr (MASKED) {
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                vis[v] = kb0 + 16 * (v >> 3) + 8 * h + (v & 7) < vis_end;
-                if (!vis[v]) s[v] = -INFINITY;
-            }
-        }
-        float mx = s[0];
+            for (int t = 0; t < NT; ++t)
 #pragma unroll
-        for (int v = 1; v < 16; ++v) mx = fmaxf(mx, s[v]);
+                for (int v = 0; v < 16; ++v) {
+                    vis[t][v] = kb0 + 32 * t + 16 * (v >> 3) + 8 * h + (v & 7) < vis_end;
+                    if (!vis[t][v]) s[t][v] = -INFINITY;
+                }
+        }
+        float mx = s[0][0];
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+            for (int v = t ? 0 : 1; v < 16; ++v) mx = fmaxf(mx, s[t][v]);
         // Lazy rescale: the reference maximum of a row only moves when a new score exceeds it by
         // more than 2^kLazyLog2 in the scaled domain (exact, because softmax is shift-invariant; the
-        // probabilities just range up to 2^kLazyLog2 instead of 1).  Each lane tests the 16 keys it
+        // probabilities just range up to 2^kLazyLog2 instead of 1).  Each lane tests the keys it
         // holds; only when some lane of the wavefront sees such a score (or has no reference yet)
         // do the two lanes of a row exchange their maxima and the accumulators get rescaled.
         const bool grow = m_run == -INFINITY || (mx - m_run) * scale_log2e > kLazyLog2;
@@ -168,19 +187,20 @@ __global__ __launch_bounds__(256, 3) void attn_wide_kernel(
                 for (int blk = 0; blk < NB; ++blk) o[blk] *= alpha;
             }
         }
-        // page by page: the matrix-core work of page 0 is issued before the exponentials of page 1,
+        // page by page: the matrix-core work of a page is issued before the exponentials of the next,
         // so that inside this wavefront the two have something to overlap with
         float psum = 0.f;
 #pragma unroll
-        for (int pg = 0; pg < 2; ++pg) {
+        for (int pg = 0; pg < PAGES; ++pg) {
+            const int t = pg / 2, v0 = 8 * (pg % 2);
             u32x4 praw;
 #pragma unroll
             for (int jj = 0; jj < 4; ++jj) {
-                float p0 = fast_exp2(__builtin_fmaf(s[8 * pg + 2 * jj], scale_log2e, -mc));
-                float p1 = fast_exp2(__builtin_fmaf(s[8 * pg + 2 * jj + 1], scale_log2e, -mc));
+                float p0 = fast_exp2(__builtin_fmaf(s[t][v0 + 2 * jj], scale_log2e, -mc));
+                float p1 = fast_exp2(__builtin_fmaf(s[t][v0 + 2 * jj + 1], scale_log2e, -mc));
                 if constexpr (MASKED) {
-                    p0 = vis[8 * pg + 2 * jj] ? p0 : 0.f;
-                    p1 = vis[8 * pg + 2 * jj + 1] ? p1 : 0.f;
+                    p0 = vis[t][v0 + 2 * jj] ? p0 : 0.f;
+                    p1 = vis[t][v0 + 2 * jj + 1] ? p1 : 0.f;
                 }
                 praw[jj] = T::pack2(p0, p1);
                 psum = T::add_pair(praw[jj], psum);  // the sum of what the matrix core will see

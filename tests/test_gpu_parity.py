@@ -152,6 +152,20 @@ def test_merge_of_any_number_of_parts(oracle, monkeypatch, parts, head_dim):
     check_case(oracle, H.make_case(b, fill="nan"))
 
 
+@pytest.mark.parametrize("kv_len", [1, 31, 32, 33, 63, 64, 65, 96, 127, 128, 129, 191, 193])
+@pytest.mark.parametrize("head_dim", [64, 128])
+def test_matrix_core_kernel_block_edges(oracle, monkeypatch, kv_len, head_dim):
+    """KV lengths around the 32- and 64-key blocks of the 128-row kernel, whole and cut into parts of
+    32 keys (a part then ends in the middle of a 64-key block: keys behind it are not the part's)."""
+    new = min(kv_len, 41)
+    b = wl.custom([kv_len - new, 70], [new, 40], num_q_heads=2, num_kv_heads=1, head_dim=head_dim,
+                  dtype="bf16" if kv_len % 2 else "f16", seed=700 + kv_len)
+    check_case(oracle, H.make_case(b, fill="nan"))
+    monkeypatch.setenv("PV_MIN_SPLIT_KEYS", "32")
+    monkeypatch.setenv("PV_SPLIT_TARGET", "64")
+    check_case(oracle, H.make_case(b, fill="nan"))
+
+
 def test_workspace_is_checked():
     import torch
     from paper_2312_05516_amd import binding as pv
