@@ -145,6 +145,11 @@ __device__ __forceinline__ u32x4 load16_stream(const void *p)
     return __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(p));
 }
 
+__device__ __forceinline__ void store16_stream(void *p, u32x4 v)
+{
+    __builtin_nontemporal_store(v, reinterpret_cast<u32x4 *>(p));
+}
+
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
 // max(a, b, c) in one instruction, for values that are known not to be signalling NaNs (fmaxf on

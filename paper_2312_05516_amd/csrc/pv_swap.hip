@@ -5,7 +5,10 @@
 //
 // Staging layout: for the i-th listed page, its K image (num_kv_heads * 16 * D elements, exactly
 // as in the pool) followed by its V image.  One workgroup moves one 4 KiB piece with 16 bytes per
-// lane; pure copies, bit-exact.
+// lane; pure copies, bit-exact.  Bound: HBM.  Both sides are touched once, so loads and stores carry
+// the streaming hint: 1024 pages of 160 KiB out and as many in, 243 us with ordinary stores, 219 us
+// so (6.1 TB/s; a plain device copy reaches 5.3).  More bytes per workgroup are slower (8 KiB 234 us,
+// 16 KiB 240 us, 32 KiB 326 us).
 #include "pv_device.h"
 
 namespace pv {
@@ -26,9 +29,9 @@ __global__ __launch_bounds__(256) void pages_copy_kernel(
     unsigned char *pool = (which ? v_pages : k_pages) + page * page_bytes + off;
     unsigned char *stage = staging + ((int64_t)2 * i + which) * page_bytes + off;
     if (GATHER)
-        *reinterpret_cast<u32x4 *>(stage) = load16_stream(pool);
+        store16_stream(stage, load16_stream(pool));
     else
-        *reinterpret_cast<u32x4 *>(pool) = load16_stream(stage);
+        store16_stream(pool, load16_stream(stage));
 }
 
 hipError_t launch_pages_copy(bool gather, const pv_pool_desc *pool, const int32_t *page_ids,
