@@ -13,15 +13,17 @@
 
 namespace pv {
 
-template <int D>
-__global__ __launch_bounds__(D) void kv_append_kernel(
-    const AppendGroup *__restrict__ groups, const uint16_t *__restrict__ k_new,
-    const uint16_t *__restrict__ v_new, const int32_t *__restrict__ page_table, int32_t max_pages,
-    int32_t num_kv_heads, uint16_t *__restrict__ k_pages, uint16_t *__restrict__ v_pages)
+// KV head h of the tokens of one append group
+template <int D, bool STREAM>
+__device__ __forceinline__ void append_group(const AppendGroup &g, int h,
+                                             const uint16_t *__restrict__ k_new,
+                                             const uint16_t *__restrict__ v_new,
+                                             const int32_t *__restrict__ page_table,
+                                             int32_t max_pages, int32_t num_kv_heads,
+                                             uint16_t *__restrict__ k_pages,
+                                             uint16_t *__restrict__ v_pages)
 {
     constexpr int CH = D / 8;
-    const AppendGroup g = groups[blockIdx.x];
-    const int h = (int)blockIdx.y;
     const int t = (int)threadIdx.x;
     const int64_t page = page_table[(int64_t)g.req * max_pages + (g.t_begin >> 4)];
     const int slot0 = g.t_begin & 15;  // slot of the group's first token; the group stays in one
@@ -35,32 +37,48 @@ __global__ __launch_bounds__(D) void kv_append_kernel(
     {
         const int j = t / CH, c8 = t % CH;
         if (j < g.count) {
-            const u32x4 kv = load16(ksrc + j * row_stride + 8 * c8);
+            const u32x4 kv = load16_as<STREAM>(ksrc + j * row_stride + 8 * c8);
             *reinterpret_cast<u32x4 *>(k_pages + tile + (c8 * 16 + slot0 + j) * 8) = kv;
         }
     }
     // V: thread -> head dimension d = t
-    scatter_v_group<D>(vsrc, row_stride, g.count, slot0, t, v_pages + tile);
+    scatter_v_group<D, 1, STREAM>(vsrc, row_stride, g.count, 1, slot0, t, v_pages + tile);
+}
+
+template <int D, bool STREAM>
+__global__ __launch_bounds__(D) void kv_append_kernel(
+    const AppendGroup *__restrict__ groups, const uint16_t *__restrict__ k_new,
+    const uint16_t *__restrict__ v_new, const int32_t *__restrict__ page_table, int32_t max_pages,
+    int32_t num_kv_heads, uint16_t *__restrict__ k_pages, uint16_t *__restrict__ v_pages)
+{
+    const AppendGroup g = groups[blockIdx.x];
+    append_group<D, STREAM>(g, (int)blockIdx.y, k_new, v_new, page_table, max_pages, num_kv_heads,
+                            k_pages, v_pages);
+}
+
+template <int D, bool STREAM>
+static void launch_append_t(const pv_plan *plan, const DeviceLists &dl, const void *k_new,
+                            const void *v_new, const int32_t *page_table, void *k_pages,
+                            void *v_pages, hipStream_t stream)
+{
+    const dim3 grid((unsigned)plan->append_groups.size(), (unsigned)plan->pool.num_kv_heads);
+    hipLaunchKernelGGL((kv_append_kernel<D, STREAM>), grid, dim3(D), 0, stream, dl.append_groups,
+                       (const uint16_t *)k_new, (const uint16_t *)v_new, page_table,
+                       plan->max_pages_per_req, plan->pool.num_kv_heads, (uint16_t *)k_pages,
+                       (uint16_t *)v_pages);
 }
 
 hipError_t launch_kv_append(const pv_plan *plan, const DeviceLists &dl, const void *k_new, const void *v_new,
                             const int32_t *page_table, void *k_pages, void *v_pages,
                             hipStream_t stream)
 {
-    const int D = plan->pool.head_dim;
-    const size_t groups = plan->append_groups.size();
-    if (groups == 0) return hipSuccess;
-    const dim3 grid((unsigned)groups, (unsigned)plan->pool.num_kv_heads);
-    if (D == 128)
-        hipLaunchKernelGGL((kv_append_kernel<128>), grid, dim3(128), 0, stream,
-                           dl.append_groups, (const uint16_t *)k_new, (const uint16_t *)v_new,
-                           page_table, plan->max_pages_per_req, plan->pool.num_kv_heads,
-                           (uint16_t *)k_pages, (uint16_t *)v_pages);
-    else
-        hipLaunchKernelGGL((kv_append_kernel<64>), grid, dim3(64), 0, stream,
-                           dl.append_groups, (const uint16_t *)k_new, (const uint16_t *)v_new,
-                           page_table, plan->max_pages_per_req, plan->pool.num_kv_heads,
-                           (uint16_t *)k_pages, (uint16_t *)v_pages);
+    if (plan->append_groups.empty()) return hipSuccess;
+    const bool many =
+        (int64_t)plan->append_groups.size() * plan->pool.num_kv_heads > kManyRows;
+    auto go = plan->pool.head_dim == 128
+                  ? (many ? launch_append_t<128, true> : launch_append_t<128, false>)
+                  : (many ? launch_append_t<64, true> : launch_append_t<64, false>);
+    go(plan, dl, k_new, v_new, page_table, k_pages, v_pages, stream);
     return hipGetLastError();
 }
 

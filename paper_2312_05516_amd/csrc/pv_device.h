@@ -145,6 +145,12 @@ __device__ __forceinline__ u32x4 load16_stream(const void *p)
     return __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(p));
 }
 
+template <bool STREAM>
+__device__ __forceinline__ u32x4 load16_as(const void *p)
+{
+    return STREAM ? load16_stream(p) : load16(p);
+}
+
 __device__ __forceinline__ void store16_stream(void *p, u32x4 v)
 {
     __builtin_nontemporal_store(v, reinterpret_cast<u32x4 *>(p));
@@ -189,30 +195,46 @@ __device__ __forceinline__ void lds_dma16(const void *uniform_base, uint32_t lan
 }
 
 // V part of the KV append, shared by the plain and the rotary-fused append kernels so that the
-// bit-exact path exists once.  Thread d (of D) owns head dimension d of one (page, head) tile:
-// it gathers that dimension from the `count` (1..8) consecutive new tokens of an append group
-// (rows of `vsrc`, `row_stride` elements apart) and stores them at slots slot0 .. slot0+count-1,
-// which lie inside one 8-slot run of the V tile.  A full run is one 16-byte store; a partial one
-// is written element by element so that the other slots keep their contents.
-template <int D>
-__device__ __forceinline__ void scatter_v_group(const uint16_t *vsrc, int64_t row_stride,
-                                                int count, int slot0, int d, uint16_t *v_tile)
+// bit-exact path exists once.  Thread d (of D) owns head dimension d of HB (page, head) tiles, those
+// of heads 0 .. heads-1 behind `vsrc` and `v_tiles` (`heads` <= HB): it gathers that dimension from
+// the `count` (1..8) consecutive new tokens of an append group (rows of `vsrc`, `row_stride` elements
+// apart) and stores them at slots slot0 .. slot0+count-1, which lie inside one 8-slot run of a V
+// tile.  A full run is one 16-byte store; a partial one is written element by element so that the
+// other slots keep their contents.  All loads are issued before the first store; a row past the
+// group's last is that last row once more, so that no load depends on a condition.  STREAM: the loads
+// carry the streaming hint (see kManyRows).
+template <int D, int HB, bool STREAM>
+__device__ __forceinline__ void scatter_v_group(const uint16_t *__restrict__ vsrc,
+                                                int64_t row_stride, int count, int heads, int slot0,
+                                                int d, uint16_t *__restrict__ v_tiles)
 {
-    uint16_t vals[8];
+    uint16_t vals[HB][8];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) vals[j] = j < count ? vsrc[j * row_stride + d] : (uint16_t)0;
-    uint16_t *vdst = v_tile + ((int64_t)((slot0 >> 3) * D + d) * 8);
-    if (count == 8) {
-        u32x4 packed;
+    for (int i = 0; i < HB; ++i) {
+        const uint16_t *src = vsrc + (i < heads ? i : 0) * D + d;
 #pragma unroll
-        for (int jj = 0; jj < 4; ++jj)
-            packed[jj] = (uint32_t)vals[2 * jj] | ((uint32_t)vals[2 * jj + 1] << 16);
-        *reinterpret_cast<u32x4 *>(vdst) = packed;
-    } else {
-        const int s0 = slot0 & 7;
+        for (int j = 0; j < 8; ++j) {
+            const uint16_t *from = src + (j < count ? j : count - 1) * row_stride;
+            vals[i][j] = STREAM ? __builtin_nontemporal_load(from) : *from;
+        }
+    }
+    const int64_t run = (int64_t)((slot0 >> 3) * D + d) * 8;
 #pragma unroll
-        for (int j = 0; j < 8; ++j)
-            if (j < count) vdst[s0 + j] = vals[j];
+    for (int i = 0; i < HB; ++i) {
+        if (i >= heads) break;
+        uint16_t *vdst = v_tiles + i * (16 * D) + run;
+        if (count == 8) {
+            u32x4 packed;
+#pragma unroll
+            for (int jj = 0; jj < 4; ++jj)
+                packed[jj] = (uint32_t)vals[i][2 * jj] | ((uint32_t)vals[i][2 * jj + 1] << 16);
+            *reinterpret_cast<u32x4 *>(vdst) = packed;
+        } else {
+            const int s0 = slot0 & 7;
+#pragma unroll
+            for (int j = 0; j < 8; ++j)
+                if (j < count) vdst[s0 + j] = vals[i][j];
+        }
     }
 }
 

@@ -65,6 +65,14 @@ struct AppendGroup {
 };
 static_assert(sizeof(AppendGroup) == 16, "AppendGroup is read by the kernel as 4 int32");
 
+// Append and rotary kernels: with more (append group, head) rows than this the new rows are read with
+// the streaming hint, because they are read once and what is written (K/V pages, rotated queries) is
+// read by the attention that follows: 2600 tokens x 40 heads, append and attention 187.5 -> 185.5 us;
+// 7 K tokens with the rotary embedding see pick_rope.  Below, the rows of a small batch are still in a
+// cache when they come from the kernel before (4 generation steps, 64/8 heads: 26.0 us, 26.3 with the
+// hint).  Streaming the stores too is slower (first prompts 193 -> 204 us).
+constexpr int64_t kManyRows = 4096;
+
 constexpr int kNarrowRows = 16;  // rows per item of the bandwidth-oriented kernel
 constexpr int kWideRows = 128;   // rows per item of the matrix-core kernel (4 waves x 32 rows)
 constexpr int kTileRows = 256;   // rows per item of the 256-row matrix-core kernel (4 waves x 64)

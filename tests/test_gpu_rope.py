@@ -132,6 +132,25 @@ def test_fused_rope_append_matches_oracle(oracle, style, dtype, D):
     _close_bits(q_got, q_want, "rotated Q", case.q, dtype)
 
 
+@pytest.mark.parametrize("style", ["interleaved", "half"])
+@pytest.mark.parametrize("hq,hkv", [(6, 3), (10, 5), (7, 7), (12, 1)])
+def test_batches_of_many_rows_take_several_heads_a_workgroup(oracle, style, hq, hkv):
+    """More than 4096 (append group, head) pairs: two or four heads a workgroup, head counts that do
+    not divide by that on either side, partial 8-slot groups at both ends."""
+    n = 8 * (4096 // (hq + hkv) + 2)
+    b = wl.custom([5, 0], [n, 3], num_q_heads=hq, num_kv_heads=hkv, head_dim=64, dtype="bf16",
+                  seed=320 + hq)
+    case = H.make_case(b, fill="nan")
+    table = oracle.rope_table(10000.0, 64, n + 5)
+    q_want, _, kp_want, vp_want = _oracle_fused(oracle, case, table, style)
+    q_got, kp_got, vp_got, _ = _gpu_fused(case, table, style)
+    assert np.array_equal(vp_got, vp_want)
+    _check_k(b, kp_got, kp_want, case, oracle, b.dtype)
+    _close_bits(q_got, q_want, "rotated Q", case.q, b.dtype)
+    q_got, _, _, _ = _gpu_fused(case, table, style, in_place=True)
+    _close_bits(q_got, q_want, "rotated Q in place", case.q, b.dtype)
+
+
 def test_slots_not_addressed_keep_their_contents(oracle):
     b = wl.custom([3, 20], [2, 9], num_q_heads=2, num_kv_heads=2, head_dim=64, dtype="f16", seed=302)
     case = H.make_case(b, fill="random")
