@@ -246,19 +246,19 @@ pv_status pv_plan_kernel_ms(pv_plan *plan, int32_t kind, float *ms);
 
 /*
  * One-shot forms with explicit arrays: convenient, not meant for the per-layer hot loop (use a
- * plan there).  They build a temporary plan from the HOST length arrays (read during the call),
- * launch, and free the plan.  q_start must be the exclusive prefix sum of q_lens and total_q their
- * sum, else PV_ERR_INVALID_ARG.  slot_offsets[r] is the logical position of request r's first
- * new token (normally ctx_lens[r]).
+ * plan there).  The HOST length arrays are read during the call.  q_start must be the exclusive
+ * prefix sum of q_lens and total_q their sum, else PV_ERR_INVALID_ARG.  slot_offsets[r] is the
+ * logical position of request r's first new token (normally ctx_lens[r]).
  *   pv_multi_token_paged_attn: when `workspace` (256-byte aligned) holds at least
  *     pv_attn_workspace_bytes(...) bytes, the temporary plan's lists go behind the partial results
  *     in it: nothing is allocated, the lists are copied with hipMemcpyAsync on `stream`, the
- *     library does not synchronise, and the temporary plan is freed by a host function queued on
- *     `stream` behind the launches (what the runtime does for a copy out of pageable host memory
- *     is its own business; it may wait for that one copy).  With a smaller workspace that still
+ *     library does not synchronise (the runtime performs a copy out of pageable host memory, as
+ *     this one is, synchronously), and the temporary plan is freed when the call returns, or, in a
+ *     stream capture, by a host function behind the launches.  With a smaller workspace that still
  *     covers the partial results, the lists go to temporary device memory and the call waits for
  *     the stream before freeing it.
- *   pv_kv_append has no buffer argument: temporary device memory, and it waits for the stream.
+ *   pv_kv_append has no buffer argument and needs no plan: the positions travel as kernel
+ *     arguments.  It waits for the stream.
  */
 pv_status pv_kv_append(const pv_pool_desc *pool, const void *k_new, const void *v_new,
                        const int32_t *page_table /* device */, int32_t max_pages_per_req,

@@ -56,6 +56,54 @@ __global__ __launch_bounds__(D) void kv_append_kernel(
                             k_pages, v_pages);
 }
 
+// The same for a batch that has no plan: the requests come with the launch, and a workgroup works out
+// its append group from them (a binary search of at most seven steps in the kernel's arguments).
+// So the one-shot call needs no device memory for a list, no copy of one and no wait for that copy.
+template <int D>
+__global__ __launch_bounds__(D) void kv_append_reqs_kernel(
+    const AppendReqs reqs, const uint16_t *__restrict__ k_new, const uint16_t *__restrict__ v_new,
+    const int32_t *__restrict__ page_table, int32_t max_pages, int32_t num_kv_heads,
+    uint16_t *__restrict__ k_pages, uint16_t *__restrict__ v_pages)
+{
+    const int gi = (int)blockIdx.x;
+    int lo = 0, hi = reqs.n - 1;  // the last request whose first group is not behind this one
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (reqs.r[mid].group0 <= gi)
+            lo = mid;
+        else
+            hi = mid - 1;
+    }
+    const AppendReq r = reqs.r[lo];
+    const int run = (r.t_begin >> 3) + gi - r.group0;  // 8-slot run of the request's positions
+    const int end = r.t_begin + r.count;
+    AppendGroup g;
+    g.req = r.req;
+    g.t_begin = max(8 * run, r.t_begin);
+    g.count = min(8 * run + 8, end) - g.t_begin;
+    g.q_row = r.q_row + g.t_begin - r.t_begin;
+    append_group<D, false>(g, (int)blockIdx.y, k_new, v_new, page_table, max_pages, num_kv_heads,
+                           k_pages, v_pages);
+}
+
+hipError_t launch_kv_append_reqs(const pv_pool_desc *pool, const AppendReqs &reqs,
+                                 const void *k_new, const void *v_new, const int32_t *page_table,
+                                 int32_t max_pages, void *k_pages, void *v_pages,
+                                 hipStream_t stream)
+{
+    if (reqs.n <= 0) return hipSuccess;
+    const dim3 grid((unsigned)reqs.groups, (unsigned)pool->num_kv_heads);
+    if (pool->head_dim == 128)
+        hipLaunchKernelGGL((kv_append_reqs_kernel<128>), grid, dim3(128), 0, stream, reqs,
+                           (const uint16_t *)k_new, (const uint16_t *)v_new, page_table, max_pages,
+                           pool->num_kv_heads, (uint16_t *)k_pages, (uint16_t *)v_pages);
+    else
+        hipLaunchKernelGGL((kv_append_reqs_kernel<64>), grid, dim3(64), 0, stream, reqs,
+                           (const uint16_t *)k_new, (const uint16_t *)v_new, page_table, max_pages,
+                           pool->num_kv_heads, (uint16_t *)k_pages, (uint16_t *)v_pages);
+    return hipGetLastError();
+}
+
 template <int D, bool STREAM>
 static void launch_append_t(const pv_plan *plan, const DeviceLists &dl, const void *k_new,
                             const void *v_new, const int32_t *page_table, void *k_pages,

@@ -12,6 +12,10 @@ namespace pv {
 hipError_t launch_kv_append(const pv_plan *plan, const DeviceLists &dl, const void *k_new,
                             const void *v_new, const int32_t *page_table, void *k_pages,
                             void *v_pages, hipStream_t stream);
+hipError_t launch_kv_append_reqs(const pv_pool_desc *pool, const AppendReqs &reqs,
+                                 const void *k_new, const void *v_new, const int32_t *page_table,
+                                 int32_t max_pages, void *k_pages, void *v_pages,
+                                 hipStream_t stream);
 hipError_t launch_attn_narrow(const pv_plan *plan, const DeviceLists &dl, const void *q,
                               const void *k_pages, const void *v_pages,
                               const int32_t *page_table, float scale, void *out, float *ws_o,
@@ -341,20 +345,36 @@ pv_status pv_kv_append(const pv_pool_desc *pool, const void *k_new, const void *
     pv_status s = check_prefix(q_lens, q_start, num_reqs, total_q);
     if (s != PV_OK) return s;
     if (!pool || pool->num_kv_heads <= 0) return PV_ERR_INVALID_ARG;
-    pv_plan *plan = nullptr;
     // the append only needs positions, so any head grouping is fine: use G = 1
-    s = pv_plan_create(pool, pool->num_kv_heads, slot_offsets, q_lens, num_reqs, max_pages_per_req,
-                       &plan);
-    if (s != PV_OK) return s;
-    // this form has no buffer of the caller's to put the lists in: temporary device memory, and
-    // a wait for the stream before it is freed
-    if (plan->total_q > 0) s = pv_plan_upload(plan);
-    if (s == PV_OK)
-        s = pv_kv_append_planned(plan, k_new, v_new, page_table, k_pages, v_pages, stream);
-    if (s == PV_OK && plan->total_q > 0 &&
-        hipStreamSynchronize(static_cast<hipStream_t>(stream)) != hipSuccess)
-        s = PV_ERR_HIP;
-    pv_plan_destroy(plan);
+    int32_t total = 0;
+    s = pv::check_batch(pool, pool->num_kv_heads, slot_offsets, q_lens, num_reqs, max_pages_per_req,
+                        &total);
+    if (s != PV_OK || total == 0) return s;
+    if (!k_new || !v_new || !page_table || !k_pages || !v_pages) return PV_ERR_INVALID_ARG;
+    if (!pv::aligned16(k_new) || !pv::aligned16(v_new) || !pv::aligned16(k_pages) ||
+        !pv::aligned16(v_pages))
+        return PV_ERR_INVALID_ARG;
+    // The positions travel as kernel arguments, up to kAppendReqs requests a launch, in place of a
+    // temporary list that had to be allocated, copied, waited for and freed: with the host function
+    // of the attention call gone too, 129 -> 68 us for an append and the attention behind it (3
+    // requests over 2 K tokens, 64/8 heads).
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    pv::AppendReqs reqs;
+    reqs.n = reqs.groups = 0;
+    for (int32_t r = 0; r < num_reqs; ++r) {
+        if (q_lens[r] > 0) {
+            reqs.r[reqs.n++] =
+                pv::AppendReq{r, slot_offsets[r], q_lens[r], q_start[r], reqs.groups};
+            reqs.groups += (int32_t)pv::append_group_count(slot_offsets[r], q_lens[r]);
+        }
+        if ((reqs.n == pv::kAppendReqs || r + 1 == num_reqs) && reqs.n > 0) {
+            if (pv::launch_kv_append_reqs(pool, reqs, k_new, v_new, page_table, max_pages_per_req,
+                                          k_pages, v_pages, st) != hipSuccess)
+                s = PV_ERR_HIP;
+            reqs.n = reqs.groups = 0;
+        }
+    }
+    if (hipStreamSynchronize(st) != hipSuccess && s == PV_OK) s = PV_ERR_HIP;
     return s;
 }
 
@@ -398,7 +418,16 @@ pv_status pv_multi_token_paged_attn(const pv_pool_desc *pool, int32_t num_q_head
         s = pv_multi_token_paged_attn_planned(plan, q, k_pages, v_pages, page_table, scale, out,
                                               workspace, workspace_bytes, stream);
     if (s == PV_OK && !wait) {
-        // the plan holds no device memory and no events here: freeing it is a plain delete,
+        // Outside a capture the plan can go at once: a copy out of pageable memory, as the plan's
+        // image is, is performed synchronously, and the launches hold their arguments.  (A host
+        // function behind the launches costs about 20 us of host time.)
+        hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(static_cast<hipStream_t>(stream), &capture) == hipSuccess &&
+            capture == hipStreamCaptureStatusNone) {
+            pv_plan_destroy(plan);
+            return PV_OK;
+        }
+        // under capture the copy runs later.  The plan holds no device memory and no events here: freeing it is a plain delete,
         // which a host function may do (it must not call into the runtime)
         if (hipLaunchHostFunc(static_cast<hipStream_t>(stream),
                               [](void *p) { delete static_cast<pv_plan *>(p); },

@@ -278,12 +278,10 @@ static void build_image(pv_plan *plan)
             std::memcpy(plan->image.data() + plan->image_off[i], parts[i].src, parts[i].bytes);
 }
 
-pv_status build_plan(const pv_pool_desc *pool, int32_t num_q_heads, const int32_t *ctx_lens,
-                     const int32_t *q_lens, int32_t num_reqs, int32_t max_pages_per_req,
-                     const Tuning &tune, pv_plan **out)
+pv_status check_batch(const pv_pool_desc *pool, int32_t num_q_heads, const int32_t *ctx_lens,
+                      const int32_t *q_lens, int32_t num_reqs, int32_t max_pages_per_req,
+                      int32_t *total_q_out)
 {
-    if (!out) return PV_ERR_INVALID_ARG;
-    *out = nullptr;
     pv_status why;
     if (!pool_desc_valid(pool, &why)) return why;
     if (num_q_heads <= 0 || num_q_heads % pool->num_kv_heads != 0) return PV_ERR_INVALID_ARG;
@@ -304,6 +302,21 @@ pv_status build_plan(const pv_pool_desc *pool, int32_t num_q_heads, const int32_
     // rows of q/out are indexed with 64-bit arithmetic in the kernels; the row count itself and
     // the workspace slot numbers stay 32-bit
     if (total_q > INT32_MAX / 2) return PV_ERR_OUT_OF_RANGE;
+    *total_q_out = (int32_t)total_q;
+    return PV_OK;
+}
+
+pv_status build_plan(const pv_pool_desc *pool, int32_t num_q_heads, const int32_t *ctx_lens,
+                     const int32_t *q_lens, int32_t num_reqs, int32_t max_pages_per_req,
+                     const Tuning &tune, pv_plan **out)
+{
+    if (!out) return PV_ERR_INVALID_ARG;
+    *out = nullptr;
+    int32_t total_q = 0;
+    const pv_status ok = check_batch(pool, num_q_heads, ctx_lens, q_lens, num_reqs,
+                                     max_pages_per_req, &total_q);
+    if (ok != PV_OK) return ok;
+    const int32_t G = num_q_heads / pool->num_kv_heads;
 
     pv_plan *plan = new (std::nothrow) pv_plan();
     if (!plan) return PV_ERR_INVALID_ARG;
@@ -312,7 +325,7 @@ pv_status build_plan(const pv_pool_desc *pool, int32_t num_q_heads, const int32_
     plan->group = G;
     plan->num_reqs = num_reqs;
     plan->max_pages_per_req = max_pages_per_req;
-    plan->total_q = (int32_t)total_q;
+    plan->total_q = total_q;
     plan->ctx_lens.assign(ctx_lens, ctx_lens + num_reqs);
     plan->q_lens.assign(q_lens, q_lens + num_reqs);
     plan->q_start.resize(num_reqs);

@@ -73,6 +73,27 @@ static_assert(sizeof(AppendGroup) == 16, "AppendGroup is read by the kernel as 4
 // hint).  Streaming the stores too is slower (first prompts 193 -> 204 us).
 constexpr int64_t kManyRows = 4096;
 
+// Requests with new tokens that the append takes as a kernel argument, and how many one launch takes
+// (2 KB of arguments).  Request i of the launch has the append groups group0[i] .. group0[i + 1] - 1.
+struct AppendReq {
+    int32_t req;
+    int32_t t_begin;  // logical position of its first new token
+    int32_t count;    // new tokens (at least one)
+    int32_t q_row;    // row of the first one in k_new / v_new
+    int32_t group0;
+};
+constexpr int kAppendReqs = 96;
+struct AppendReqs {
+    int32_t n;
+    int32_t groups;  // of all n requests
+    AppendReq r[kAppendReqs];
+};
+// append groups (8-slot runs touched) of `count` new tokens from position t_begin on
+constexpr int64_t append_group_count(int64_t t_begin, int64_t count)
+{
+    return count > 0 ? (t_begin + count + 7) / 8 - t_begin / 8 : 0;
+}
+
 constexpr int kNarrowRows = 16;  // rows per item of the bandwidth-oriented kernel
 constexpr int kWideRows = 128;   // rows per item of the matrix-core kernel (4 waves x 32 rows)
 constexpr int kTileRows = 256;   // rows per item of the 256-row matrix-core kernel (4 waves x 64)
@@ -156,6 +177,10 @@ namespace pv {
 DeviceLists lists_at(const pv_plan *plan, const void *base);
 bool pool_desc_valid(const pv_pool_desc *p, pv_status *why);
 Tuning default_tuning();
+// what every plan demands of a batch; *total_q = its new tokens
+pv_status check_batch(const pv_pool_desc *pool, int32_t num_q_heads, const int32_t *ctx_lens,
+                      const int32_t *q_lens, int32_t num_reqs, int32_t max_pages_per_req,
+                      int32_t *total_q);
 pv_status build_plan(const pv_pool_desc *pool, int32_t num_q_heads, const int32_t *ctx_lens,
                      const int32_t *q_lens, int32_t num_reqs, int32_t max_pages_per_req,
                      const Tuning &tune, pv_plan **out);

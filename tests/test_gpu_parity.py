@@ -71,6 +71,21 @@ def test_one_shot_entry_points_match_planned(oracle):
     assert np.array_equal(planned, one)
 
 
+@pytest.mark.parametrize("reqs,head_dim", [(1, 128), (95, 64), (96, 128), (97, 64), (193, 128)])
+def test_one_shot_append_of_any_number_of_requests(oracle, reqs, head_dim):
+    """The one-shot append takes 96 requests a launch as kernel arguments: counts on both sides of
+    that, requests without new tokens among them, runs that start and end anywhere in a page."""
+    rng = np.random.default_rng(reqs)
+    new = np.where(rng.random(reqs) < 0.2, 0, rng.integers(1, 41, size=reqs))
+    new[-1] = 17
+    b = wl.custom(rng.integers(0, 60, size=reqs), new, num_q_heads=2, num_kv_heads=2,
+                  head_dim=head_dim, dtype="bf16", seed=900 + reqs)
+    case = H.make_case(b, fill="nan")
+    out, kp, vp = H.gpu_run(case, one_shot=True)
+    assert np.array_equal(kp, case.k_pool1.ravel()) and np.array_equal(vp, case.v_pool1.ravel())
+    assert np.abs(H.bits_to_f64(out, b.dtype) - oracle_out(oracle, case)).max() <= H.TOL[b.dtype]
+
+
 def test_one_shot_calls_back_to_back_and_without_room_for_the_lists(oracle, monkeypatch):
     """The one-shot attention call keeps its temporary plan alive until the stream has passed the
     launches (it is freed by a host function queued behind them): several calls in a row without
