@@ -121,8 +121,8 @@ hipError_t launch_kv_append(const pv_plan *plan, const DeviceLists &dl, const vo
                             hipStream_t stream)
 {
     if (plan->append_groups.empty()) return hipSuccess;
-    const bool many =
-        (int64_t)plan->append_groups.size() * plan->pool.num_kv_heads > kManyRows;
+    const bool many = (int64_t)plan->total_q * plan->pool.num_kv_heads * plan->pool.head_dim * 4 >
+                      kStreamBytes;
     auto go = plan->pool.head_dim == 128
                   ? (many ? launch_append_t<128, true> : launch_append_t<128, false>)
                   : (many ? launch_append_t<64, true> : launch_append_t<64, false>);

@@ -202,7 +202,7 @@ __device__ __forceinline__ void lds_dma16(const void *uniform_base, uint32_t lan
 // tile.  A full run is one 16-byte store; a partial one is written element by element so that the
 // other slots keep their contents.  All loads are issued before the first store; a row past the
 // group's last is that last row once more, so that no load depends on a condition.  STREAM: the loads
-// carry the streaming hint (see kManyRows).
+// carry the streaming hint (see kStreamBytes).
 template <int D, int HB, bool STREAM>
 __device__ __forceinline__ void scatter_v_group(const uint16_t *__restrict__ vsrc,
                                                 int64_t row_stride, int count, int heads, int slot0,

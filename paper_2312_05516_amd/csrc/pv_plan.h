@@ -65,13 +65,14 @@ struct AppendGroup {
 };
 static_assert(sizeof(AppendGroup) == 16, "AppendGroup is read by the kernel as 4 int32");
 
-// Append and rotary kernels: with more (append group, head) rows than this the new rows are read with
-// the streaming hint, because they are read once and what is written (K/V pages, rotated queries) is
-// read by the attention that follows: 2600 tokens x 40 heads, append and attention 187.5 -> 185.5 us;
-// 7 K tokens with the rotary embedding see pick_rope.  Below, the rows of a small batch are still in a
-// cache when they come from the kernel before (4 generation steps, 64/8 heads: 26.0 us, 26.3 with the
-// hint).  Streaming the stores too is slower (first prompts 193 -> 204 us).
-constexpr int64_t kManyRows = 4096;
+// Append and rotary kernels: new rows of more bytes than this, the L2 caches of all XCDs together, are
+// read with the streaming hint, because they are read once and what is written (K/V pages, rotated
+// queries) is read by the attention that follows: 53 MB (2600 tokens, 40 heads), append and attention
+// 187.0 -> 184.7 us; 7 K tokens with the rotary embedding see pick_rope.  A smaller batch finds its
+// rows in a cache when they come from the kernel before: 14 MB (2736 tokens, 10 heads) 64.5 us, 67.3
+// with the hint; 4 generation steps with the rotary embedding 26.0 and 26.3.  Streaming the stores too
+// is slower (first prompts 193 -> 204 us).
+constexpr int64_t kStreamBytes = 32 << 20;
 
 // Requests with new tokens that the append takes as a kernel argument, and how many one launch takes
 // (2 KB of arguments).  Request i of the launch has the append groups group0[i] .. group0[i + 1] - 1.

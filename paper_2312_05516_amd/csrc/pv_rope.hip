@@ -159,7 +159,7 @@ static void launch_rope_t(const pv_plan *plan, const DeviceLists &dl, const void
 }
 
 // A large batch: two rows a thread (two heads a workgroup, four where pairs span the halves of a
-// head and half of the threads do a head), and the rows are read with the streaming hint (kManyRows).
+// head and half of the threads do a head), and the rows are read with the streaming hint (kStreamBytes).
 // 8 prompts, 7 K tokens, whole step: 40/40 heads, interleaved pairs 190 -> 181 us (187 with one head,
 // 182 with four; 190 with four and no hint), half pairs 185 -> 177 (185 with two, 178 with eight);
 // 64/8 heads, 4 K tokens, half pairs 95 -> 91.  A small batch keeps one head a workgroup, the more of
@@ -178,8 +178,8 @@ hipError_t launch_rope_append(const pv_plan *plan, const DeviceLists &dl, int st
 {
     if (plan->append_groups.empty()) return hipSuccess;
     const bool f = plan->pool.dtype == PV_F16;
-    const int64_t heads = plan->pool.num_kv_heads + (q_in ? plan->num_q_heads : 0);
-    const bool many = (int64_t)plan->append_groups.size() * heads > kManyRows;
+    const int64_t rows = 2 * plan->pool.num_kv_heads + (q_in ? plan->num_q_heads : 0);
+    const bool many = plan->total_q * rows * plan->pool.head_dim * 2 > kStreamBytes;
     auto go = plan->pool.head_dim == 128
                   ? (f ? pick_rope<F16, 128>(style, many) : pick_rope<BF16, 128>(style, many))
                   : (f ? pick_rope<F16, 64>(style, many) : pick_rope<BF16, 64>(style, many));
