@@ -181,6 +181,18 @@ def test_matrix_core_kernel_block_edges(oracle, monkeypatch, kv_len, head_dim):
     check_case(oracle, H.make_case(b, fill="nan"))
 
 
+@pytest.mark.parametrize("reqs,longest", [(512, 15), (513, 15), (513, 40), (700, 1100)])
+def test_lists_longer_than_the_slots_of_the_narrow_kernel(oracle, reqs, longest):
+    """With more items than run at once an item also touches the page ids of a later one: lists just
+    up to and beyond that, page tables of one column and of more columns than a wavefront has lanes."""
+    rng = np.random.default_rng(reqs + longest)
+    ctx = rng.integers(0, 15, size=reqs)
+    ctx[reqs // 2] = ctx[-1] = longest - 1
+    b = wl.custom(ctx, np.ones(reqs, dtype=np.int64), num_q_heads=1, num_kv_heads=1, head_dim=128,
+                  dtype="f16", seed=1100 + reqs)
+    check_case(oracle, H.make_case(b, fill="nan"))
+
+
 def test_workspace_is_checked():
     import torch
     from paper_2312_05516_amd import binding as pv
