@@ -82,8 +82,12 @@ __global__ __launch_bounds__(256, 3) void attn_wide_kernel(
         const uint16_t *qrow = q + ((int64_t)(it.q_row0 + tok) * num_q_heads + hq) * D;
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
+            // loaded without a condition (a lane without a row reads the request's first one): eight
+            // branches less in front of the page ids; 19 first prompts, 64/8 heads 33.0 -> 32.5 us, 8
+            // longer ones, 40/40 heads 181.7 -> 179.6
+            const u32x4 got = load16(qrow + 16 * ks + 8 * h);
             u32x4 raw = {0u, 0u, 0u, 0u};
-            if (valid) raw = load16(qrow + 16 * ks + 8 * h);
+            if (valid) raw = got;
             raw ^= q_sign;  // a negative scale is applied as |scale| on negated queries
             qf[ks] = as_vec8<T>(raw);
         }
