@@ -98,7 +98,7 @@ constexpr int64_t append_group_count(int64_t t_begin, int64_t count)
 constexpr int kNarrowRows = 16;  // rows per item of the bandwidth-oriented kernel
 constexpr int kWideRows = 128;   // rows per item of the matrix-core kernel (4 waves x 32 rows)
 constexpr int kTileRows = 256;   // rows per item of the 256-row matrix-core kernel (4 waves x 64)
-constexpr int kNarrowSlots = 512;  // workgroups that run at once: 256 CUs x 2 (256 registers a lane)
+constexpr int kNarrowSlots = 512;  // workgroups that run at once: 256 CUs x 2 (212 registers a lane)
 constexpr int kWideSlots = 768;    // 256 CUs x 3 (168 registers a lane, 48 KiB of LDS)
 constexpr int kNarrowKeyNs = 16;   // time of an item per key while the GPU is not full, measured
 constexpr int kWideKeyNs = 31;
