@@ -68,7 +68,8 @@ static_assert(sizeof(AppendGroup) == 16, "AppendGroup is read by the kernel as 4
 // Append and rotary kernels: new rows of more bytes than this, the L2 caches of all XCDs together, are
 // read with the streaming hint, because they are read once and what is written (K/V pages, rotated
 // queries) is read by the attention that follows: 53 MB (2600 tokens, 40 heads), append and attention
-// 187.0 -> 184.7 us; 7 K tokens with the rotary embedding see pick_rope.  A smaller batch finds its
+// 187.0 -> 184.7 us (219 -> 217 with the kernel that writes the rows in front); 7 K tokens with the
+// rotary embedding see pick_rope.  A smaller batch finds its
 // rows in a cache when they come from the kernel before: 14 MB (2736 tokens, 10 heads) 64.5 us, 67.3
 // with the hint; 4 generation steps with the rotary embedding 26.0 and 26.3.  Streaming the stores too
 // is slower (first prompts 193 -> 204 us).
