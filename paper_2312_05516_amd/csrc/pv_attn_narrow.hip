@@ -26,7 +26,16 @@ struct NarrowFrag {
     u32x4 v[D / 16];     // [16-wide block of d]
 };
 
-template <typename T, int D>
+// TWO: the probabilities enter the second product as two 16-bit terms, 95 % of the value and the rest,
+// which is rounded to a twentieth of the error of one term.  With one term the largest probability of
+// a wavefront's keys is exactly 1 and the others are rounded, so that fewer and longer parts of a KV
+// range mean results further from those in 64 bits (56 requests over 2 K keys, 64/8 heads, bf16:
+// 2.117e-3 in three parts, 2.182e-3 whole).  With two the error is that of the result's own rounding
+// (1.66e-3), so lists that are cut into fewer parts (pv_plan::narrow_two_terms) take it: 8 more
+// matrix-core instructions and about 40 of the vector ALU per block, 4 generation steps over 0.7-9 K
+// keys 23.6 -> 23.9 us.  Both terms of a positive probability are positive, so that an infinite V
+// gives infinity and not infinity minus infinity.
+template <typename T, int D, bool TWO>
 __global__ __launch_bounds__(256, 2) void attn_narrow_kernel(
     const WorkItem *__restrict__ items, const uint16_t *__restrict__ q,
     const uint16_t *__restrict__ k_pages, const uint16_t *__restrict__ v_pages,
@@ -177,12 +186,25 @@ __global__ __launch_bounds__(256, 2) void attn_narrow_kernel(
 #pragma unroll
             for (int blk = 0; blk < NB; ++blk) o[blk] *= alpha;
         }
-        u32x4 praw;
+        constexpr float MOST = TWO ? 0.95f : 1.f;
+        u32x4 pmost, prest;
 #pragma unroll
-        for (int jj = 0; jj < 4; ++jj) praw[jj] = T::pack2(x[2 * jj], x[2 * jj + 1]);
-        const vec8 pf = as_vec8<T>(praw);
+        for (int jj = 0; jj < 4; ++jj) {
+            pmost[jj] = T::pack2(x[2 * jj] * MOST, x[2 * jj + 1] * MOST);
+            if constexpr (TWO) {
+                float m0, m1;
+                T::unpack2(pmost[jj], m0, m1);
+                prest[jj] = T::pack2(x[2 * jj] - m0, x[2 * jj + 1] - m1);
+            }
+        }
 #pragma unroll
-        for (int blk = 0; blk < NB; ++blk) o[blk] = T::mfma16(as_vec8<T>(f.v[blk]), pf, o[blk]);
+        for (int blk = 0; blk < NB; ++blk)
+            o[blk] = T::mfma16(as_vec8<T>(f.v[blk]), as_vec8<T>(pmost), o[blk]);
+        if constexpr (TWO) {
+#pragma unroll
+            for (int blk = 0; blk < NB; ++blk)
+                o[blk] = T::mfma16(as_vec8<T>(f.v[blk]), as_vec8<T>(prest), o[blk]);
+        }
     };
 
     int touched = 0;
@@ -348,11 +370,12 @@ static hipError_t launch_narrow_t(const pv_plan *plan, const DeviceLists &dl, co
 {
     const int n = (int)plan->narrow.size();
     if (n == 0) return hipSuccess;
-    hipLaunchKernelGGL((attn_narrow_kernel<T, D>), dim3(n), dim3(256), 0, stream, dl.narrow,
-                       (const uint16_t *)q, (const uint16_t *)k_pages, (const uint16_t *)v_pages,
-                       page_table, plan->max_pages_per_req, plan->num_q_heads,
-                       plan->pool.num_kv_heads, plan->group, scale * kLog2e, (uint16_t *)out, ws_o,
-                       ws_ml);
+    auto kernel = plan->narrow_two_terms ? attn_narrow_kernel<T, D, true>
+                                         : attn_narrow_kernel<T, D, false>;
+    hipLaunchKernelGGL(kernel, dim3(n), dim3(256), 0, stream, dl.narrow, (const uint16_t *)q,
+                       (const uint16_t *)k_pages, (const uint16_t *)v_pages, page_table,
+                       plan->max_pages_per_req, plan->num_q_heads, plan->pool.num_kv_heads,
+                       plan->group, scale * kLog2e, (uint16_t *)out, ws_o, ws_ml);
     return hipGetLastError();
 }
 

@@ -21,7 +21,8 @@
 // block, preceded by a wait that leaves only the newest loads in flight.  Blocks that touch the
 // causal boundary or the end of the sequence take a separate, masked instantiation so the
 // steady-state loop has no branches.  The running maximum is only moved when a new score exceeds
-// it by more than 2^8 (softmax is shift-invariant), which makes rescaling the accumulator rare.
+// it by more than 2^8, or 2^2 in lists that are cut into few parts (softmax is shift-invariant),
+// which makes rescaling the accumulator rare.
 #include <type_traits>
 
 #include "pv_device.h"
@@ -33,7 +34,7 @@ __global__ __launch_bounds__(256, 3) void attn_wide_kernel(
     const WorkItem *__restrict__ items, const uint16_t *__restrict__ q,
     const uint16_t *__restrict__ k_pages, const uint16_t *__restrict__ v_pages,
     const int32_t *__restrict__ page_table, int32_t max_pages, int32_t num_q_heads,
-    int32_t num_kv_heads, int32_t group, float scale_log2e, uint32_t q_sign,
+    int32_t num_kv_heads, int32_t group, float scale_log2e, uint32_t q_sign, float lazy_log2,
     uint16_t *__restrict__ out, float *__restrict__ ws_o, float *__restrict__ ws_ml)
 {
     // Keys per block: 32 for head size 128; 64 for head size 64, where 32 keys are only 8 matrix-core
@@ -171,15 +172,15 @@ __global__ __launch_bounds__(256, 3) void attn_wide_kernel(
 #pragma unroll
             for (int v = t ? 0 : 1; v < 16; ++v) mx = fmaxf(mx, s[t][v]);
         // Lazy rescale: the reference maximum of a row only moves when a new score exceeds it by
-        // more than 2^kLazyLog2 in the scaled domain (exact, because softmax is shift-invariant; the
-        // probabilities just range up to 2^kLazyLog2 instead of 1).  Each lane tests the keys it
+        // more than 2^lazy_log2 in the scaled domain (exact, because softmax is shift-invariant; the
+        // probabilities just range up to 2^lazy_log2 instead of 1).  Each lane tests the keys it
         // holds; only when some lane of the wavefront sees such a score (or has no reference yet)
         // do the two lanes of a row exchange their maxima and the accumulators get rescaled.
-        const bool grow = m_run == -INFINITY || (mx - m_run) * scale_log2e > kLazyLog2;
+        const bool grow = m_run == -INFINITY || (mx - m_run) * scale_log2e > lazy_log2;
         if (__any(grow)) {
             mx = fmaxf(mx, __shfl_xor(mx, 32));
             const float m_new =
-                (m_run == -INFINITY || (mx - m_run) * scale_log2e > kLazyLog2) ? mx : m_run;
+                (m_run == -INFINITY || (mx - m_run) * scale_log2e > lazy_log2) ? mx : m_run;
             const float m_safe = m_new == -INFINITY ? 0.f : m_new;
             const float alpha =
                 m_run == -INFINITY ? 0.f : fast_exp2((m_run - m_safe) * scale_log2e);
@@ -340,8 +341,8 @@ static hipError_t launch_wide_t(const pv_plan *plan, const DeviceLists &dl, cons
     hipLaunchKernelGGL((attn_wide_kernel<T, D>), dim3(n), dim3(256), 0, stream, dl.wide,
                        (const uint16_t *)q, (const uint16_t *)k_pages, (const uint16_t *)v_pages,
                        page_table, plan->max_pages_per_req, plan->num_q_heads,
-                       plan->pool.num_kv_heads, plan->group, c, q_sign, (uint16_t *)out, ws_o,
-                       ws_ml);
+                       plan->pool.num_kv_heads, plan->group, c, q_sign, plan->wide_lazy_log2,
+                       (uint16_t *)out, ws_o, ws_ml);
     return hipGetLastError();
 }
 

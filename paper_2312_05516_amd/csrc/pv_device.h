@@ -17,7 +17,6 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
 constexpr float kLog2e = 1.4426950408889634f;
-constexpr float kLazyLog2 = 8.f;  // the running maximum may lag the true one by this many powers of 2
 
 struct F16 {
     typedef f16x8 vec8;
@@ -69,6 +68,14 @@ struct F16 {
         h2 v = {(_Float16)lo, (_Float16)hi};
         return __builtin_bit_cast(uint32_t, v);
     }
+    // the two values of a packed pair, low half first
+    static __device__ __forceinline__ void unpack2(uint32_t packed, float &lo, float &hi)
+    {
+        typedef _Float16 h2 __attribute__((ext_vector_type(2)));
+        const h2 v = __builtin_bit_cast(h2, packed);
+        lo = (float)v[0];
+        hi = (float)v[1];
+    }
     // acc + low half + high half of a packed pair, in fp32 (one v_dot2 against (1, 1))
     static __device__ __forceinline__ float add_pair(uint32_t packed, float acc)
     {
@@ -119,6 +126,11 @@ struct BF16 {
         typedef __bf16 b2 __attribute__((ext_vector_type(2)));
         b2 v = {(__bf16)lo, (__bf16)hi};
         return __builtin_bit_cast(uint32_t, v);
+    }
+    static __device__ __forceinline__ void unpack2(uint32_t packed, float &lo, float &hi)
+    {
+        lo = __builtin_bit_cast(float, packed << 16);
+        hi = __builtin_bit_cast(float, packed & 0xFFFF0000u);
     }
     static __device__ __forceinline__ float add_pair(uint32_t packed, float acc)
     {

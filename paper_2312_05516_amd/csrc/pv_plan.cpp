@@ -94,51 +94,80 @@ static int64_t item_cost(const WorkItem &w, int rows_per_step)
 // many parts, and longer ones at items more than twice as long as the target's share.
 constexpr int32_t kFewItems = 512;
 
-static void split_items(std::vector<WorkItem> &items, std::vector<CombineItem> &combine,
+// A way to cut a list: every item longer than `longest_whole` (and of at least 2 * min_keys keys) into
+// parts of about `chunk` keys, evened out and rounded up to whole blocks.
+struct Cut {
+    int64_t chunk, longest_whole, min_keys;
+    int64_t parts(int64_t len) const
+    {
+        if (len <= longest_whole || len < 2 * min_keys) return 1;
+        const int64_t n = (len + chunk - 1) / chunk;
+        const int64_t part_len = ((len + n - 1) / n + kKvBlock - 1) / kKvBlock * kKvBlock;
+        return (len + part_len - 1) / part_len;
+    }
+};
+
+// The cut into about `target` equal parts: every item of a list that is shorter than that, only items
+// more than twice as long as a target-th of the keys in a longer one.
+static Cut target_cut(int64_t total_keys, size_t items, int32_t target, const Tuning &tune)
+{
+    Cut c;
+    c.min_keys = tune.min_split_keys;
+    c.chunk = std::max<int64_t>((total_keys + target - 1) / target, c.min_keys);
+    c.chunk = (c.chunk + kKvBlock - 1) / kKvBlock * kKvBlock;
+    c.longest_whole = (int64_t)items >= target ? 2 * c.chunk : c.chunk;
+    return c;
+}
+
+// Returns true where an item gets fewer parts than the cut into about split_target parts gives it.
+static bool split_items(std::vector<WorkItem> &items, std::vector<CombineItem> &combine,
                         int64_t &slots_out, const Tuning &tune, int32_t slots, int32_t key_ns,
                         int32_t head_dim, int64_t max_len = 0)
 {
-    if (items.empty()) return;
+    if (items.empty()) return false;
     if (tune.split_by_hand) slots = 0;
-    const int32_t target = slots ? kFewItems : tune.split_target;
-    int64_t total_keys = 0;
-    for (const WorkItem &w : items) total_keys += w.kv_end - w.kv_begin;
-    int64_t chunk = (total_keys + target - 1) / target;
-    const bool outliers_only = (int64_t)items.size() >= target;
-    if (slots && !outliers_only) chunk = (total_keys + slots - 1) / slots;
-    chunk = std::max<int64_t>(chunk, tune.min_split_keys);
-    chunk = (chunk + kKvBlock - 1) / kKvBlock * kKvBlock;
-    while (slots && !outliers_only) {
-        int64_t parts = 0;
-        for (const WorkItem &w : items) parts += (w.kv_end - w.kv_begin + chunk - 1) / chunk;
-        if (parts <= slots) break;
-        chunk += (chunk / 32 + kKvBlock - 1) / kKvBlock * kKvBlock;
-    }
-    const int64_t longest_whole = !outliers_only ? chunk : slots ? chunk + chunk / 4 : 2 * chunk;
-    auto too_long = [&](int64_t len) { return max_len > 0 && len > max_len; };
-    auto wants_split = [&](const WorkItem &w) {
-        const int64_t len = w.kv_end - w.kv_begin;
-        return too_long(len) || (len > longest_whole && len >= 2 * (int64_t)tune.min_split_keys);
-    };
-    bool any = false;
-    int64_t longest = 0, part_rows = 0;
+    int64_t total_keys = 0, longest = 0;
     for (const WorkItem &w : items) {
-        if (!wants_split(w)) continue;
-        any = true;
-        const int64_t len = w.kv_end - w.kv_begin;
-        longest = std::max(longest, len);
-        part_rows += w.row_count * ((len + chunk - 1) / chunk);
+        total_keys += w.kv_end - w.kv_begin;
+        longest = std::max<int64_t>(longest, w.kv_end - w.kv_begin);
     }
-    if (!any) return;  // the common case of a long list: nothing is copied
-    if (slots && !too_long(longest) &&
-        (longest - longest_whole) * key_ns < 7000 + part_rows * head_dim * 8 / 4000)
-        return;
+    const Cut even = target_cut(total_keys, items.size(), tune.split_target, tune);
+    Cut cut = even;
+    if (slots) {
+        const bool outliers_only = (int64_t)items.size() >= kFewItems;
+        const int32_t target = outliers_only ? kFewItems : slots;
+        int64_t chunk = std::max<int64_t>((total_keys + target - 1) / target, tune.min_split_keys);
+        chunk = (chunk + kKvBlock - 1) / kKvBlock * kKvBlock;
+        while (!outliers_only) {
+            int64_t parts = 0;
+            for (const WorkItem &w : items) parts += (w.kv_end - w.kv_begin + chunk - 1) / chunk;
+            if (parts <= slots) break;
+            chunk += (chunk / 32 + kKvBlock - 1) / kKvBlock * kKvBlock;
+        }
+        cut.chunk = chunk;
+        cut.longest_whole = outliers_only ? chunk + chunk / 4 : chunk;
+        int64_t part_rows = 0;
+        for (const WorkItem &w : items) {
+            const int64_t len = w.kv_end - w.kv_begin;
+            if (cut.parts(len) > 1) part_rows += w.row_count * ((len + chunk - 1) / chunk);
+        }
+        if ((longest - cut.longest_whole) * key_ns < 7000 + part_rows * head_dim * 8 / 4000)
+            cut.longest_whole = longest;
+    }
+    auto too_long = [&](int64_t len) { return max_len > 0 && len > max_len; };
+    bool coarse = false;
+    if (slots && longest > even.longest_whole)
+        for (size_t i = 0; i < items.size() && !coarse; ++i) {
+            const int64_t len = items[i].kv_end - items[i].kv_begin;
+            coarse = cut.parts(len) < even.parts(len);
+        }
+    if (longest <= cut.longest_whole && !too_long(longest))
+        return coarse;  // the common case of a long list: nothing is copied
     std::vector<WorkItem> result;
     result.reserve(items.size() * 2);
     for (const WorkItem &w : items) {
         const int64_t len = w.kv_end - w.kv_begin;
-        int64_t parts = (len + chunk - 1) / chunk;
-        if (len <= longest_whole || len < 2 * (int64_t)tune.min_split_keys) parts = 1;
+        int64_t parts = cut.parts(len);
         if (too_long(len)) parts = std::max(parts, (len + max_len - 1) / max_len);
         if (parts <= 1) {
             result.push_back(w);
@@ -173,6 +202,7 @@ static void split_items(std::vector<WorkItem> &items, std::vector<CombineItem> &
         slots_out += parts * w.row_count;
     }
     items.swap(result);
+    return coarse;
 }
 
 // Order of the work list = order of workgroup dispatch.  Two goals:
@@ -467,9 +497,12 @@ pv_status build_plan(const pv_pool_desc *pool, int32_t num_q_heads, const int32_
         }
     }
     int64_t slots = 0;
-    split_items(plan->narrow, plan->combine, slots, tune, kNarrowSlots, kNarrowKeyNs,
-                pool->head_dim);
-    split_items(plan->wide, plan->combine, slots, tune, kWideSlots, kWideKeyNs, pool->head_dim);
+    plan->narrow_two_terms = split_items(plan->narrow, plan->combine, slots, tune, kNarrowSlots,
+                                         kNarrowKeyNs, pool->head_dim);
+    plan->wide_lazy_log2 = split_items(plan->wide, plan->combine, slots, tune, kWideSlots, kWideKeyNs,
+                                       pool->head_dim)
+                               ? kCoarseLazyLog2
+                               : kLazyLog2;
     split_items(plan->tile256, plan->combine, slots, tune, 0, 0, pool->head_dim,
                 (int64_t)kTileMaxPages * pool->page_size - kKvBlock);
     if (slots > INT32_MAX / 2) {

@@ -104,6 +104,15 @@ constexpr int kWideSlots = 768;    // 256 CUs x 3 (168 registers a lane, 48 KiB 
 constexpr int kNarrowKeyNs = 16;   // time of an item per key while the GPU is not full, measured
 constexpr int kWideKeyNs = 31;
 constexpr int kKvBlock = 32;     // keys per inner step (two pages)
+constexpr float kLazyLog2 = 8.f;  // matrix-core kernels: the reference maximum of a row may lag the
+                                  // true one by this many powers of 2
+// The same for a list of the 128-row kernel that is cut into fewer parts than the cut into about
+// split_target parts gives it.  A probability is rounded to 16 bits unless it is the reference's own,
+// which is exactly 1, and every part has a reference: fewer parts alone would mean results further
+// from those in 64 bits (10 requests, 128 tokens over 1000, 40 heads, bf16: 2.311e-3 in three parts,
+// 2.329e-3 whole).  A reference that follows closer makes up for it (2.284e-3) for some rescaling of
+// the accumulators: 53.9 -> 58.8 us, where the three parts take 85.5.
+constexpr float kCoarseLazyLog2 = 2.f;
 constexpr int kTileMaxPages = 8192;  // page ids an item of the 256-row kernel may span (it keeps
                                      // them in LDS): its KV range is at most 16 times that
 
@@ -154,6 +163,11 @@ struct pv_plan {
     std::vector<pv::AppendGroup> append_groups;
     std::vector<pv::CombineChunk> combine_chunks;
     int64_t partial_slots;  // workspace row slots
+    // Precision of lists that are cut into fewer parts than the cut into about split_target parts
+    // gives them: the narrow kernel's probabilities in two 16-bit terms, and how far the reference
+    // maximum of the 128-row kernel may lag
+    bool narrow_two_terms;
+    float wide_lazy_log2;
     size_t workspace_bytes;
 
     // Host image of everything the kernels read from the plan: the nine arrays above, each at a

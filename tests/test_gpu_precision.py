@@ -1,0 +1,114 @@
+"""Distance of the attention results from attention in 64 bits, over lists that the plan cuts in
+different ways."""
+import math
+
+import numpy as np
+import pytest
+
+from paper_2312_05516_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+MHA, GQA, GQA_D64, PART = (40, 40, 128), (64, 8, 128), (32, 8, 64), (12, 12, 64)
+
+
+def _state(ctx, new, heads, dtype, seed):
+    """Batch with N(0, 1) values in the pool and the queries (the new rows are in the pool too)."""
+    import torch
+    b = wl.custom(ctx, new, num_q_heads=heads[0], num_kv_heads=heads[1], head_dim=heads[2],
+                  dtype=dtype, seed=seed)
+    td = torch.float16 if dtype == "f16" else torch.bfloat16
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(seed)
+
+    def draw(*shape):
+        return torch.empty(shape, dtype=td, device="cuda").normal_(generator=gen)
+    pool = (b.num_pages, b.num_kv_heads * 16 * b.head_dim)
+    return b, draw(b.total_q, b.num_q_heads, b.head_dim), draw(*pool), draw(*pool)
+
+
+def _run(b, q, k, v):
+    import torch
+    from paper_2312_05516_amd import binding as pv
+    desc = pv.pool_desc(b.num_pages, b.num_kv_heads, b.head_dim, b.dtype)
+    plan = pv.plan_create(desc, b.num_q_heads, b.ctx_lens, b.q_lens, b.max_pages_per_req)
+    pv.plan_upload(plan)
+    ws = torch.empty(max(pv.plan_workspace_bytes(plan), 256), dtype=torch.uint8, device="cuda")
+    out = torch.full_like(q, float("nan"))
+    pv.multi_token_paged_attn_planned(plan, q, k, v, torch.from_numpy(b.page_table).cuda(), b.scale,
+                                      out, ws)
+    torch.cuda.synchronize()
+    items = [pv.plan_num_work_items(plan, kind) for kind in (0, 1)]
+    plan.destroy()
+    return out, items
+
+
+def _in_64_bits(b, q, k, v):
+    import torch
+    hkv, d, g = b.num_kv_heads, b.head_dim, b.num_q_heads // b.num_kv_heads
+    kv_, vv = k.view(b.num_pages, hkv, d // 8, 16, 8), v.view(b.num_pages, hkv, 2, d, 8)
+    want = torch.empty(q.shape, dtype=torch.float64, device="cuda")
+    for r in range(b.num_reqs):
+        c, n, s0 = int(b.ctx_lens[r]), int(b.q_lens[r]), int(b.q_start[r])
+        kv = c + n
+        pages = torch.from_numpy(b.page_table[r, :(kv + 15) // 16].astype(np.int64)).cuda()
+        kk = kv_[pages].permute(1, 0, 3, 2, 4).reshape(hkv, -1, d)[:, :kv].double()
+        vd = vv[pages].permute(1, 0, 2, 4, 3).reshape(hkv, -1, d)[:, :kv].double()
+        qq = q[s0:s0 + n].double().view(n, hkv, g, d).permute(1, 2, 0, 3).reshape(hkv, g * n, d)
+        hidden = (torch.arange(kv, device="cuda")[None, :] >
+                  (c + torch.arange(n, device="cuda"))[:, None]).repeat(g, 1)
+        s = torch.bmm(qq.contiguous(), kk.transpose(1, 2).contiguous()) * b.scale
+        o = torch.bmm(torch.softmax(s.masked_fill_(hidden[None], -math.inf), -1), vd.contiguous())
+        want[s0:s0 + n] = o.view(hkv, g, n, d).permute(2, 0, 1, 3).reshape(n, hkv * g, d)
+    return want
+
+
+def _error(out, want):
+    return float((out.double() - want).norm() / want.norm())
+
+
+@pytest.mark.parametrize("ctx,new,heads,dtype", [
+    ([700, 3000, 9000, 5000], [1] * 4, GQA, "bf16"),       # parts that run at once
+    ([1999] * 56, [1] * 56, GQA, "bf16"),                  # whole
+    ([100 + 150 * i for i in range(20)], [1] * 20, GQA, "f16"),
+    ([600, 1999, 2600, 4000] * 20, [1] * 80, GQA, "bf16"),  # only the longest are cut
+    ([150 * i for i in range(24)], [1] * 24, GQA_D64, "f16"),
+    ([1000] * 10, [128] * 10, MHA, "bf16"),                # matrix-core kernel, whole
+    ([1500] * 18, [50] * 18, MHA, "f16"),
+    ([400, 900, 1700, 3000] * 2, [200] * 8, GQA, "bf16"),
+    ([900] * 6, [100] * 6, GQA_D64, "bf16"),
+    ([300 * i for i in range(10)], [60] * 10, PART, "f16"),
+])
+def test_lists_cut_into_fewer_parts_are_no_further_from_64_bits(monkeypatch, ctx, new, heads, dtype):
+    """The probabilities are rounded to 16 bits, except that of each part's reference, so fewer parts
+    alone mean a larger error.  Against the cut into about 1024 parts, on the same values: the bound
+    is that cut's own error (the two share every rounding of inputs, and the sums run over 0.3
+    million elements and more, so that the sampling error of their quotient is below 0.1 %)."""
+    b, q, k, v = _state(ctx, new, heads, dtype, 61)
+    want = _in_64_bits(b, q, k, v)
+    out, items = _run(b, q, k, v)
+    monkeypatch.setenv("PV_SPLIT_TARGET", "1024")
+    even, even_items = _run(b, q, k, v)
+    err, even_err = _error(out, want), _error(even, want)
+    print(f"{items} {err:.4e}, {even_items} {even_err:.4e}", flush=True)
+    assert err <= even_err * 1.001
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+def test_infinite_values_stay_infinite(dtype):
+    """Generation steps over enough requests that the list is left whole (two-term probabilities): a
+    V of plus or minus infinity at a visible key gives that infinity in its dimension, and no NaN."""
+    import torch
+    b, q, k, v = _state([1999] * 56, [1] * 56, GQA, dtype, 67)
+    clean, _ = _run(b, q, k, v)
+    vv = v.view(b.num_pages, 8, 2, 128, 8)
+    for r, d, sign in ((0, 3, 1.0), (17, 100, -1.0), (55, 127, 1.0)):
+        page = int(b.page_table[r, 5])  # keys 80-95
+        vv[page, :, 1, d, 2] = sign * math.inf
+        out, items = _run(b, q, k, v)
+        got = out[int(b.q_start[r])]
+        assert bool((got[:, d] == sign * math.inf).all()), (items, got[:, d])
+        vv[page, :, 1, d, 2] = 0.0
+        keep = torch.ones(128, dtype=torch.bool, device="cuda")
+        keep[d] = False
+        assert torch.equal(got[:, keep], clean[int(b.q_start[r])][:, keep])
