@@ -253,10 +253,12 @@ pv_status pv_plan_kernel_ms(pv_plan *plan, int32_t kind, float *ms);
  *     pv_attn_workspace_bytes(...) bytes, the temporary plan's lists go behind the partial results
  *     in it: nothing is allocated, the lists are copied with hipMemcpyAsync on `stream`, the
  *     library does not synchronise (the runtime performs a copy out of pageable host memory, as
- *     this one is, synchronously), and the temporary plan is freed when the call returns, or, in a
- *     stream capture, by a host function behind the launches.  With a smaller workspace that still
- *     covers the partial results, the lists go to temporary device memory and the call waits for
- *     the stream before freeing it.
+ *     this one is, synchronously), and the temporary plan is freed when the call returns.  With a
+ *     smaller workspace that still covers the partial results, the lists go to temporary device
+ *     memory and the call waits for the stream before freeing it.
+ *     In a stream capture the lists are stored in the workspace by kernels that hold them as
+ *     arguments, so that every replay of the graph stores its own and reads no host memory; a
+ *     workspace without room for them is then PV_ERR_WORKSPACE, and nothing is queued.
  *   pv_kv_append has no buffer argument and needs no plan: the positions travel as kernel
  *     arguments.  It waits for the stream.
  */

@@ -1,6 +1,7 @@
 // C ABI entry points that touch the GPU: plan upload, the planned launches and the one-shot forms.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdlib>
 #include <cstring>
@@ -55,6 +56,39 @@ static pv_status ensure_ready(const pv_plan *plan)
     return PV_OK;
 }
 
+// Lists stored by kernels that carry them as arguments, for a launch that may run again after its
+// plan is gone: a captured graph keeps its own copy of the arguments of each of its kernels.
+struct ListPiece {
+    uint32_t words[960];  // 3840 bytes: the arguments of a kernel are limited to 4 KiB
+};
+constexpr size_t kPieceBytes = sizeof(ListPiece);
+typedef uint32_t list_u32x4 __attribute__((ext_vector_type(4)));
+
+__global__ __launch_bounds__(256) void store_piece_kernel(const ListPiece piece, list_u32x4 *dst,
+                                                          int32_t n)
+{
+    const int i = (int)threadIdx.x;
+    if (i < n)
+        dst[i] = list_u32x4{piece.words[4 * i], piece.words[4 * i + 1], piece.words[4 * i + 2],
+                            piece.words[4 * i + 3]};
+}
+
+// the plan's image (a whole number of 256-byte lines) to `buf`
+static hipError_t store_lists(const pv_plan *plan, void *buf, hipStream_t stream)
+{
+    ListPiece piece;
+    for (size_t at = 0; at < plan->image.size(); at += kPieceBytes) {
+        const size_t bytes = std::min(kPieceBytes, plan->image.size() - at);
+        std::memcpy(piece.words, plan->image.data() + at, bytes);
+        hipLaunchKernelGGL(store_piece_kernel, dim3(1), dim3(256), 0, stream, piece,
+                           reinterpret_cast<list_u32x4 *>(static_cast<unsigned char *>(buf) + at),
+                           (int32_t)(bytes / 16));
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
 // Brackets one kernel launch with the plan's events when timing is on.
 struct KernelTimer {
     pv_plan *plan;
@@ -104,6 +138,18 @@ pv_status pv_plan_kernel_ms(pv_plan *plan, int32_t kind, float *ms)
     return PV_OK;
 }
 
+// From here on the plan's launches take its lists from `device_buf` on device `dev`.
+static void lists_live_at(pv_plan *plan, void *device_buf, int dev)
+{
+    if (plan->d_owned && plan->d_owned != device_buf) {
+        (void)hipFree(plan->d_owned);
+        plan->d_owned = nullptr;
+    }
+    plan->dev = pv::lists_at(plan, device_buf);
+    plan->device = dev;
+    plan->uploaded = true;
+}
+
 pv_status pv_plan_upload_to(pv_plan *plan, void *device_buf, size_t bytes, void *stream)
 {
     if (!plan || !device_buf) return PV_ERR_INVALID_ARG;
@@ -114,13 +160,7 @@ pv_status pv_plan_upload_to(pv_plan *plan, void *device_buf, size_t bytes, void 
     if (hipMemcpyAsync(device_buf, plan->image.data(), plan->image.size(), hipMemcpyHostToDevice,
                        static_cast<hipStream_t>(stream)) != hipSuccess)
         return PV_ERR_HIP;
-    if (plan->d_owned && plan->d_owned != device_buf) {
-        (void)hipFree(plan->d_owned);
-        plan->d_owned = nullptr;
-    }
-    plan->dev = pv::lists_at(plan, device_buf);
-    plan->device = dev;
-    plan->uploaded = true;
+    lists_live_at(plan, device_buf, dev);
     return PV_OK;
 }
 
@@ -397,17 +437,39 @@ pv_status pv_multi_token_paged_attn(const pv_pool_desc *pool, int32_t num_q_head
     }
     // The caller's workspace holds the partial results first and, behind them, the plan's lists
     // when it is large enough for both (pv_attn_workspace_bytes is): then nothing is allocated
-    // and the library does not wait; the temporary plan, whose host image the copy of the lists
-    // reads, is freed by a host function queued on the stream behind the launches.  Otherwise:
-    // temporary device memory and a wait.
+    // and the library does not wait.  Otherwise: temporary device memory and a wait.
     const size_t ws_part = pv::align_up(plan->workspace_bytes, 256);
     const bool ws_ok = workspace && (reinterpret_cast<uintptr_t>(workspace) & 255u) == 0;
     if (plan->workspace_bytes > 0 && (!ws_ok || workspace_bytes < plan->workspace_bytes)) {
         pv_plan_destroy(plan);
         return PV_ERR_WORKSPACE;
     }
+    const bool room = ws_ok && workspace_bytes >= ws_part + plan->image.size();
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(static_cast<hipStream_t>(stream), &capture) == hipSuccess &&
+        capture != hipStreamCaptureStatusNone) {
+        // The graph may run any number of times, long after this call: it must not read the plan,
+        // and nothing can be allocated or waited for here.
+        int dev = -1;
+        if (!room)
+            s = PV_ERR_WORKSPACE;
+        else
+            s = attn_args_ok(plan, q, k_pages, v_pages, page_table, scale, out);
+        if (s == PV_OK &&
+            (hipGetDevice(&dev) != hipSuccess ||
+             pv::store_lists(plan, static_cast<unsigned char *>(workspace) + ws_part,
+                             static_cast<hipStream_t>(stream)) != hipSuccess))
+            s = PV_ERR_HIP;
+        if (s == PV_OK) {
+            lists_live_at(plan, static_cast<unsigned char *>(workspace) + ws_part, dev);
+            s = pv_multi_token_paged_attn_planned(plan, q, k_pages, v_pages, page_table, scale, out,
+                                                  workspace, workspace_bytes, stream);
+        }
+        pv_plan_destroy(plan);
+        return s;
+    }
     bool wait = false;
-    if (ws_ok && workspace_bytes >= ws_part + plan->image.size()) {
+    if (room) {
         s = pv_plan_upload_to(plan, static_cast<unsigned char *>(workspace) + ws_part,
                               workspace_bytes - ws_part, stream);
     } else {
@@ -418,22 +480,11 @@ pv_status pv_multi_token_paged_attn(const pv_pool_desc *pool, int32_t num_q_head
         s = pv_multi_token_paged_attn_planned(plan, q, k_pages, v_pages, page_table, scale, out,
                                               workspace, workspace_bytes, stream);
     if (s == PV_OK && !wait) {
-        // Outside a capture the plan can go at once: a copy out of pageable memory, as the plan's
-        // image is, is performed synchronously, and the launches hold their arguments.  (A host
-        // function behind the launches costs about 20 us of host time.)
-        hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-        if (hipStreamIsCapturing(static_cast<hipStream_t>(stream), &capture) == hipSuccess &&
-            capture == hipStreamCaptureStatusNone) {
-            pv_plan_destroy(plan);
-            return PV_OK;
-        }
-        // under capture the copy runs later.  The plan holds no device memory and no events here: freeing it is a plain delete,
-        // which a host function may do (it must not call into the runtime)
-        if (hipLaunchHostFunc(static_cast<hipStream_t>(stream),
-                              [](void *p) { delete static_cast<pv_plan *>(p); },
-                              plan) == hipSuccess)
-            return PV_OK;
-        wait = true;  // could not queue it: wait instead
+        // The plan can go at once: a copy out of pageable memory, as the plan's image is, is performed
+        // synchronously, and the launches hold their arguments.  (A host function behind the launches
+        // costs about 20 us of host time.)
+        pv_plan_destroy(plan);
+        return PV_OK;
     }
     if (s != PV_OK) wait = true;  // a copy that reads the plan's image may have been queued
     if (wait && hipStreamSynchronize(static_cast<hipStream_t>(stream)) != hipSuccess && s == PV_OK)

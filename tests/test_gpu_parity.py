@@ -452,6 +452,58 @@ def test_graph_replay_matches_eager(oracle, kernels, monkeypatch):
     plan.destroy()
 
 
+@pytest.mark.parametrize("requests", [3, 300])
+def test_one_shot_attention_captured_into_a_graph(oracle, requests):
+    """The one-shot attention call under capture: its temporary plan is gone when the graph runs, so
+    every replay has to bring its own lists.  One piece of them and several (300 requests); replays
+    with the workspace overwritten and other one-shot calls (their plans reuse the freed host memory)
+    in between.  Without room for the lists the call is refused and the capture stays usable."""
+    import torch
+    from paper_2312_05516_amd import binding as pv
+    rng = np.random.default_rng(requests)
+    b = wl.custom(rng.integers(0, 900 if requests == 3 else 30, size=requests),
+                  rng.integers(1, 60 if requests == 3 else 5, size=requests), num_q_heads=4,
+                  num_kv_heads=2, head_dim=128, dtype="f16", seed=63)
+    case = H.make_case(b, fill="nan")
+    planned, kpool, vpool = H.gpu_run(case)
+    other = wl.custom(rng.integers(0, 30, size=requests), rng.integers(1, 60, size=requests),
+                      num_q_heads=4, num_kv_heads=2, head_dim=128, dtype="f16", seed=64)
+    kp = H.to_dev_bits(kpool.reshape(case.k_pool0.shape), b.dtype)
+    vp = H.to_dev_bits(vpool.reshape(case.v_pool0.shape), b.dtype)
+    q = H.to_dev_bits(case.q, b.dtype)
+    table = torch.from_numpy(b.page_table).cuda()
+    desc = pv.pool_desc(b.num_pages, b.num_kv_heads, b.head_dim, b.dtype)
+    ws = torch.empty(pv.attn_workspace_bytes(desc, 4, b.num_reqs, b.total_q, int(b.kv_lens.max())),
+                     dtype=torch.uint8, device="cuda")
+    out = torch.zeros_like(q)
+    plan = pv.plan_create(desc, 4, b.ctx_lens, b.q_lens, b.max_pages_per_req)
+    lists = pv.plan_device_bytes(plan)
+    small = torch.empty((pv.plan_workspace_bytes(plan) + 255) // 256 * 256 + lists - 256,
+                        dtype=torch.uint8, device="cuda")
+    plan.destroy()
+    assert (lists > 2 * 3840) == (requests == 300)
+
+    def call(space):
+        pv.multi_token_paged_attn(desc, 4, q, kp, vp, table, b.max_pages_per_req, b.ctx_lens, b.q_lens,
+                                  b.q_start, b.scale, out, space)
+
+    g = torch.cuda.CUDAGraph()
+    cap = torch.cuda.Stream()
+    with torch.cuda.graph(g, stream=cap):
+        with pytest.raises(pv.PvError):
+            call(small)
+        call(ws)
+    for rep in range(4):
+        out.zero_()
+        ws.fill_(0xA5)
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(H.from_dev_bits(out), planned), rep
+        H.gpu_run(H.make_case(other), one_shot=True)
+        torch.cuda.synchronize()
+
+
 @pytest.mark.parametrize("scale", [-0.25, 0.0, 3.0])
 def test_unusual_scales(oracle, scale):
     """`scale` is any finite multiplier: negative (the kernels negate the queries), zero (uniform
