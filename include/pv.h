@@ -252,8 +252,9 @@ pv_status pv_plan_kernel_ms(pv_plan *plan, int32_t kind, float *ms);
  *   pv_multi_token_paged_attn: when `workspace` (256-byte aligned) holds at least
  *     pv_attn_workspace_bytes(...) bytes, the temporary plan's lists go behind the partial results
  *     in it: nothing is allocated, the lists are copied with hipMemcpyAsync on `stream`, the
- *     library does not synchronise (the runtime performs a copy out of pageable host memory, as
- *     this one is, synchronously), and the temporary plan is freed when the call returns.  With a
+ *     library does not synchronise.  The temporary plan is freed when the call returns: the
+ *     runtime has then read the lists, which lie in pageable host memory.  (Where the program has
+ *     registered that memory, a host function behind the launches frees the plan.)  With a
  *     smaller workspace that still covers the partial results, the lists go to temporary device
  *     memory and the call waits for the stream before freeing it.
  *     In a stream capture the lists are stored in the workspace by kernels that hold them as

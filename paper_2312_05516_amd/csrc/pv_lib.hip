@@ -56,6 +56,22 @@ static pv_status ensure_ready(const pv_plan *plan)
     return PV_OK;
 }
 
+// Whether the runtime knows nothing of these bytes of host memory (they are neither pinned nor
+// registered): hipMemcpyAsync out of such memory is synchronous to the host.
+static bool pageable(const unsigned char *p, size_t bytes)
+{
+    for (const void *at : {static_cast<const void *>(p), static_cast<const void *>(p + bytes - 1)}) {
+        hipPointerAttribute_t attr;
+        const hipError_t e = hipPointerGetAttributes(&attr, at);
+        if (e == hipErrorInvalidValue) {
+            (void)hipGetLastError();  // "not one of ours": the next launch must not report it
+            continue;
+        }
+        if (e != hipSuccess || attr.type != hipMemoryTypeUnregistered) return false;
+    }
+    return true;
+}
+
 // Lists stored by kernels that carry them as arguments, for a launch that may run again after its
 // plan is gone: a captured graph keeps its own copy of the arguments of each of its kernels.
 struct ListPiece {
@@ -480,11 +496,21 @@ pv_status pv_multi_token_paged_attn(const pv_pool_desc *pool, int32_t num_q_head
         s = pv_multi_token_paged_attn_planned(plan, q, k_pages, v_pages, page_table, scale, out,
                                               workspace, workspace_bytes, stream);
     if (s == PV_OK && !wait) {
-        // The plan can go at once: a copy out of pageable memory, as the plan's image is, is performed
-        // synchronously, and the launches hold their arguments.  (A host function behind the launches
-        // costs about 20 us of host time.)
-        pv_plan_destroy(plan);
-        return PV_OK;
+        // A copy out of pageable memory has read its source when it returns, and the launches hold
+        // their arguments: the plan can go.  If a program has registered the memory that its heap
+        // gave us, the copy may still have to run: then the plan goes when the stream has passed it.
+        // (Not always so, because a host function costs about 20 us of host time.)
+        if (pv::pageable(plan->image.data(), plan->image.size())) {
+            pv_plan_destroy(plan);
+            return PV_OK;
+        }
+        // the plan holds no device memory and no events here: freeing it is a plain delete, which a
+        // host function may do (it must not call into the runtime)
+        if (hipLaunchHostFunc(static_cast<hipStream_t>(stream),
+                              [](void *p) { delete static_cast<pv_plan *>(p); },
+                              plan) == hipSuccess)
+            return PV_OK;
+        wait = true;  // could not queue it: wait instead
     }
     if (s != PV_OK) wait = true;  // a copy that reads the plan's image may have been queued
     if (wait && hipStreamSynchronize(static_cast<hipStream_t>(stream)) != hipSuccess && s == PV_OK)

@@ -87,38 +87,50 @@ def test_one_shot_append_of_any_number_of_requests(oracle, reqs, head_dim):
 
 
 def test_one_shot_calls_back_to_back_and_without_room_for_the_lists(oracle, monkeypatch):
-    """The one-shot attention call keeps its temporary plan alive until the stream has passed the
-    launches (it is freed by a host function queued behind them): several calls in a row without
-    a wait in between, each into its own output, then once more with no workspace at all (the
-    lists then go to temporary device memory and the call waits).  All give the planned result."""
+    """Several one-shot attention calls in a row behind a kernel that keeps the stream busy, without a
+    wait in between: the temporary plan of each is gone when its kernels start, and the next call's,
+    of a batch with other lengths, may lie in the same host memory.  Then once more with no workspace
+    at all (the lists then go to temporary device memory and the call waits).  All give their
+    batch's planned result."""
     import torch
     from paper_2312_05516_amd import binding as pv
     monkeypatch.setenv("PV_SPLIT_TARGET", "1")  # no split KV ranges: no partial results to hold
-    b = wl.custom([300, 17, 900, 0], [33, 1, 140, 64], num_q_heads=8, num_kv_heads=2, head_dim=128,
-                  dtype="bf16", seed=47)
-    case = H.make_case(b)
-    planned, kpool, vpool = H.gpu_run(case)
-    desc = pv.pool_desc(b.num_pages, b.num_kv_heads, b.head_dim, b.dtype)
-    kp, vp = H.to_dev_bits(kpool.reshape(case.k_pool0.shape), b.dtype), \
-        H.to_dev_bits(vpool.reshape(case.v_pool0.shape), b.dtype)  # pools after the append
-    q = H.to_dev_bits(case.q, b.dtype)
-    table = torch.from_numpy(b.page_table).cuda()
-    nbytes = pv.attn_workspace_bytes(desc, b.num_q_heads, b.num_reqs, b.total_q, int(b.kv_lens.max()))
-    outs, spaces = [], []
-    for i in range(4):
-        outs.append(torch.full_like(q, float("nan")))
-        spaces.append(torch.empty(nbytes, dtype=torch.uint8, device="cuda"))
-    for i in range(4):
+    calls = []
+    for i, (ctx, new) in enumerate([([300, 17, 900, 0], [33, 1, 140, 64]),
+                                    ([17, 900, 0, 300], [1, 64, 140, 33]),
+                                    ([0, 301, 33, 860], [140, 33, 64, 1]),
+                                    ([900, 0, 300, 16], [64, 140, 33, 2])]):
+        b = wl.custom(ctx, new, num_q_heads=8, num_kv_heads=2, head_dim=128, dtype="bf16",
+                      seed=47 + i)
+        case = H.make_case(b)
+        planned, kpool, vpool = H.gpu_run(case)
+        desc = pv.pool_desc(b.num_pages, b.num_kv_heads, b.head_dim, b.dtype)
+        q = H.to_dev_bits(case.q, b.dtype)
+        nbytes = pv.attn_workspace_bytes(desc, b.num_q_heads, b.num_reqs, b.total_q,
+                                         int(b.kv_lens.max()))
+        calls.append((b, planned, desc, q, H.to_dev_bits(kpool.reshape(case.k_pool0.shape), b.dtype),
+                      H.to_dev_bits(vpool.reshape(case.v_pool0.shape), b.dtype),
+                      torch.from_numpy(b.page_table).cuda(), torch.full_like(q, float("nan")),
+                      torch.empty(nbytes, dtype=torch.uint8, device="cuda")))
+
+    def call(i, out, space):
+        b, _, desc, q, kp, vp, table, _, _ = calls[i]
         pv.multi_token_paged_attn(desc, b.num_q_heads, q, kp, vp, table, b.max_pages_per_req,
-                                  b.ctx_lens, b.q_lens, b.q_start, b.scale, outs[i], spaces[i])
+                                  b.ctx_lens, b.q_lens, b.q_start, b.scale, out, space)
+
+    busy = torch.randn(4096, 4096, device="cuda")
     torch.cuda.synchronize()
-    for o in outs:
-        assert np.array_equal(H.from_dev_bits(o), planned)
-    last = torch.full_like(q, float("nan"))
-    pv.multi_token_paged_attn(desc, b.num_q_heads, q, kp, vp, table, b.max_pages_per_req,
-                              b.ctx_lens, b.q_lens, b.q_start, b.scale, last, None)
+    for _ in range(8):
+        busy = busy @ busy * 1e-2
+    for i in range(4):
+        call(i, calls[i][7], calls[i][8])
     torch.cuda.synchronize()
-    assert np.array_equal(H.from_dev_bits(last), planned)
+    for c in calls:
+        assert np.array_equal(H.from_dev_bits(c[7]), c[1])
+    last = torch.full_like(calls[0][3], float("nan"))
+    call(0, last, None)
+    torch.cuda.synchronize()
+    assert np.array_equal(H.from_dev_bits(last), calls[0][1])
 
 
 def test_empty_batch_is_a_no_op():
