@@ -21,20 +21,21 @@
 // block, preceded by a wait that leaves only the newest loads in flight.  Blocks that touch the
 // causal boundary or the end of the sequence take a separate, masked instantiation so the
 // steady-state loop has no branches.  The running maximum is only moved when a new score exceeds
-// it by more than 2^8, or 2^2 in lists that are cut into few parts (softmax is shift-invariant),
-// which makes rescaling the accumulator rare.
+// it by more than 2^8 (softmax is shift-invariant), which makes rescaling the accumulator rare.
 #include <type_traits>
 
 #include "pv_device.h"
 
 namespace pv {
 
-template <typename T, int D>
+// RENEW: some item has renew_blocks.  Lists without any keep an instantiation of their own (with the
+// test for it in the loop they take 1 % longer: 64 mixed requests, 64/8 heads, 270.5 -> 273.1 us).
+template <typename T, int D, bool RENEW>
 __global__ __launch_bounds__(256, 3) void attn_wide_kernel(
     const WorkItem *__restrict__ items, const uint16_t *__restrict__ q,
     const uint16_t *__restrict__ k_pages, const uint16_t *__restrict__ v_pages,
     const int32_t *__restrict__ page_table, int32_t max_pages, int32_t num_q_heads,
-    int32_t num_kv_heads, int32_t group, float scale_log2e, uint32_t q_sign, float lazy_log2,
+    int32_t num_kv_heads, int32_t group, float scale_log2e, uint32_t q_sign,
     uint16_t *__restrict__ out, float *__restrict__ ws_o, float *__restrict__ ws_ml)
 {
     // Keys per block: 32 for head size 128; 64 for head size 64, where 32 keys are only 8 matrix-core
@@ -137,10 +138,11 @@ __global__ __launch_bounds__(256, 3) void attn_wide_kernel(
 #pragma unroll
         for (int v = 0; v < 16; ++v) o[blk][v] = 0.f;
     float m_run = -INFINITY;  // reference maximum of the RAW scores (before scaling)
+    float m_top = -INFINITY;  // the highest reference so far
     float l_run = 0.f;        // this lane's share of the running sum
     float mc = 0.f;           // m_run in the exp2 domain (0 while there is no reference yet)
 
-    auto compute_block = [&](const unsigned char *sb, int kb0, auto masked_tag) {
+    auto compute_block = [&](const unsigned char *sb, int kb0, bool renew, auto masked_tag) {
         constexpr bool MASKED = decltype(masked_tag)::value;
         f32x16 s[NT];
 #pragma unroll
@@ -172,15 +174,21 @@ __global__ __launch_bounds__(256, 3) void attn_wide_kernel(
 #pragma unroll
             for (int v = t ? 0 : 1; v < 16; ++v) mx = fmaxf(mx, s[t][v]);
         // Lazy rescale: the reference maximum of a row only moves when a new score exceeds it by
-        // more than 2^lazy_log2 in the scaled domain (exact, because softmax is shift-invariant; the
-        // probabilities just range up to 2^lazy_log2 instead of 1).  Each lane tests the keys it
+        // more than 2^kLazyLog2 in the scaled domain (exact, because softmax is shift-invariant; the
+        // probabilities just range up to 2^kLazyLog2 instead of 1).  Each lane tests the keys it
         // holds; only when some lane of the wavefront sees such a score (or has no reference yet)
         // do the two lanes of a row exchange their maxima and the accumulators get rescaled.
-        const bool grow = m_run == -INFINITY || (mx - m_run) * scale_log2e > lazy_log2;
+        // A renewal takes the block's own maximum as the reference also where it is lower (by no more
+        // than 2^kRenewLog2 than any reference so far, so that nothing grows by more than that): see
+        // WorkItem::renew_blocks.
+        const float base = renew ? m_top : m_run;
+        const float margin = renew ? -kRenewLog2 : kLazyLog2;
+        const bool grow = m_run == -INFINITY || (mx - base) * scale_log2e > margin;
         if (__any(grow)) {
             mx = fmaxf(mx, __shfl_xor(mx, 32));
             const float m_new =
-                (m_run == -INFINITY || (mx - m_run) * scale_log2e > lazy_log2) ? mx : m_run;
+                (m_run == -INFINITY || (mx - base) * scale_log2e > margin) ? mx : m_run;
+            if constexpr (RENEW) m_top = fmaxf(m_top, m_new);
             const float m_safe = m_new == -INFINITY ? 0.f : m_new;
             const float alpha =
                 m_run == -INFINITY ? 0.f : fast_exp2((m_run - m_safe) * scale_log2e);
@@ -248,16 +256,19 @@ __global__ __launch_bounds__(256, 3) void attn_wide_kernel(
         __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, 0));
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
+    int to_renewal = it.renew_blocks ? it.renew_blocks + 1 : 0;  // 0: counts down and never gets there
     for (int b = 0; b < nblocks; ++b) {
         const bool more = b + 2 < nblocks;
         if (more) dma_block(b + 2, id0, id1);  // its stage held block b-1: everyone is done with it
         page_ids(b + 3, id0, id1);
         const int kb0 = it.kv_begin + BK * b;
+        const bool renew = RENEW && --to_renewal == 0;
+        if (renew) to_renewal = it.renew_blocks;
         if (kb0 < wave_end) {
             if (kb0 + BK <= unmasked_end)
-                compute_block(smem[b % STAGES], kb0, std::false_type{});
+                compute_block(smem[b % STAGES], kb0, renew, std::false_type{});
             else
-                compute_block(smem[b % STAGES], kb0, std::true_type{});
+                compute_block(smem[b % STAGES], kb0, renew, std::true_type{});
         }
         // block b+1 (issued one iteration ago) must have landed before the barrier publishes it;
         // this iteration's own copies may stay in flight.  This wavefront's LDS reads of block b
@@ -338,11 +349,12 @@ static hipError_t launch_wide_t(const pv_plan *plan, const DeviceLists &dl, cons
     const int n = (int)plan->wide.size();
     const float c = (scale < 0.f ? -scale : scale) * kLog2e;
     const uint32_t q_sign = scale < 0.f ? 0x80008000u : 0u;
-    hipLaunchKernelGGL((attn_wide_kernel<T, D>), dim3(n), dim3(256), 0, stream, dl.wide,
-                       (const uint16_t *)q, (const uint16_t *)k_pages, (const uint16_t *)v_pages,
+    auto kernel = plan->wide_renews ? attn_wide_kernel<T, D, true> : attn_wide_kernel<T, D, false>;
+    hipLaunchKernelGGL(kernel, dim3(n), dim3(256), 0, stream, dl.wide, (const uint16_t *)q,
+                       (const uint16_t *)k_pages, (const uint16_t *)v_pages,
                        page_table, plan->max_pages_per_req, plan->num_q_heads,
-                       plan->pool.num_kv_heads, plan->group, c, q_sign, plan->wide_lazy_log2,
-                       (uint16_t *)out, ws_o, ws_ml);
+                       plan->pool.num_kv_heads, plan->group, c, q_sign, (uint16_t *)out, ws_o,
+                       ws_ml);
     return hipGetLastError();
 }
 

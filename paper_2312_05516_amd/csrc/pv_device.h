@@ -17,6 +17,7 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
 constexpr float kLog2e = 1.4426950408889634f;
+constexpr float kRenewLog2 = 4.f;  // how far below the highest one a renewed reference may lie
 
 struct F16 {
     typedef f16x8 vec8;

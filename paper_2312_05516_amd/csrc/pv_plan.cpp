@@ -98,12 +98,15 @@ constexpr int32_t kFewItems = 512;
 // parts of about `chunk` keys, evened out and rounded up to whole blocks.
 struct Cut {
     int64_t chunk, longest_whole, min_keys;
-    int64_t parts(int64_t len) const
+    int32_t parts(int64_t len) const
     {
-        if (len <= longest_whole || len < 2 * min_keys) return 1;
+        return len <= longest_whole || len < 2 * min_keys ? 1 : ((int32_t)len - 1) / part_len(len) + 1;
+    }
+    // length of the parts of an item that is cut
+    int32_t part_len(int64_t len) const
+    {
         const uint32_t keys = (uint32_t)len, n = (keys - 1) / (uint32_t)chunk + 1;
-        const uint32_t part_len = ((keys - 1) / n + kKvBlock) / kKvBlock * kKvBlock;
-        return (keys - 1) / part_len + 1;
+        return (int32_t)(((keys - 1) / n + kKvBlock) / kKvBlock * kKvBlock);
     }
 };
 
@@ -119,13 +122,12 @@ static Cut target_cut(int64_t total_keys, size_t items, int32_t target, const Tu
     return c;
 }
 
-// Returns how many times the parts of this cut the cut into about split_target parts would have, above
-// 1 if it has more of any item.
-static float split_items(std::vector<WorkItem> &items, std::vector<CombineItem> &combine,
+// Returns true where an item gets fewer parts than the cut into about split_target parts gives it.
+static bool split_items(std::vector<WorkItem> &items, std::vector<CombineItem> &combine,
                         int64_t &slots_out, const Tuning &tune, int32_t slots, int32_t key_ns,
                         int32_t head_dim, int64_t max_len = 0)
 {
-    if (items.empty()) return 1.f;
+    if (items.empty()) return false;
     if (tune.split_by_hand) slots = 0;
     int64_t total_keys = 0, longest = 0;
     for (const WorkItem &w : items) {
@@ -156,22 +158,18 @@ static float split_items(std::vector<WorkItem> &items, std::vector<CombineItem> 
             cut.longest_whole = longest;
     }
     auto too_long = [&](int64_t len) { return max_len > 0 && len > max_len; };
-    float coarse = 1.f;
+    // items that get fewer parts than the even cut gives them
+    bool fewer = false;
     if (longest > even.longest_whole &&
-        (cut.chunk > even.chunk || cut.longest_whole > even.longest_whole)) {
-        int64_t parts = 0, even_parts = 0;
-        bool fewer = false;
-        for (const WorkItem &w : items) {
+        (cut.chunk > even.chunk || cut.longest_whole > even.longest_whole))
+        for (WorkItem &w : items) {
             const int64_t len = w.kv_end - w.kv_begin;
-            const int64_t mine = cut.parts(len), other = even.parts(len);
-            parts += mine;
-            even_parts += other;
-            fewer = fewer || mine < other;
+            if (even.parts(len) <= cut.parts(len)) continue;
+            fewer = true;
+            w.renew_blocks = std::max(even.part_len(len) / (head_dim == 128 ? 32 : 64), 1);
         }
-        if (fewer) coarse = std::max((float)even_parts / (float)parts, 1.001f);
-    }
     if (longest <= cut.longest_whole && !too_long(longest))
-        return coarse;  // the common case of a long list: nothing is copied
+        return fewer;  // the common case of a long list: nothing is copied
     std::vector<WorkItem> result;
     result.reserve(items.size() * 2);
     for (const WorkItem &w : items) {
@@ -211,7 +209,7 @@ static float split_items(std::vector<WorkItem> &items, std::vector<CombineItem> 
         slots_out += parts * w.row_count;
     }
     items.swap(result);
-    return coarse;
+    return fewer;
 }
 
 // Order of the work list = order of workgroup dispatch.  Two goals:
@@ -507,10 +505,9 @@ pv_status build_plan(const pv_pool_desc *pool, int32_t num_q_heads, const int32_
     }
     int64_t slots = 0;
     plan->narrow_two_terms = split_items(plan->narrow, plan->combine, slots, tune, kNarrowSlots,
-                                         kNarrowKeyNs, pool->head_dim) > 1.f;
-    plan->wide_lazy_log2 = lazy_log2_for(split_items(plan->wide, plan->combine, slots, tune, kWideSlots,
-                                                     kWideKeyNs, pool->head_dim),
-                                         pool->head_dim);
+                                         kNarrowKeyNs, pool->head_dim);
+    plan->wide_renews = split_items(plan->wide, plan->combine, slots, tune, kWideSlots, kWideKeyNs,
+                                    pool->head_dim);
     split_items(plan->tile256, plan->combine, slots, tune, 0, 0, pool->head_dim,
                 (int64_t)kTileMaxPages * pool->page_size - kKvBlock);
     if (slots > INT32_MAX / 2) {

@@ -23,7 +23,14 @@ struct WorkItem {
     int32_t partial_base; // first workspace row slot of this item (split_count > 1), else -1
     int32_t q_row0;       // q_start[req]
     int32_t ctx;          // ctx_lens[req]
-    int32_t reserved;
+    // 128-row kernel: the reference maximum is renewed every so many blocks (0 = never), where a part
+    // would begin if the KV range were cut into about split_target parts.  A probability is rounded to
+    // 16 bits unless it is the reference's own, which is exactly 1, so that fewer parts alone would
+    // mean results further from those in 64 bits.  Error against that cut's, without and with renewal,
+    // and time of the attention call: 10 requests, 128 tokens over 1000, 40/40 heads, bf16, whole
+    // instead of in three parts +0.77 % / 0.00 %, 51.1 / 51.0 us (the three parts take 85); 6 of 50 tokens
+    // over 900, 64/8 heads, whole instead of in four +1.32 % / 0.00 %, 28.5 / 30.0 us.
+    int32_t renew_blocks;
 };
 static_assert(sizeof(WorkItem) == 48, "WorkItem is read by the kernels as 12 int32");
 
@@ -106,24 +113,6 @@ constexpr int kWideKeyNs = 31;
 constexpr int kKvBlock = 32;     // keys per inner step (two pages)
 constexpr float kLazyLog2 = 8.f;  // matrix-core kernels: the reference maximum of a row may lag the
                                   // true one by this many powers of 2
-// The same for a list of the 128-row kernel, by how many times its parts the cut into about
-// split_target parts would have.  A probability is rounded to 16 bits unless it is the reference's own,
-// which is exactly 1, and every part has a reference: fewer parts alone would mean results further from
-// those in 64 bits.  A reference that follows closer makes up for it, for some rescaling of the
-// accumulators.  Error against that cut's, bf16 and f16 alike, and time of the attention call:
-//   10 requests, 128 tokens over 1000, 40/40 heads, whole (three parts each take 85 us):
-//     lag 2^8 +0.77 % 52.6 us, 2^3 +0.09 % 54.5, 2^2 -0.85 % 56-57
-//   18 of 50 tokens over 1500, whole (two): 2^8 +0.27 % 115.1 us, 2^3 -0.39 % 114.9, 2^2 -1.2 % 116.5
-//   3 first prompts, 64/8 heads (1.4 times the parts): 2^8 +0.05 % 29.6 us, 2^3.5 0.00 % 30.5
-//   6 of 100 tokens over 900, 32/8 heads, whole (four take 27.8 us): 2^2 +0.86 % 20.0, 2^1 -0.35 % 20.2
-constexpr float lazy_log2_for(float coarseness, int head_dim)
-{
-    const float few = head_dim == 128 ? 2.f : 1.f;
-    return coarseness <= 1.f    ? kLazyLog2
-           : coarseness <= 1.5f ? 3.5f
-           : coarseness <= 2.1f ? few + 1.f
-                                : few;
-}
 constexpr int kTileMaxPages = 8192;  // page ids an item of the 256-row kernel may span (it keeps
                                      // them in LDS): its KV range is at most 16 times that
 
@@ -174,11 +163,10 @@ struct pv_plan {
     std::vector<pv::AppendGroup> append_groups;
     std::vector<pv::CombineChunk> combine_chunks;
     int64_t partial_slots;  // workspace row slots
-    // Precision of lists that are cut into fewer parts than the cut into about split_target parts
-    // gives them: the narrow kernel's probabilities in two 16-bit terms, and how far the reference
-    // maximum of the 128-row kernel may lag (lazy_log2_for)
-    bool narrow_two_terms;
-    float wide_lazy_log2;
+    // Where an item gets fewer parts than the cut into about split_target parts gives it (see
+    // split_items): the narrow kernel takes its probabilities in two 16-bit terms, items of the 128-row
+    // kernel renew their reference
+    bool narrow_two_terms, wide_renews;
     size_t workspace_bytes;
 
     // Host image of everything the kernels read from the plan: the nine arrays above, each at a
