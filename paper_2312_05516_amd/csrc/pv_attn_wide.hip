@@ -138,11 +138,12 @@ __global__ __launch_bounds__(256, 3) void attn_wide_kernel(
 #pragma unroll
         for (int v = 0; v < 16; ++v) o[blk][v] = 0.f;
     float m_run = -INFINITY;  // reference maximum of the RAW scores (before scaling)
-    float m_top = -INFINITY;  // the highest reference so far
+    float m_top = -INFINITY;  // the highest reference so far (RENEW)
+    float m_cmp = -INFINITY;  // what the test for a new reference compares with: m_run, but for a renewal
     float l_run = 0.f;        // this lane's share of the running sum
     float mc = 0.f;           // m_run in the exp2 domain (0 while there is no reference yet)
 
-    auto compute_block = [&](const unsigned char *sb, int kb0, bool renew, auto masked_tag) {
+    auto compute_block = [&](const unsigned char *sb, int kb0, auto masked_tag) {
         constexpr bool MASKED = decltype(masked_tag)::value;
         f32x16 s[NT];
 #pragma unroll
@@ -178,17 +179,16 @@ __global__ __launch_bounds__(256, 3) void attn_wide_kernel(
         // probabilities just range up to 2^kLazyLog2 instead of 1).  Each lane tests the keys it
         // holds; only when some lane of the wavefront sees such a score (or has no reference yet)
         // do the two lanes of a row exchange their maxima and the accumulators get rescaled.
-        // A renewal takes the block's own maximum as the reference also where it is lower (by no more
-        // than 2^kRenewLog2 than any reference so far, so that nothing grows by more than that): see
-        // WorkItem::renew_blocks.
-        const float base = renew ? m_top : m_run;
-        const float margin = renew ? -kRenewLog2 : kLazyLog2;
-        const bool grow = m_run == -INFINITY || (mx - base) * scale_log2e > margin;
+        const float base = RENEW ? m_cmp : m_run;
+        const bool grow = m_run == -INFINITY || (mx - base) * scale_log2e > kLazyLog2;
         if (__any(grow)) {
             mx = fmaxf(mx, __shfl_xor(mx, 32));
             const float m_new =
-                (m_run == -INFINITY || (mx - base) * scale_log2e > margin) ? mx : m_run;
-            if constexpr (RENEW) m_top = fmaxf(m_top, m_new);
+                (m_run == -INFINITY || (mx - base) * scale_log2e > kLazyLog2) ? mx : m_run;
+            if constexpr (RENEW) {
+                m_top = fmaxf(m_top, m_new);
+                m_cmp = m_new;
+            }
             const float m_safe = m_new == -INFINITY ? 0.f : m_new;
             const float alpha =
                 m_run == -INFINITY ? 0.f : fast_exp2((m_run - m_safe) * scale_log2e);
@@ -256,19 +256,27 @@ __global__ __launch_bounds__(256, 3) void attn_wide_kernel(
         __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, 0));
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
+    const float renew_margin = (kLazyLog2 + kRenewLog2) / scale_log2e;  // +inf for a zero scale: never
     int to_renewal = it.renew_blocks ? it.renew_blocks + 1 : 0;  // 0: counts down and never gets there
     for (int b = 0; b < nblocks; ++b) {
         const bool more = b + 2 < nblocks;
         if (more) dma_block(b + 2, id0, id1);  // its stage held block b-1: everyone is done with it
         page_ids(b + 3, id0, id1);
         const int kb0 = it.kv_begin + BK * b;
-        const bool renew = RENEW && --to_renewal == 0;
-        if (renew) to_renewal = it.renew_blocks;
+        if constexpr (RENEW) {
+            // A renewal takes the block's own maximum as the reference also where it is lower, by no more
+            // than 2^kRenewLog2 than any reference so far, so that nothing grows by more than that.
+            m_cmp = m_run;
+            if (--to_renewal == 0) {
+                to_renewal = it.renew_blocks;
+                m_cmp = m_top - renew_margin;
+            }
+        }
         if (kb0 < wave_end) {
             if (kb0 + BK <= unmasked_end)
-                compute_block(smem[b % STAGES], kb0, renew, std::false_type{});
+                compute_block(smem[b % STAGES], kb0, std::false_type{});
             else
-                compute_block(smem[b % STAGES], kb0, renew, std::true_type{});
+                compute_block(smem[b % STAGES], kb0, std::true_type{});
         }
         // block b+1 (issued one iteration ago) must have landed before the barrier publishes it;
         // this iteration's own copies may stay in flight.  This wavefront's LDS reads of block b
