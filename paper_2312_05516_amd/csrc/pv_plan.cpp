@@ -72,28 +72,6 @@ static int64_t item_cost(const WorkItem &w, int rows_per_step)
     return (int64_t)(w.kv_end - w.kv_begin) * steps;
 }
 
-// Cut long items into parts of the KV range.  A cut is not free: every part pays the set-up of an
-// item, writes its rows in fp32, and the merge reads them back.  `slots` = workgroups of the kernel
-// that the GPU holds at once.
-//  * A list of fewer than kFewItems is cut everywhere, into parts of the shortest length (never below
-//    min_split_keys) at which all of them still run at once: one part more than there are slots
-//    starts when the others are nearly done and doubles the time.
-//  * In a longer list only the outliers are cut, items more than a quarter longer than `chunk` = the
-//    KV length of kFewItems equal items, because one workgroup walking such an item alone would
-//    outlast everything else.
-//  * Whatever the list, no part is longer than max_len keys (0 = no such limit).
-//  * Nothing is cut where the merge costs more than the shorter longest item gives: the merge is a
-//    launch of about 7 us, and moves 8 bytes per partial row element at about 4 TB/s; an item takes
-//    key_ns per key.
-// Measured, whole step, against a rule that cut every list of fewer than 1024 items into about 1024
-// parts: 28 requests, 752 items of the 128-row kernel (64/8 heads) 114 -> 82 us; 16 requests, 570
-// items (40/10 heads) 82 -> 54; 4 generation steps over 0.7-9 K keys, 64/8 heads 30 -> 27; 96 of them
-// 97 -> 93.  With 768 in place of kFewItems the first two stay at 102 and 80.  The cost of the merge:
-// 3 first prompts of 191-755 tokens, 64/8 heads (472 items of 24 blocks of 32 keys) 46 -> 39 us.
-// `slots` = 0, or a target set by hand: lists shorter than split_target are cut into about that
-// many parts, and longer ones at items more than twice as long as the target's share.
-constexpr int32_t kFewItems = 512;
-
 // A way to cut a list: every item longer than `longest_whole` (and of at least 2 * min_keys keys) into
 // parts of about `chunk` keys, evened out and rounded up to whole blocks.
 struct Cut {
@@ -122,13 +100,51 @@ static Cut target_cut(int64_t total_keys, size_t items, int32_t target, const Tu
     return c;
 }
 
-// Returns true where an item gets fewer parts than the cut into about split_target parts gives it.
+// A list of the narrow or the 128-row kernel, and what the rules below need to know of that kernel.
+struct CutRule {
+    int32_t slots;       // workgroups that the GPU holds at once
+    int32_t long_list;   // from this many items on only outliers are cut (0: see target_cut)
+    int32_t long_share;  // ... items more than a quarter longer than a long_share-th of the keys
+    int32_t stretch_pct; // parts may be longer than a slots-th of the keys by so much, to run at once
+    bool always_stretch; // also where they do not run at once even so (else: target_cut)
+    int32_t key_ns;      // what a key less in the longest item saves while the GPU is not full
+    int32_t always_cut;  // up to this many items that is not weighed against the merge
+};
+
+// Cut long items into parts of the KV range.  A cut is not free: every part pays the set-up of an
+// item, writes its rows in fp32, and the merge reads them back.  Returns true where an item gets fewer
+// parts than the cut into about split_target parts gives it.
+//  * Parts that all run at once are best where little more than a slots-th of the keys each does it:
+//    one part more than there are slots starts when the others are nearly done.  4 generation steps
+//    over 0.7-9 K keys, 64/8 heads, attention alone: 512 parts 19.1 us, 568 parts 21.7, 416 20.2.  Lists
+//    of 416 to 512 equal items are left whole by that (480 over 2 K keys: 75.5 us, 85.9 in 3 parts each;
+//    376, which 1.25 does not reach: 68.5 whole, 63.1 in two, 69.4 in three).
+//  * Otherwise the narrow kernel, which is bound by bandwidth, wants about 1024 parts, so that no
+//    workgroup walks a long item alone while the others have left: 62 requests over 500 keys and one
+//    over 32 K, 64/8 heads, 48.3 us (211 in parts that run at once: the short items take up their
+//    slots); 520 equal items 94.7 us (101 whole).  From 640 items on (head size 128) enough run behind
+//    one another for cutting outliers alone: 672 items over 0.1-8 K keys 83.3 us against 86.0, 720
+//    equal ones 112 whole against 121 in two parts (800: 140 against 139).  Not so for head size 64,
+//    where an item takes half the time per key: 45.8 against 42.2.
+//  * The 128-row kernel, bound by its arithmetic, with 16 times the rows to merge, takes as few parts
+//    as keep the longest within twice a slots-th of the keys: 11 requests of 100 tokens and one over 30
+//    K, 40/40 heads, 163 us against 177 in about 1024 parts, 10 of 128 tokens over 1000 whole 53
+//    against 90, 19 (760 items, one over 30 K) 170 against 188.
+//  * Nothing is cut where the merge costs more than the shorter longest item gives: a launch of about
+//    7 us, and 8 bytes per partial row element at about 4 TB/s.  16 generation steps over 520-640 keys
+//    are left whole (10.8-11.2 us; cut 11.7), over 900 cut (11.9; whole 14.9); head size 64 up to 1000
+//    (9.0 against 11.7 at 640, 13.4 against 11.7 at 1400).  6 requests of 100 tokens over 900 keys, 32/8
+//    heads, 128-row kernel: 19.0 whole, 27.6 cut; over 2500 40.6 and 38.8.  Where the cut of all long
+//    items does not pay, that of the longest few may.  Up to 128 items of the 128-row kernel are cut in
+//    any case: 80 items 19.8 us, 21.9 whole; 20 items 18.2 and 21.3; 120 items 22.1 and 22.7.
+//  * Whatever the list, no part is longer than max_len keys (0 = no such limit).
+// No rule (the 256-row kernel), or a target set by hand: target_cut.
 static bool split_items(std::vector<WorkItem> &items, std::vector<CombineItem> &combine,
-                        int64_t &slots_out, const Tuning &tune, int32_t slots, int32_t key_ns,
+                        int64_t &slots_out, const Tuning &tune, const CutRule *rule,
                         int32_t head_dim, int64_t max_len = 0)
 {
     if (items.empty()) return false;
-    if (tune.split_by_hand) slots = 0;
+    if (tune.split_by_hand) rule = nullptr;
     int64_t total_keys = 0, longest = 0;
     for (const WorkItem &w : items) {
         total_keys += w.kv_end - w.kv_begin;
@@ -136,26 +152,54 @@ static bool split_items(std::vector<WorkItem> &items, std::vector<CombineItem> &
     }
     const Cut even = target_cut(total_keys, items.size(), tune.split_target, tune);
     Cut cut = even;
-    if (slots) {
-        const bool outliers_only = (int64_t)items.size() >= kFewItems;
-        const int32_t target = outliers_only ? kFewItems : slots;
-        int64_t chunk = std::max<int64_t>((total_keys + target - 1) / target, tune.min_split_keys);
-        chunk = (chunk + kKvBlock - 1) / kKvBlock * kKvBlock;
-        while (!outliers_only) {
-            int64_t parts = 0;
-            for (const WorkItem &w : items) parts += (w.kv_end - w.kv_begin + chunk - 1) / chunk;
-            if (parts <= slots) break;
-            chunk += (chunk / 32 + kKvBlock - 1) / kKvBlock * kKvBlock;
+    if (rule) {
+        auto blocks = [](int64_t keys) { return (keys + kKvBlock - 1) / kKvBlock * kKvBlock; };
+        if (rule->long_list && (int64_t)items.size() >= rule->long_list) {
+            const int64_t share = (total_keys + rule->long_share - 1) / rule->long_share;
+            cut.chunk = blocks(std::max<int64_t>(share, tune.min_split_keys));
+            cut.longest_whole = cut.chunk + cut.chunk / 4;
+        } else if (rule->always_stretch || (int64_t)items.size() <= rule->slots) {
+            auto at_once = [&](int64_t chunk) {
+                const Cut c = {chunk, chunk, cut.min_keys};
+                int64_t parts = 0;
+                for (const WorkItem &w : items) parts += c.parts(w.kv_end - w.kv_begin);
+                return parts <= rule->slots;
+            };
+            const int64_t share = (total_keys + rule->slots - 1) / rule->slots;
+            int64_t lo = blocks(std::max<int64_t>(share, tune.min_split_keys));
+            int64_t hi = blocks(lo + lo * rule->stretch_pct / 100);
+            if (at_once(lo)) {
+                hi = lo;
+            } else if (at_once(hi)) {
+                while (hi - lo > std::max<int64_t>(kKvBlock, lo / 32)) {
+                    const int64_t mid = blocks((lo + hi) / 2);
+                    (at_once(mid) ? hi : lo) = mid;
+                }
+            } else if (!rule->always_stretch) {
+                hi = 0;
+            }
+            if (hi) cut.chunk = cut.longest_whole = hi;
         }
-        cut.chunk = chunk;
-        cut.longest_whole = outliers_only ? chunk + chunk / 4 : chunk;
-        int64_t part_rows = 0;
-        for (const WorkItem &w : items) {
-            const int64_t len = w.kv_end - w.kv_begin;
-            if (cut.parts(len) > 1) part_rows += w.row_count * ((len + chunk - 1) / chunk);
+        // the cut of all long items, or where that does not pay, of the longest few
+        for (bool few = false; cut.longest_whole < longest; few = true) {
+            int64_t part_rows = 0, whole = 0;
+            for (const WorkItem &w : items) {
+                const int64_t len = w.kv_end - w.kv_begin, parts = cut.parts(len);
+                if (parts > 1)
+                    part_rows += w.row_count * parts;
+                else
+                    whole = std::max(whole, len);
+            }
+            if (cut.parts(longest) > 1) {
+                const int64_t part_len = cut.part_len(longest);
+                const int64_t after =
+                    few || rule->always_stretch ? std::max(whole, part_len) : part_len;
+                if ((longest - after) * rule->key_ns >= 7000 + part_rows * head_dim * 8 / 4000 ||
+                    (int64_t)items.size() <= rule->always_cut)
+                    break;
+            }
+            cut.chunk = cut.longest_whole = 2 * cut.longest_whole;
         }
-        if ((longest - cut.longest_whole) * key_ns < 7000 + part_rows * head_dim * 8 / 4000)
-            cut.longest_whole = longest;
     }
     auto too_long = [&](int64_t len) { return max_len > 0 && len > max_len; };
     // items that get fewer parts than the even cut gives them
@@ -504,11 +548,17 @@ pv_status build_plan(const pv_pool_desc *pool, int32_t num_q_heads, const int32_
         }
     }
     int64_t slots = 0;
-    plan->narrow_two_terms = split_items(plan->narrow, plan->combine, slots, tune, kNarrowSlots,
-                                         kNarrowKeyNs, pool->head_dim);
-    plan->wide_renews = split_items(plan->wide, plan->combine, slots, tune, kWideSlots, kWideKeyNs,
-                                    pool->head_dim);
-    split_items(plan->tile256, plan->combine, slots, tune, 0, 0, pool->head_dim,
+    const bool wide_rows = pool->head_dim == 128;
+    const CutRule narrow_rule = {
+        kNarrowSlots, wide_rows ? kNarrowSlots * 5 / 4 : 0, kNarrowSlots, 25, false,
+        wide_rows ? 16 : (int64_t)plan->narrow.size() > kNarrowSlots ? 12 : 9, 0};
+    const CutRule wide_rule = {kWideSlots, kFewWideItems, kFewWideItems, 100, true,
+                               wide_rows ? 31 : 16, wide_rows ? 128 : 0};
+    plan->narrow_two_terms =
+        split_items(plan->narrow, plan->combine, slots, tune, &narrow_rule, pool->head_dim);
+    plan->wide_renews =
+        split_items(plan->wide, plan->combine, slots, tune, &wide_rule, pool->head_dim);
+    split_items(plan->tile256, plan->combine, slots, tune, nullptr, pool->head_dim,
                 (int64_t)kTileMaxPages * pool->page_size - kKvBlock);
     if (slots > INT32_MAX / 2) {
         delete plan;

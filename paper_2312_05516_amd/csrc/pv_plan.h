@@ -106,10 +106,12 @@ constexpr int64_t append_group_count(int64_t t_begin, int64_t count)
 constexpr int kNarrowRows = 16;  // rows per item of the bandwidth-oriented kernel
 constexpr int kWideRows = 128;   // rows per item of the matrix-core kernel (4 waves x 32 rows)
 constexpr int kTileRows = 256;   // rows per item of the 256-row matrix-core kernel (4 waves x 64)
-constexpr int kNarrowSlots = 512;  // workgroups that run at once: 256 CUs x 2 (212 registers a lane)
-constexpr int kWideSlots = 768;    // 256 CUs x 3 (168 registers a lane, 48 KiB of LDS)
-constexpr int kNarrowKeyNs = 16;   // time of an item per key while the GPU is not full, measured
-constexpr int kWideKeyNs = 31;
+// Workgroups that run at once on the 256 CUs: two of the narrow kernel on each (212 registers a lane;
+// head size 64 has room for three, but 512 parts are ahead of more: 4 generation steps, 32/8 heads,
+// 13.4 us with 512 parts, 14.2 with 656), three of the 128-row kernel (168 registers, 48 KiB of LDS).
+constexpr int kNarrowSlots = 512;
+constexpr int kWideSlots = 768;
+constexpr int kFewWideItems = 512;  // shorter lists of the 128-row kernel are cut to fill the GPU
 constexpr int kKvBlock = 32;     // keys per inner step (two pages)
 constexpr float kLazyLog2 = 8.f;  // matrix-core kernels: the reference maximum of a row may lag the
                                   // true one by this many powers of 2
@@ -129,10 +131,11 @@ struct DeviceLists {
 };
 
 struct Tuning {
-    int32_t split_target;    // cut a list that is shorter into about this many work items (the
-                             // 256-row kernel, and every kernel when it is set by hand)
-    bool split_by_hand;
-    int32_t min_split_keys;  // never make a KV part shorter than this
+    int32_t split_target;    // cut a list that is shorter into about this many work items
+    bool split_by_hand;      // whatever the kernel (see split_items)
+    int32_t min_split_keys;  // items are cut from twice this many keys on, by parts of at least this
+                             // many before they are evened out (which leaves at least half of it, and
+                             // less in an item's last part)
     int32_t wide_min_rows;   // (request, KV head) units with n*G >= this use the matrix-core
                              // kernel; smaller ones are cut into 16-row items of the narrow kernel
     int32_t xcds;            // L2 domains the work list is interleaved over

@@ -179,8 +179,9 @@ def test_plan_cuts_outliers_of_a_long_list(pv):
     ([9000, 200], [150, 90], 40, 40, 1, 768),
 ])
 def test_plan_cuts_a_short_list_into_parts_that_run_at_once(pv, ctx, qn, hq, hkv, kind, slots):
-    """Fewer than 512 items: parts of one length that all fit the GPU at once, covering every unit's
-    KV range without gaps; no part below the shortest length unless it is a last one."""
+    """Lists whose items are long for their number: parts of one length that all fit the GPU at once,
+    covering every unit's KV range without gaps; no part below half of the shortest length (256 keys,
+    from which parts are evened out) unless it is a last one."""
     plan = pv.plan_create(pv.pool_desc(1 << 17, hkv, 128, "f16"), hq, ctx, qn, 4096)
     items = _items(pv, plan, kind)
     assert pv.plan_num_work_items(plan, 2) > 0
@@ -196,6 +197,70 @@ def test_plan_cuts_a_short_list_into_parts_that_run_at_once(pv, ctx, qn, hq, hkv
         group = hq // hkv
         assert int(parts[-1][5]) == ctx[req] + (row0 + int(parts[0][3]) - 1) // group + 1
         assert all(int(p[5] - p[4]) >= 128 for p in parts[:-1])
+    plan.destroy()
+
+
+def _longest_and_share(pv, ctx, qn, hq, hkv, head_dim, kind, slots):
+    plan = pv.plan_create(pv.pool_desc(1 << 20, hkv, head_dim, "f16"), hq, ctx, qn, 8192)
+    items = _items(pv, plan, kind)
+    assert items and not _items(pv, plan, 1 - kind)
+    lens = [int(it[5] - it[4]) for it in items]
+    plan.destroy()
+    return max(lens), max(256, -(-sum(lens) // slots))
+
+
+def _lognormal(seed, n):
+    rng = np.random.default_rng(seed)
+    return [int(x) for x in np.clip(np.exp(rng.normal(np.log(1000), 1, size=n)), 16, 8192)]
+
+
+@pytest.mark.parametrize("ctx,hq,hkv", [
+    ([100] * 62 + [100000], 64, 8),
+    ([500] * 62 + [32000], 64, 8),
+    ([500] * 60 + [32000], 64, 8),
+    ([500] * 48 + [32000] * 2, 64, 8),
+    ([500] * 11 + [16000], 40, 40),
+    (_lognormal(1, 62), 64, 8),
+    (_lognormal(2, 12), 40, 40),
+])
+@pytest.mark.parametrize("head_dim", [64, 128])
+def test_plan_cuts_the_long_requests_of_a_short_skewed_list(pv, ctx, hq, hkv, head_dim):
+    """400 to 511 items of generation steps, a few of them much longer than the others: however many
+    short items there are, no part is longer than twice a slots-th of the keys (or the shortest
+    length), so that no workgroup walks a long request alone."""
+    longest, share = _longest_and_share(pv, ctx, [1] * len(ctx), hq, hkv, head_dim, 0, 512)
+    assert longest <= 2 * share
+
+
+@pytest.mark.parametrize("head_dim", [64, 128])
+def test_plan_has_no_cliff_between_short_and_long_lists(pv, head_dim):
+    """One long request among 55 to 140 short ones (448 to 1128 items): the longest part stays within
+    the same bound on both sides of every limit of the rules."""
+    for n in list(range(55, 84)) + list(range(120, 141)):
+        longest, share = _longest_and_share(pv, [500] * n + [32000], [1] * (n + 1), 64, 8, head_dim, 0,
+                                            512)
+        assert longest <= 2 * share, n
+
+
+@pytest.mark.parametrize("short,long_ctx", [(11, 30000), (10, 8000), (7, 20000), (18, 30000)])
+@pytest.mark.parametrize("head_dim", [64, 128])
+def test_plan_cuts_the_long_prompts_of_a_short_skewed_list(pv, short, long_ctx, head_dim):
+    """The same for the 128-row kernel: prompts of 100 tokens, one of them over a long history (768
+    workgroups run at once; a 512th is the share that counts from 512 items on)."""
+    ctx = [200] * short + [long_ctx]
+    longest, share = _longest_and_share(pv, ctx, [100] * len(ctx), 40, 40, head_dim, 1,
+                                        512 if 40 * len(ctx) >= 512 else 768)
+    assert longest <= 2 * share + 32
+
+
+@pytest.mark.parametrize("reqs,parts", [(47, 2), (52, 1), (60, 1), (64, 1), (65, 2), (70, 2), (80, 1)])
+def test_plan_cuts_equal_items_by_how_they_fill_the_gpu(pv, reqs, parts):
+    """Equal items over 2 K keys, head size 128: whole where they fill (nearly) all of the 512 slots,
+    cut where they do not, or where a few would be left for a second round."""
+    plan = pv.plan_create(pv.pool_desc(1 << 17, 8, 128, "f16"), 64, [1999] * reqs, [1] * reqs, 4096)
+    items = _items(pv, plan, 0)
+    counts = {int(it[7]) for it in items}
+    assert (counts == {1}) == (parts == 1) and (parts == 1 or min(counts) >= 2)
     plan.destroy()
 
 
