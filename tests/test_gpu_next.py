@@ -112,14 +112,19 @@ def _chunk_cost_ms(pv, torch, l: int, heads: int = 8, reps: int = 20) -> float:
     for _ in range(3):
         pv.multi_token_paged_attn_planned(plan, q, kp, vp, table, b.scale, out, ws)
     torch.cuda.synchronize()
-    start, stop = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
-    start.record()
-    for _ in range(reps):
-        pv.multi_token_paged_attn_planned(plan, q, kp, vp, table, b.scale, out, ws)
-    stop.record()
-    torch.cuda.synchronize()
+    # the shortest of five runs: the shortest contexts are launch-bound (12 us), where a busy host adds
+    # a few microseconds to a single run
+    times = []
+    for _ in range(5):
+        start, stop = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        start.record()
+        for _ in range(reps):
+            pv.multi_token_paged_attn_planned(plan, q, kp, vp, table, b.scale, out, ws)
+        stop.record()
+        torch.cuda.synchronize()
+        times.append(start.elapsed_time(stop) / reps)
     plan.destroy()
-    return start.elapsed_time(stop) / reps
+    return min(times)
 
 
 def test_cost_profile_measured_with_the_kernel_feeds_the_cost_model(oracle):
