@@ -296,7 +296,7 @@ __global__ __launch_bounds__(256, 2) void attn_narrow_kernel(
 }
 
 // Merge of split-KV partial results: out = sum_s 2^(m_s - M) O_s / sum_s 2^(m_s - M) l_s.
-// One workgroup = eight groups of 32 threads; combine_groups() of them share a row, each taking every
+// One workgroup = eight groups of 32 threads; CombineItem::groups of them share a row, each taking every
 // so-manyth part (D/32 output elements per thread), and add up through LDS.  The parts of a row are
 // megabytes apart from any other access, so what bounds this kernel is the number of dependent round
 // trips to memory: the 32 threads read all (max, sum) pairs of the row at once, and the partial
@@ -312,7 +312,7 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(
     __shared__ vecf sm_acc[8][32];
     const CombineChunk ch = chunks[blockIdx.x];
     const CombineItem it = items[ch.item];
-    const int groups = combine_groups(it.split_count);
+    const int groups = it.groups;
     const int t = (int)threadIdx.x & 31;
     const int grp = (int)threadIdx.x >> 5;
     const int part = grp % groups;

@@ -239,7 +239,7 @@ static bool split_items(std::vector<WorkItem> &items, std::vector<CombineItem> &
         c.partial_base = (int32_t)slots_out;
         c.split_count = (int32_t)parts;
         c.q_row0 = w.q_row0;
-        c.reserved = 0;
+        c.groups = 1;  // set when all rows are known
         combine.push_back(c);
         for (int64_t s = 0; s < parts; ++s) {
             WorkItem part = w;
@@ -568,10 +568,14 @@ pv_status build_plan(const pv_pool_desc *pool, int32_t num_q_heads, const int32_
     order_items(plan->wide, kWideRows, tune.xcds);
     order_items(plan->tile256, kTileRows, tune.xcds);
     plan->partial_slots = slots;
-    for (size_t i = 0; i < plan->combine.size(); ++i)
-        for (int32_t r0 = 0; r0 < plan->combine[i].row_count;
-             r0 += 8 / combine_groups(plan->combine[i].split_count))
+    int64_t merge_rows = 0;
+    for (const CombineItem &c : plan->combine) merge_rows += c.row_count;
+    for (size_t i = 0; i < plan->combine.size(); ++i) {
+        CombineItem &c = plan->combine[i];
+        c.groups = combine_groups(c.split_count, merge_rows);
+        for (int32_t r0 = 0; r0 < c.row_count; r0 += 8 / c.groups)
             plan->combine_chunks.push_back(CombineChunk{(int32_t)i, r0});
+    }
     // workspace: fp32 partial outputs [slots][D], then (running max, running sum) [slots][2]
     plan->workspace_bytes = (size_t)slots * (size_t)(pool->head_dim + 2) * sizeof(float);
     build_image(plan);

@@ -43,19 +43,28 @@ struct CombineItem {
     int32_t partial_base; // slot of split 0, row 0; split s, row i lives at base + s*row_count + i
     int32_t split_count;
     int32_t q_row0;
-    int32_t reserved;
+    int32_t groups;       // thread groups of the merge that share a row (combine_groups)
 };
 static_assert(sizeof(CombineItem) == 32, "CombineItem is read by the kernels as 8 int32");
 
 // How many of a merge workgroup's eight thread groups share one row, by the number of parts to add:
 // with few parts one group reads them all, with many the reads are spread over the groups, so that
-// nobody reads more than four parts after one another up to 32 of them.
-constexpr int combine_groups(int split_count)
+// nobody reads more than four parts after one another up to 32 of them.  But only as long as that is
+// no more than kMergeGroups workgroups for the rows of the whole merge: more rows than that keep the
+// GPU busy by themselves, and every further group of a row reads the row's (max, sum) pairs again.
+// Attention call, with and without that limit: 2 prompts of 256 tokens over 2 K and 16 K, 64/8 heads,
+// 210 and 219 us; 128 tokens over 16 K, 40/40 heads, 84.8 and 88.4; 200 over 30 K, 32/8 heads, 78.3 and
+// 81.3; 56 generation steps (288 items of 8 rows) 66.7 and 67.2; 4 of them (32 items) 19.2 either way,
+// 21.0 with one group a row.  Limits of 1024 and 2048: the same within 1 us.
+constexpr int kMergeGroups = 512;
+constexpr int combine_groups(int split_count, int64_t merge_rows)
 {
-    return split_count >= 16 ? 8 : split_count >= 8 ? 4 : split_count >= 4 ? 2 : 1;
+    int groups = split_count >= 16 ? 8 : split_count >= 8 ? 4 : split_count >= 4 ? 2 : 1;
+    while (groups > 1 && merge_rows * groups > 8 * kMergeGroups) groups /= 2;
+    return groups;
 }
 
-// 8 / combine_groups() rows of one combine item: the unit of work of one merge workgroup.
+// 8 / CombineItem::groups rows of one combine item: the unit of work of one merge workgroup.
 struct CombineChunk {
     int32_t item;  // index into the combine list
     int32_t row0;  // first row (relative to the item) of the chunk

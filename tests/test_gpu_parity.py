@@ -179,6 +179,22 @@ def test_merge_of_any_number_of_parts(oracle, monkeypatch, parts, head_dim):
     check_case(oracle, H.make_case(b, fill="nan"))
 
 
+@pytest.mark.parametrize("new,hkv,parts", [(128, 4, 16), (64, 16, 17), (128, 33, 9), (128, 33, 17)])
+def test_merge_of_many_rows(oracle, monkeypatch, new, hkv, parts):
+    """Merges of 512 to 4224 rows: eight, four and two thread groups a row become four, two and one
+    where the rows fill the GPU by themselves, on both sides of the limit of 4096 rows times groups."""
+    from paper_2312_05516_amd import binding as pv
+    monkeypatch.setenv("PV_MIN_SPLIT_KEYS", "32")
+    monkeypatch.setenv("PV_SPLIT_TARGET", str(parts * hkv))
+    b = wl.custom([32 * parts - new], [new], num_q_heads=hkv, num_kv_heads=hkv, head_dim=64,
+                  dtype="f16", seed=520 + parts)
+    desc = pv.pool_desc(b.num_pages, b.num_kv_heads, b.head_dim, b.dtype)
+    plan = pv.plan_create(desc, b.num_q_heads, b.ctx_lens, b.q_lens, b.max_pages_per_req)
+    assert pv.plan_num_work_items(plan, 1) == parts * hkv and pv.plan_num_work_items(plan, 2) == hkv
+    plan.destroy()
+    check_case(oracle, H.make_case(b, fill="nan"))
+
+
 @pytest.mark.parametrize("kv_len", [1, 31, 32, 33, 63, 64, 65, 96, 127, 128, 129, 191, 193])
 @pytest.mark.parametrize("head_dim", [64, 128])
 def test_matrix_core_kernel_block_edges(oracle, monkeypatch, kv_len, head_dim):
