@@ -5,10 +5,13 @@
 //
 // Staging layout: for the i-th listed page, its K image (num_kv_heads * 16 * D elements, exactly
 // as in the pool) followed by its V image.  One workgroup moves one 4 KiB piece with 16 bytes per
-// lane; pure copies, bit-exact.  Bound: HBM.  Both sides are touched once, so loads and stores carry
-// the streaming hint: 1024 pages of 160 KiB out and as many in, 243 us with ordinary stores, 219 us
-// so (6.1 TB/s; a plain device copy reaches 5.3).  More bytes per workgroup are slower (8 KiB 234 us,
-// 16 KiB 240 us, 32 KiB 326 us).
+// lane; pure copies, bit-exact.  Bound: HBM.  What is read is read once and carries the streaming hint,
+// and so does what is stored in the staging buffer.  Pages that come in are read by that layer's
+// attention next: their stores do not.  Copy in and the attention behind it, K and V of 160 KiB each a
+// page, without and with the hint on those stores: 64 pages 19.1 / 20.2 us, 128 29.6 / 31.4, 256 48.7 /
+// 49.4, 512 83.4 / 88.5, 1024 157.3 / 167.2 (the copy alone 122.9 / 110.5: the hint only moves the cost
+// into the attention); 1024 pages of 2 x 32 KiB 41.8 / 43.2.  More bytes per workgroup are slower (1024
+// pages of 2 x 160 KiB out and as many in, 4 KiB 219 us, 8 KiB 234, 16 KiB 240, 32 KiB 326).
 #include "pv_device.h"
 
 namespace pv {
@@ -31,7 +34,7 @@ __global__ __launch_bounds__(256) void pages_copy_kernel(
     if (GATHER)
         store16_stream(stage, load16_stream(pool));
     else
-        store16_stream(pool, load16_stream(stage));
+        *reinterpret_cast<u32x4 *>(pool) = load16_stream(stage);
 }
 
 hipError_t launch_pages_copy(bool gather, const pv_pool_desc *pool, const int32_t *page_ids,
