@@ -179,6 +179,19 @@ def test_merge_of_any_number_of_parts(oracle, monkeypatch, parts, head_dim):
     check_case(oracle, H.make_case(b, fill="nan"))
 
 
+@pytest.mark.parametrize("hkv,head_dim,dtype", [(33, 64, "f16"), (33, 64, "bf16"), (17, 128, "f16")])
+def test_append_of_more_rows_than_the_streaming_limit(hkv, head_dim, dtype):
+    """New rows of just over 32 MiB are read with the streaming hint: K and V bit for bit, partial
+    8-slot groups at both ends of the long request."""
+    n = (32 << 20) // (hkv * head_dim * 4) + 3
+    b = wl.custom([5, 0], [n, 3], num_q_heads=hkv, num_kv_heads=hkv, head_dim=head_dim, dtype=dtype,
+                  seed=540 + head_dim)
+    assert b.total_q * hkv * head_dim * 4 > 32 << 20
+    case = H.make_case(b, fill="nan")
+    _, kp, vp = H.gpu_run(case)
+    assert np.array_equal(kp, case.k_pool1.ravel()) and np.array_equal(vp, case.v_pool1.ravel())
+
+
 @pytest.mark.parametrize("new,hkv,parts", [(128, 4, 16), (64, 16, 17), (128, 33, 9), (128, 33, 17)])
 def test_merge_of_many_rows(oracle, monkeypatch, new, hkv, parts):
     """Merges of 512 to 4224 rows: eight, four and two thread groups a row become four, two and one

@@ -133,15 +133,18 @@ def test_fused_rope_append_matches_oracle(oracle, style, dtype, D):
 
 
 @pytest.mark.parametrize("style", ["interleaved", "half"])
-@pytest.mark.parametrize("hq,hkv", [(70, 7), (67, 1), (33, 11)])
-def test_batches_of_many_rows_take_several_heads_a_workgroup(oracle, style, hq, hkv):
+@pytest.mark.parametrize("hq,hkv,D,dtype", [(70, 7, 128, "bf16"), (67, 1, 128, "bf16"),
+                                            (33, 11, 128, "bf16"), (70, 7, 128, "f16"),
+                                            (70, 7, 64, "bf16"), (67, 1, 64, "f16"),
+                                            (33, 11, 64, "f16")])
+def test_batches_of_many_rows_take_several_heads_a_workgroup(oracle, style, hq, hkv, D, dtype):
     """New rows of more than 32 MiB: two or four heads a workgroup, head counts that do not divide by
     that on either side, partial 8-slot groups at both ends."""
-    n = (32 << 20) // ((hq + 2 * hkv) * 256) + 9
-    b = wl.custom([5, 0], [n, 3], num_q_heads=hq, num_kv_heads=hkv, head_dim=128, dtype="bf16",
+    n = (32 << 20) // ((hq + 2 * hkv) * D * 2) + 9
+    b = wl.custom([5, 0], [n, 3], num_q_heads=hq, num_kv_heads=hkv, head_dim=D, dtype=dtype,
                   seed=320 + hq)
     case = H.make_case(b, fill="nan")
-    table = oracle.rope_table(10000.0, 128, n + 5)
+    table = oracle.rope_table(10000.0, D, n + 5)
     q_want, _, kp_want, vp_want = _oracle_fused(oracle, case, table, style)
     q_got, kp_got, vp_got, _ = _gpu_fused(case, table, style)
     assert np.array_equal(vp_got, vp_want)
