@@ -553,23 +553,26 @@ size_t pv_attn_workspace_bytes(const pv_pool_desc *pool, int32_t num_q_heads, in
     if (!pv::pool_desc_valid(pool, nullptr) || num_q_heads <= 0 || num_reqs < 0 || total_q < 0 ||
         max_kv_len < 0)
         return 0;
-    // Splitting only happens while a kernel has fewer items than the target and never makes a
-    // part shorter than half the target share, so each kernel ends with fewer than
-    // items + split_target parts of at most 16, kWideRows resp. kTileRows rows.  Independently, a row can be
-    // in at most max_kv_len / min_split_keys + 1 parts.
+    // Rows of partial results.  Each of the three lists has at most kPartsPerTarget * split_target parts
+    // of cut items, of at most kNarrowRows, kWideRows resp. kTileRows rows; beyond that the 256-row
+    // kernel's items are cut at kTileMaxKeys however many they are.  Independently, a row can be in at
+    // most max_kv_len / min_split_keys + 1 parts.
     const pv::Tuning t = pv::default_tuning();
     const int64_t rows = (int64_t)total_q * num_q_heads +
                          (int64_t)num_reqs * pool->num_kv_heads * pv::kNarrowRows;
     const int64_t max_parts = (int64_t)max_kv_len / t.min_split_keys + 1;
     const int64_t by_rows = rows * max_parts;
+    const int64_t tile_parts =
+        max_kv_len > pv::kTileMaxKeys ? (int64_t)max_kv_len / pv::kTileMaxKeys + 1 : 0;
+    const int64_t list_parts = pv::kPartsPerTarget * (int64_t)t.split_target;
     const int64_t by_items =
-        2 * (int64_t)t.split_target * (pv::kNarrowRows + pv::kWideRows + pv::kTileRows);
+        list_parts * (pv::kNarrowRows + pv::kWideRows + pv::kTileRows) + rows * tile_parts;
     const int64_t slots = by_rows < by_items ? by_rows : by_items;
     // behind the partial results: room for the plan's lists (three int32 per request, 48 bytes
     // per work item and 40 per merge item and its chunks, 16 per append group, nine 256-byte
     // alignments), so that the one-shot call neither allocates nor waits
     const int64_t n_items = rows / pv::kNarrowRows + (int64_t)num_reqs * pool->num_kv_heads * 3 +
-                            2 * (int64_t)t.split_target * 3;
+                            list_parts * 3 + rows / pv::kTileRows * tile_parts;
     const int64_t lists = 12 * (int64_t)num_reqs + 48 * n_items + 40 * n_items / 2 +
                           8 * (slots / 8 + n_items) + 16 * ((int64_t)total_q + 2 * num_reqs) +
                           10 * 256;

@@ -43,7 +43,7 @@ Tuning default_tuning()
     Tuning t;
     t.split_target = env_int("PV_SPLIT_TARGET", 0);
     t.split_by_hand = t.split_target > 0;
-    if (!t.split_by_hand) t.split_target = 1024;
+    if (!t.split_by_hand) t.split_target = kSplitTarget;
     t.min_split_keys = env_int("PV_MIN_SPLIT_KEYS", 256);
     t.wide_min_rows = env_int("PV_WIDE_MIN_ROWS", 33);
     t.xcds = env_int("PV_XCDS", 8);
@@ -559,7 +559,7 @@ pv_status build_plan(const pv_pool_desc *pool, int32_t num_q_heads, const int32_
     plan->wide_renews =
         split_items(plan->wide, plan->combine, slots, tune, &wide_rule, pool->head_dim);
     split_items(plan->tile256, plan->combine, slots, tune, nullptr, pool->head_dim,
-                (int64_t)kTileMaxPages * pool->page_size - kKvBlock);
+                kTileMaxKeys);
     if (slots > INT32_MAX / 2) {
         delete plan;
         return PV_ERR_OUT_OF_RANGE;

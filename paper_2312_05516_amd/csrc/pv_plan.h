@@ -120,12 +120,24 @@ constexpr int kTileRows = 256;   // rows per item of the 256-row matrix-core ker
 // 13.4 us with 512 parts, 14.2 with 656), three of the 128-row kernel (168 registers, 48 KiB of LDS).
 constexpr int kNarrowSlots = 512;
 constexpr int kWideSlots = 768;
+constexpr int kSplitTarget = 1024;
 constexpr int kFewWideItems = 512;  // shorter lists of the 128-row kernel are cut to fill the GPU
 constexpr int kKvBlock = 32;     // keys per inner step (two pages)
 constexpr float kLazyLog2 = 8.f;  // matrix-core kernels: the reference maximum of a row may lag the
                                   // true one by this many powers of 2
 constexpr int kTileMaxPages = 8192;  // page ids an item of the 256-row kernel may span (it keeps
                                      // them in LDS): its KV range is at most 16 times that
+constexpr int kTileMaxKeys = kTileMaxPages * 16 - kKvBlock;
+
+// No list has more parts of cut items than this times the target (see split_items): with a chunk of a
+// target-th of the keys, `target` parts and one more for each cut item, of which there are no more than
+// `target`; the other cuts take a slots-th or a long_share-th of the keys for their chunk or more, and
+// no more items are cut than there are in a short list or four fifths of that share.
+constexpr int kPartsPerTarget = 2;
+static_assert(kNarrowSlots * 9 / 5 <= kPartsPerTarget * kSplitTarget &&
+                  kFewWideItems * 9 / 5 <= kPartsPerTarget * kSplitTarget &&
+                  kWideSlots + kFewWideItems <= kPartsPerTarget * kSplitTarget,
+              "pv_attn_workspace_bytes counts on it");
 
 // Where the lists of a plan live on a device: pointers into one buffer laid out as the plan's
 // host image (see pv_plan::image).  The launchers take the lists through this, so that the same

@@ -364,7 +364,12 @@ def test_workspace_bound_covers_plans(pv):
     # mixed batch routed to one kernel, seeded random mixes
     rng = np.random.default_rng(23)
     shapes = [([50000], [1], 64, 8), ([300] * 200 + [60000], [1] * 201, 8, 8),
-              ([40000, 100, 7000], [200, 1, 1], 8, 2), ([20000], [64], 2, 1)]
+              ([40000, 100, 7000], [200, 1, 1], 8, 2), ([20000], [64], 2, 1),
+              # short and long lists of each kernel that are cut; items of the 256-row kernel that are
+              # too long for it, more of them than a list is cut into parts
+              ([2000] * 65, [1] * 65, 64, 8), ([500] * 62 + [32000], [1] * 63, 64, 8),
+              ([600, 4000, 9000] * 27, [1] * 81, 64, 8), ([300] * 15 + [30000], [100] * 16, 40, 40),
+              ([60000] * 3, [100] * 3, 40, 40), ([200000] * 16, [512] * 16, 64, 8)]
     for _ in range(20):
         n = int(rng.integers(1, 40))
         shapes.append((rng.integers(0, 30000, n).tolist(),
@@ -372,7 +377,7 @@ def test_workspace_bound_covers_plans(pv):
                        int(rng.choice([8, 16])), int(rng.choice([1, 2, 8]))))
     for ctx, qn, hq, hkv in shapes:
         desc = pv.pool_desc(1 << 16, hkv, 128, "bf16")
-        plan = pv.plan_create(desc, hq, ctx, qn, 4096)
+        plan = pv.plan_create(desc, hq, ctx, qn, 1 << 14)
         kv_max = max([c + q for c, q in zip(ctx, qn)] + [0])
         bound = pv.attn_workspace_bytes(desc, hq, len(ctx), int(sum(qn)), kv_max)
         need = (pv.plan_workspace_bytes(plan) + 255) // 256 * 256 + pv.plan_device_bytes(plan)
