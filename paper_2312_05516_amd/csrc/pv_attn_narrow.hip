@@ -26,15 +26,15 @@ struct NarrowFrag {
     u32x4 v[D / 16];     // [16-wide block of d]
 };
 
-// TWO: the probabilities enter the second product as two 16-bit terms, 95 % of the value and the rest,
-// which is rounded to a twentieth of the error of one term.  With one term the largest probability of
-// a wavefront's keys is exactly 1 and the others are rounded, so that fewer and longer parts of a KV
-// range mean results further from those in 64 bits (56 requests over 2 K keys, 64/8 heads, bf16:
-// 2.117e-3 in three parts, 2.182e-3 whole).  With two the error is that of the result's own rounding
-// (1.66e-3), so lists that are cut into fewer parts (pv_plan::narrow_two_terms) take it: 8 more
-// matrix-core instructions and about 40 of the vector ALU per block, 4 generation steps over 0.7-9 K
-// keys 23.6 -> 23.9 us.  Both terms of a positive probability are positive, so that an infinite V
-// gives infinity and not infinity minus infinity.
+// TWO: the probabilities enter the second product as two 16-bit terms, 95 % of the value and the
+// rest, which is rounded to a twentieth of the error of one term.  With one term the largest
+// probability of a wavefront's keys is exactly 1 and the others are rounded, so that fewer and
+// longer parts of a KV range mean results further from those in 64 bits (56 requests over 2 K
+// keys, 64/8 heads, bf16: 2.117e-3 in three parts, 2.182e-3 whole).  With two the error is that of
+// the result's own rounding (1.66e-3), so lists that are cut into fewer parts
+// (pv_plan::narrow_two_terms) take it: 8 more matrix-core instructions and about 40 of the vector
+// ALU per block, 4 generation steps over 0.7-9 K keys 23.6 -> 23.9 us.  Both terms of a positive
+// probability are positive, so that an infinite V gives infinity and not infinity minus infinity.
 template <typename T, int D, bool TWO>
 __global__ __launch_bounds__(256, 2) void attn_narrow_kernel(
     const WorkItem *__restrict__ items, const uint16_t *__restrict__ q,
@@ -52,14 +52,16 @@ __global__ __launch_bounds__(256, 2) void attn_narrow_kernel(
     __shared__ float sm_m[NW][16];
     __shared__ float sm_l[NW][16];
 
-    // The item that is likely to take this workgroup's place: with all slots taken, workgroups start
-    // in order as others end, and this one is on the same XCD (the slots are a multiple of the XCDs).
-    // Its first page ids are fetched for that XCD's L2 while this item's K/V stream, so that of the
-    // dependent round trips in front of an item's first block (item, page ids, K/V) two are short.
-    // 32 requests x 8 tokens over 2048, 40 heads: 215.5 -> 213.0 us; 256 generation steps over 0.1-0.3
-    // K, 64/8 heads 52.2 -> 51.6.  Not for head size 64, where the one register more that lives
-    // through the loop gave another schedule of it (128 generation steps, 32/8 heads: 72 -> 76 us);
-    // the 128-row kernel, whose items are bound by arithmetic, gains nothing.
+    // The item that is likely to take this workgroup's place: with all slots taken, workgroups
+    // start in order as others end, and this one is on the same XCD (the slots are a multiple of
+    // the XCDs). Its first page ids are fetched for that XCD's L2 while this item's K/V stream, so
+    // that of the dependent round trips in front of an item's first block (item, page ids, K/V)
+    // two are short. Attention call by itself, three runs of each build in turn: 256 generation
+    // steps over 0.5-4 K, 40 heads, 1798 -> 1782 us (runs of one build within 1 us), 32 requests x
+    // 8 tokens over 2048 203.1 -> 200.9 (0.2), 64 generation steps over 0.2-0.9 K 105.5 -> 105.2.
+    // Not for head size 64, where the one register more that lives through the loop gave another
+    // schedule of it (128 generation steps, 32/8 heads: 72 -> 76 us); the 128-row kernel, whose
+    // items are bound by arithmetic, gains nothing.
     constexpr bool AHEAD = D == 128;
     int next_req = -1, next_pg = 0;
     if (AHEAD && blockIdx.x + (unsigned)kNarrowSlots < gridDim.x) {
@@ -295,10 +297,11 @@ __global__ __launch_bounds__(256, 2) void attn_narrow_kernel(
     }
 }
 
-// Merge of split-KV partial results: out = sum_s 2^(m_s - M) O_s / sum_s 2^(m_s - M) l_s.
-// One workgroup = eight groups of 32 threads; CombineItem::groups of them share a row, each taking every
-// so-manyth part (D/32 output elements per thread), and add up through LDS.  The parts of a row are
-// megabytes apart from any other access, so what bounds this kernel is the number of dependent round
+// Merge of split-KV partial results: out = sum_s 2^(m_s - M) O_s / sum_s 2^(m_s - M) l_s. One
+// workgroup = eight groups of 32 threads; CombineItem::groups of them share a row, each taking
+// every so-manyth part (D/32 output elements per thread), and add up through LDS.  The parts of a
+// row lie row_count * D * 4 bytes apart (up to 8 KiB for items of the narrow kernel, 64 and 128
+// KiB for the others), so what bounds this kernel with few rows is the number of dependent round
 // trips to memory: the 32 threads read all (max, sum) pairs of the row at once, and the partial
 // outputs of a thread are independent loads.
 template <typename T, int D>

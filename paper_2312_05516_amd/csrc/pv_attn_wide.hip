@@ -7,21 +7,22 @@
 // never materialised.
 //
 // Mapping to gfx950.  One workgroup = 4 wavefronts = one item; wavefront w owns rows 32w..32w+31.
-// The K/V page tiles of a block (two pages; four for head size 64) are copied from HBM straight into LDS
-// (global_load_lds, 16 bytes per lane, fully coalesced because a (page, head) tile is contiguous
-// in the pool; no register staging, no ds_write) into a ring of three stages, two blocks ahead of
-// their use, and every wavefront reads its matrix-core operands from there, so a tile is fetched
-// once for all 128 rows.  The pool keeps runs of 8 elements along the contracted dimension
-// together, so the plain linear copy already puts the operands where 16 consecutive lanes read 256
-// consecutive bytes (no bank conflicts, no padding, no transposes).  Scores are produced
-// transposed, S^T = K Q^T (v_mfma_f32_32x32x16), so each lane owns one query row (softmax without
-// cross-lane traffic except one exchange for the maximum) and the probabilities are already the B
-// operand of O^T += V^T P^T.  About 160 VGPRs (145 for head size 64) and 48 KiB of LDS let three workgroups share a CU, whose
-// wavefronts overlap each other's matrix-core, vector-ALU and LDS phases.  One raw s_barrier per
-// block, preceded by a wait that leaves only the newest loads in flight.  Blocks that touch the
-// causal boundary or the end of the sequence take a separate, masked instantiation so the
-// steady-state loop has no branches.  The running maximum is only moved when a new score exceeds
-// it by more than 2^8 (softmax is shift-invariant), which makes rescaling the accumulator rare.
+// The K/V page tiles of a block (two pages; four for head size 64) are copied from HBM straight
+// into LDS (global_load_lds, 16 bytes per lane, fully coalesced because a (page, head) tile is
+// contiguous in the pool; no register staging, no ds_write) into a ring of three stages, two
+// blocks ahead of their use, and every wavefront reads its matrix-core operands from there, so a
+// tile is fetched once for all 128 rows.  The pool keeps runs of 8 elements along the contracted
+// dimension together, so the plain linear copy already puts the operands where 16 consecutive
+// lanes read 256 consecutive bytes (no bank conflicts, no padding, no transposes).  Scores are
+// produced transposed, S^T = K Q^T (v_mfma_f32_32x32x16), so each lane owns one query row (softmax
+// without cross-lane traffic except one exchange for the maximum) and the probabilities are
+// already the B operand of O^T += V^T P^T.  About 165 VGPRs (147 for head size 64) and 48 KiB of
+// LDS let three workgroups share a CU, whose wavefronts overlap each other's matrix-core,
+// vector-ALU and LDS phases.  One raw s_barrier per block, preceded by a wait that leaves only the
+// newest loads in flight.  Blocks that touch the causal boundary or the end of the sequence take a
+// separate, masked instantiation so the steady-state loop has no branches.  The running maximum is
+// only moved when a new score exceeds it by more than 2^8 (softmax is shift-invariant), which
+// makes rescaling the accumulator rare.
 #include <type_traits>
 
 #include "pv_device.h"
@@ -29,7 +30,7 @@
 namespace pv {
 
 // RENEW: some item has renew_blocks.  Lists without any keep an instantiation of their own (with the
-// test for it in the loop they take 1 % longer: 64 mixed requests, 64/8 heads, 270.5 -> 273.1 us).
+// test for it in the loop they take 1 % longer: 64 mixed requests, 64/8 heads, 270.5 -> 273.1 us)
 template <typename T, int D, bool RENEW>
 __global__ __launch_bounds__(256, 3) void attn_wide_kernel(
     const WorkItem *__restrict__ items, const uint16_t *__restrict__ q,
@@ -38,10 +39,11 @@ __global__ __launch_bounds__(256, 3) void attn_wide_kernel(
     int32_t num_kv_heads, int32_t group, float scale_log2e, uint32_t q_sign,
     uint16_t *__restrict__ out, float *__restrict__ ws_o, float *__restrict__ ws_ml)
 {
-    // Keys per block: 32 for head size 128; 64 for head size 64, where 32 keys are only 8 matrix-core
-    // instructions of a wavefront against about 70 of the vector ALU, a barrier, a test for the
-    // maximum and two LDS round trips.  48 requests over 0.1-3 K tokens, 32/8 heads: 108.8 -> 104.1 us
-    // whole step.  (Head size 128 would need 231 registers a lane for 64 keys, two workgroups per CU.)
+    // Keys per block: 32 for head size 128; 64 for head size 64, where 32 keys are only 8
+    // matrix-core instructions of a wavefront against about 70 of the vector ALU, a barrier, a
+    // test for the maximum and two LDS round trips.  48 requests over 0.1-3 K tokens, 32/8 heads:
+    // 108.8 -> 104.1 us whole step.  (Head size 128 would need 231 registers a lane for 64 keys,
+    // two workgroups per CU.)
     constexpr int PAGES = D == 128 ? 2 : 4;
     constexpr int BK = 16 * PAGES;
     constexpr int NT = BK / 32;                 // 32-key score tiles of a block
@@ -84,9 +86,9 @@ __global__ __launch_bounds__(256, 3) void attn_wide_kernel(
         const uint16_t *qrow = q + ((int64_t)(it.q_row0 + tok) * num_q_heads + hq) * D;
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
-            // loaded without a condition (a lane without a row reads the request's first one): eight
-            // branches less in front of the page ids; 19 first prompts, 64/8 heads 33.0 -> 32.5 us, 8
-            // longer ones, 40/40 heads 181.7 -> 179.6
+            // loaded without a condition (a lane without a row reads the request's first one):
+            // eight branches less in front of the page ids; 19 first prompts, 64/8 heads 33.0 ->
+            // 32.5 us, 8 longer ones, 40/40 heads 181.7 -> 179.6
             const u32x4 got = load16(qrow + 16 * ks + 8 * h);
             u32x4 raw = {0u, 0u, 0u, 0u};
             if (valid) raw = got;
@@ -139,7 +141,8 @@ __global__ __launch_bounds__(256, 3) void attn_wide_kernel(
         for (int v = 0; v < 16; ++v) o[blk][v] = 0.f;
     float m_run = -INFINITY;  // reference maximum of the RAW scores (before scaling)
     float m_top = -INFINITY;  // the highest reference so far (RENEW)
-    float m_cmp = -INFINITY;  // what the test for a new reference compares with: m_run, but for a renewal
+    float m_cmp = -INFINITY;  // what the test for a new reference compares with (RENEW): m_run, lower
+                              // for a renewal
     float l_run = 0.f;        // this lane's share of the running sum
     float mc = 0.f;           // m_run in the exp2 domain (0 while there is no reference yet)
 
@@ -200,8 +203,8 @@ __global__ __launch_bounds__(256, 3) void attn_wide_kernel(
                 for (int blk = 0; blk < NB; ++blk) o[blk] *= alpha;
             }
         }
-        // page by page: the matrix-core work of a page is issued before the exponentials of the next,
-        // so that inside this wavefront the two have something to overlap with
+        // page by page: the matrix-core work of a page is issued before the exponentials of the
+        // next, so that inside this wavefront the two have something to overlap with
         float psum = 0.f;
 #pragma unroll
         for (int pg = 0; pg < PAGES; ++pg) {
@@ -256,7 +259,7 @@ __global__ __launch_bounds__(256, 3) void attn_wide_kernel(
         __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, 0));
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
-    const float renew_margin = (kLazyLog2 + kRenewLog2) / scale_log2e;  // +inf for a zero scale: never
+    const float renew_margin = (kLazyLog2 + kRenewLog2) / scale_log2e;  // zero scale: +inf, never
     int to_renewal = it.renew_blocks ? it.renew_blocks + 1 : 0;  // 0: counts down and never gets there
     for (int b = 0; b < nblocks; ++b) {
         const bool more = b + 2 < nblocks;
@@ -264,8 +267,9 @@ __global__ __launch_bounds__(256, 3) void attn_wide_kernel(
         page_ids(b + 3, id0, id1);
         const int kb0 = it.kv_begin + BK * b;
         if constexpr (RENEW) {
-            // A renewal takes the block's own maximum as the reference also where it is lower, by no more
-            // than 2^kRenewLog2 than any reference so far, so that nothing grows by more than that.
+            // A renewal takes the block's own maximum as the reference also where it is lower, by
+            // no more than 2^kRenewLog2 than any reference so far, so that nothing grows by more
+            // than that.
             m_cmp = m_run;
             if (--to_renewal == 0) {
                 to_renewal = it.renew_blocks;

@@ -412,7 +412,7 @@ pv_status pv_kv_append(const pv_pool_desc *pool, const void *k_new, const void *
         return PV_ERR_INVALID_ARG;
     // The positions travel as kernel arguments, up to kAppendReqs requests a launch, in place of a
     // temporary list that had to be allocated, copied, waited for and freed: with the host function
-    // of the attention call gone too, 129 -> 68 us for an append and the attention behind it (3
+    // of the attention call gone too, 130 -> 69 us for an append and the attention behind it (3
     // requests over 2 K tokens, 64/8 heads).
     hipStream_t st = static_cast<hipStream_t>(stream);
     pv::AppendReqs reqs;
@@ -553,10 +553,10 @@ size_t pv_attn_workspace_bytes(const pv_pool_desc *pool, int32_t num_q_heads, in
     if (!pv::pool_desc_valid(pool, nullptr) || num_q_heads <= 0 || num_reqs < 0 || total_q < 0 ||
         max_kv_len < 0)
         return 0;
-    // Rows of partial results.  Each of the three lists has at most kPartsPerTarget * split_target parts
-    // of cut items, of at most kNarrowRows, kWideRows resp. kTileRows rows; beyond that the 256-row
-    // kernel's items are cut at kTileMaxKeys however many they are.  Independently, a row can be in at
-    // most max_kv_len / min_split_keys + 1 parts.
+    // Rows of partial results.  Each of the three lists has at most kPartsPerTarget * split_target
+    // parts of cut items, of at most kNarrowRows, kWideRows resp. kTileRows rows; beyond that the
+    // 256-row kernel's items are cut at kTileMaxKeys however many they are.  Independently, a row
+    // can be in at most max_kv_len / min_split_keys + 1 parts.
     const pv::Tuning t = pv::default_tuning();
     const int64_t rows = (int64_t)total_q * num_q_heads +
                          (int64_t)num_reqs * pool->num_kv_heads * pv::kNarrowRows;

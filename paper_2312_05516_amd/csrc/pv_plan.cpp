@@ -72,8 +72,8 @@ static int64_t item_cost(const WorkItem &w, int rows_per_step)
     return (int64_t)(w.kv_end - w.kv_begin) * steps;
 }
 
-// A way to cut a list: every item longer than `longest_whole` (and of at least 2 * min_keys keys) into
-// parts of about `chunk` keys, evened out and rounded up to whole blocks.
+// A way to cut a list: every item longer than `longest_whole` (and of at least 2 * min_keys keys)
+// into parts of about `chunk` keys, evened out and rounded up to whole blocks.
 struct Cut {
     int64_t chunk, longest_whole, min_keys;
     int32_t parts(int64_t len) const
@@ -88,8 +88,8 @@ struct Cut {
     }
 };
 
-// The cut into about `target` equal parts: every item of a list that is shorter than that, only items
-// more than twice as long as a target-th of the keys in a longer one.
+// The cut into about `target` equal parts: every item of a list that is shorter than that, only
+// items more than twice as long as a target-th of the keys in a longer one.
 static Cut target_cut(int64_t total_keys, size_t items, int32_t target, const Tuning &tune)
 {
     Cut c;
@@ -112,31 +112,33 @@ struct CutRule {
 };
 
 // Cut long items into parts of the KV range.  A cut is not free: every part pays the set-up of an
-// item, writes its rows in fp32, and the merge reads them back.  Returns true where an item gets fewer
-// parts than the cut into about split_target parts gives it.
-//  * Parts that all run at once are best where little more than a slots-th of the keys each does it:
-//    one part more than there are slots starts when the others are nearly done.  4 generation steps
-//    over 0.7-9 K keys, 64/8 heads, attention alone: 512 parts 19.1 us, 568 parts 21.7, 416 20.2.  Lists
-//    of 416 to 512 equal items are left whole by that (480 over 2 K keys: 75.5 us, 85.9 in 3 parts each;
-//    376, which 1.25 does not reach: 68.5 whole, 63.1 in two, 69.4 in three).
+// item, writes its rows in fp32, and the merge reads them back.  Returns true where an item gets
+// fewer parts than the cut into about split_target parts gives it.
+//  * Parts that all run at once are best where little more than a slots-th of the keys each does
+//    it: one part more than there are slots starts when the others are nearly done.  4 generation
+//    steps over 0.7-9 K keys, 64/8 heads, attention alone: 512 parts 19.1 us, 568 parts 21.7, 416
+//    20.2.  Lists of 416 to 512 equal items are left whole by that (480 over 2 K keys: 75.5 us,
+//    85.9 in 3 parts each; 376, which 1.25 does not reach: 68.5 whole, 63.1 in two, 69.4 in
+//    three).
 //  * Otherwise the narrow kernel, which is bound by bandwidth, wants about 1024 parts, so that no
-//    workgroup walks a long item alone while the others have left: 62 requests over 500 keys and one
-//    over 32 K, 64/8 heads, 48.3 us (211 in parts that run at once: the short items take up their
-//    slots); 520 equal items 94.7 us (101 whole).  From 640 items on (head size 128) enough run behind
-//    one another for cutting outliers alone: 672 items over 0.1-8 K keys 83.3 us against 86.0, 720
-//    equal ones 112 whole against 121 in two parts (800: 140 against 139).  Not so for head size 64,
-//    where an item takes half the time per key: 45.8 against 42.2.
-//  * The 128-row kernel, bound by its arithmetic, with 16 times the rows to merge, takes as few parts
-//    as keep the longest within twice a slots-th of the keys: 11 requests of 100 tokens and one over 30
-//    K, 40/40 heads, 163 us against 177 in about 1024 parts, 10 of 128 tokens over 1000 whole 53
-//    against 90, 19 (760 items, one over 30 K) 170 against 188.
-//  * Nothing is cut where the merge costs more than the shorter longest item gives: a launch of about
-//    7 us, and 8 bytes per partial row element at about 4 TB/s.  16 generation steps over 520-640 keys
-//    are left whole (10.8-11.2 us; cut 11.7), over 900 cut (11.9; whole 14.9); head size 64 up to 1000
-//    (9.0 against 11.7 at 640, 13.4 against 11.7 at 1400).  6 requests of 100 tokens over 900 keys, 32/8
-//    heads, 128-row kernel: 19.0 whole, 27.6 cut; over 2500 40.6 and 38.8.  Where the cut of all long
-//    items does not pay, that of the longest few may.  Up to 128 items of the 128-row kernel are cut in
-//    any case: 80 items 19.8 us, 21.9 whole; 20 items 18.2 and 21.3; 120 items 22.1 and 22.7.
+//    workgroup walks a long item alone while the others have left: 62 requests over 500 keys and
+//    one over 32 K, 64/8 heads, 48.3 us (211 in parts that run at once: the short items take up
+//    their slots); 520 equal items 94.7 us (101 whole).  From 640 items on (head size 128) enough
+//    run behind one another for cutting outliers alone: 672 items over 0.1-8 K keys 83.3 us
+//    against 86.0, 720 equal ones 112 whole against 121 in two parts (800: 140 against 139).  Not
+//    so for head size 64, where an item takes half the time per key: 45.8 against 42.2.
+//  * The 128-row kernel, bound by its arithmetic, with 16 times the rows to merge, takes as few
+//    parts as keep the longest within twice a slots-th of the keys: 11 requests of 100 tokens and
+//    one over 30 K, 40/40 heads, 163 us against 177 in about 1024 parts, 10 of 128 tokens over
+//    1000 whole 53 against 90, 19 (760 items, one over 30 K) 170 against 188.
+//  * Nothing is cut where the merge costs more than the shorter longest item gives: a launch of
+//    about 7 us, and 8 bytes per partial row element at about 4 TB/s.  16 generation steps over
+//    520-640 keys are left whole (10.8-11.2 us; cut 11.7), over 900 cut (11.9; whole 14.9); head
+//    size 64 up to 1000 (9.0 against 11.7 at 640, 13.4 against 11.7 at 1400).  6 requests of 100
+//    tokens over 900 keys, 32/8 heads, 128-row kernel: 19.0 whole, 27.6 cut; over 2500 40.6 and
+//    38.8.  Where the cut of all long items does not pay, that of the longest few may.  Up to 128
+//    items of the 128-row kernel are cut in any case: 80 items 19.8 us, 21.9 whole; 20 items 18.2
+//    and 21.3; 120 items 22.1 and 22.7.
 //  * Whatever the list, no part is longer than max_len keys (0 = no such limit).
 // No rule (the 256-row kernel), or a target set by hand: target_cut.
 static bool split_items(std::vector<WorkItem> &items, std::vector<CombineItem> &combine,

@@ -23,13 +23,14 @@ struct WorkItem {
     int32_t partial_base; // first workspace row slot of this item (split_count > 1), else -1
     int32_t q_row0;       // q_start[req]
     int32_t ctx;          // ctx_lens[req]
-    // 128-row kernel: the reference maximum is renewed every so many blocks (0 = never), where a part
-    // would begin if the KV range were cut into about split_target parts.  A probability is rounded to
-    // 16 bits unless it is the reference's own, which is exactly 1, so that fewer parts alone would
-    // mean results further from those in 64 bits.  Error against that cut's, without and with renewal,
-    // and time of the attention call: 10 requests, 128 tokens over 1000, 40/40 heads, bf16, whole
-    // instead of in three parts +0.77 % / 0.00 %, 51.1 / 51.0 us (the three parts take 85); 6 of 50 tokens
-    // over 900, 64/8 heads, whole instead of in four +1.32 % / 0.00 %, 28.5 / 30.0 us.
+    // 128-row kernel: the reference maximum is renewed every so many blocks (0 = never), where a
+    // part would begin if the KV range were cut into about split_target parts.  A probability is
+    // rounded to 16 bits unless it is the reference's own, which is exactly 1, so that fewer parts
+    // alone would mean results further from those in 64 bits.  Error against that cut's, without
+    // and with renewal, and time of the attention call: 10 requests, 128 tokens over 1000, 40/40
+    // heads, bf16, whole instead of in three parts +0.77 % / 0.00 %, 51.1 / 51.0 us (the three
+    // parts take 85); 6 of 50 tokens over 900, 64/8 heads, whole instead of in four +1.32 % / 0.00
+    // %, 28.5 / 30.0 us.
     int32_t renew_blocks;
 };
 static_assert(sizeof(WorkItem) == 48, "WorkItem is read by the kernels as 12 int32");
@@ -47,15 +48,16 @@ struct CombineItem {
 };
 static_assert(sizeof(CombineItem) == 32, "CombineItem is read by the kernels as 8 int32");
 
-// How many of a merge workgroup's eight thread groups share one row, by the number of parts to add:
-// with few parts one group reads them all, with many the reads are spread over the groups, so that
-// nobody reads more than four parts after one another up to 32 of them.  But only as long as that is
-// no more than kMergeGroups workgroups for the rows of the whole merge: more rows than that keep the
-// GPU busy by themselves, and every further group of a row reads the row's (max, sum) pairs again.
-// Attention call, with and without that limit: 2 prompts of 256 tokens over 2 K and 16 K, 64/8 heads,
-// 210 and 219 us; 128 tokens over 16 K, 40/40 heads, 84.8 and 88.4; 200 over 30 K, 32/8 heads, 78.3 and
-// 81.3; 56 generation steps (288 items of 8 rows) 66.7 and 67.2; 4 of them (32 items) 19.2 either way,
-// 21.0 with one group a row.  Limits of 1024 and 2048: the same within 1 us.
+// How many of a merge workgroup's eight thread groups share one row, by the number of parts to
+// add: with few parts one group reads them all, with many the reads are spread over the groups, so
+// that nobody reads more than four parts after one another up to 32 of them.  But only as long as
+// that is no more than kMergeGroups workgroups for the rows of the whole merge: more rows than
+// that keep the GPU busy by themselves, and every further group of a row reads the row's (max,
+// sum) pairs again.  Attention call, with and without that limit: 2 prompts of 256 tokens over 2 K
+// and 16 K, 64/8 heads, 210 and 219 us; 128 tokens over 16 K, 40/40 heads, 84.8 and 88.4; 200 over
+// 30 K, 32/8 heads, 78.3 and 81.3; 56 generation steps (288 items of 8 rows) 66.7 and 67.2; 4 of
+// them (32 items) 19.2 either way, 21.0 with one group a row.  Limits of 1024 and 2048: the same
+// within 1 us.
 constexpr int kMergeGroups = 512;
 constexpr int combine_groups(int split_count, int64_t merge_rows)
 {
@@ -81,18 +83,19 @@ struct AppendGroup {
 };
 static_assert(sizeof(AppendGroup) == 16, "AppendGroup is read by the kernel as 4 int32");
 
-// Append and rotary kernels: new rows of more bytes than this, the L2 caches of all XCDs together, are
-// read with the streaming hint, because they are read once and what is written (K/V pages, rotated
-// queries) is read by the attention that follows: 53 MB (2600 tokens, 40 heads), append and attention
-// 187.0 -> 184.7 us (219 -> 217 with the kernel that writes the rows in front); 7 K tokens with the
-// rotary embedding see pick_rope.  A smaller batch finds its
-// rows in a cache when they come from the kernel before: 14 MB (2736 tokens, 10 heads) 64.5 us, 67.3
-// with the hint; 4 generation steps with the rotary embedding 26.0 and 26.3.  Streaming the stores too
-// is slower (first prompts 193 -> 204 us).
+// Append and rotary kernels: new rows of more bytes than this, the L2 caches of all XCDs together,
+// are read with the streaming hint, because they are read once and what is written (K/V pages,
+// rotated queries) is read by the attention that follows: 53 MB (2600 tokens, 40 heads), append
+// and attention 187.0 -> 184.7 us (219 -> 217 with the kernel that writes the rows in front); 7 K
+// tokens with the rotary embedding see pick_rope.  A smaller batch finds its rows in a cache when
+// they come from the kernel before: 14 MB (2736 tokens, 10 heads) 64.5 us, 67.3 with the hint; 4
+// generation steps with the rotary embedding 26.0 and 26.3.  Streaming the stores too is slower
+// (first prompts 193 -> 204 us).
 constexpr int64_t kStreamBytes = 32 << 20;
 
-// Requests with new tokens that the append takes as a kernel argument, and how many one launch takes
-// (2 KB of arguments).  Request i of the launch has the append groups group0[i] .. group0[i + 1] - 1.
+// Requests with new tokens that the append takes as a kernel argument, and how many one launch
+// takes (2 KB of arguments).  Request i of the launch has the append groups group0[i] .. group0[i
+// + 1] - 1.
 struct AppendReq {
     int32_t req;
     int32_t t_begin;  // logical position of its first new token
@@ -115,9 +118,10 @@ constexpr int64_t append_group_count(int64_t t_begin, int64_t count)
 constexpr int kNarrowRows = 16;  // rows per item of the bandwidth-oriented kernel
 constexpr int kWideRows = 128;   // rows per item of the matrix-core kernel (4 waves x 32 rows)
 constexpr int kTileRows = 256;   // rows per item of the 256-row matrix-core kernel (4 waves x 64)
-// Workgroups that run at once on the 256 CUs: two of the narrow kernel on each (212 registers a lane;
-// head size 64 has room for three, but 512 parts are ahead of more: 4 generation steps, 32/8 heads,
-// 13.4 us with 512 parts, 14.2 with 656), three of the 128-row kernel (168 registers, 48 KiB of LDS).
+// Workgroups that run at once on the 256 CUs: two of the narrow kernel on each (212-216 registers
+// a lane; head size 64 has room for three, but 512 parts are ahead of more: 4 generation steps,
+// 32/8 heads, 13.4 us with 512 parts, 14.2 with 656), three of the 128-row kernel (162-165
+// registers, 48 KiB of LDS).
 constexpr int kNarrowSlots = 512;
 constexpr int kWideSlots = 768;
 constexpr int kSplitTarget = 1024;
@@ -129,10 +133,11 @@ constexpr int kTileMaxPages = 8192;  // page ids an item of the 256-row kernel m
                                      // them in LDS): its KV range is at most 16 times that
 constexpr int kTileMaxKeys = kTileMaxPages * 16 - kKvBlock;
 
-// No list has more parts of cut items than this times the target (see split_items): with a chunk of a
-// target-th of the keys, `target` parts and one more for each cut item, of which there are no more than
-// `target`; the other cuts take a slots-th or a long_share-th of the keys for their chunk or more, and
-// no more items are cut than there are in a short list or four fifths of that share.
+// No list has more parts of cut items than this times the target (see split_items): with a chunk
+// of a target-th of the keys, `target` parts and one more for each cut item, of which there are no
+// more than `target`; the other cuts take a slots-th or a long_share-th of the keys for their
+// chunk or more, and no more items are cut than there are in a short list or four fifths of that
+// share.
 constexpr int kPartsPerTarget = 2;
 static_assert(kNarrowSlots * 9 / 5 <= kPartsPerTarget * kSplitTarget &&
                   kFewWideItems * 9 / 5 <= kPartsPerTarget * kSplitTarget &&
@@ -155,8 +160,8 @@ struct Tuning {
     int32_t split_target;    // cut a list that is shorter into about this many work items
     bool split_by_hand;      // whatever the kernel (see split_items)
     int32_t min_split_keys;  // items are cut from twice this many keys on, by parts of at least this
-                             // many before they are evened out (which leaves at least half of it, and
-                             // less in an item's last part)
+                             // many before they are evened out (which leaves at least half of it,
+                             // and less in an item's last part)
     int32_t wide_min_rows;   // (request, KV head) units with n*G >= this use the matrix-core
                              // kernel; smaller ones are cut into 16-row items of the narrow kernel
     int32_t xcds;            // L2 domains the work list is interleaved over
@@ -188,8 +193,8 @@ struct pv_plan {
     std::vector<pv::CombineChunk> combine_chunks;
     int64_t partial_slots;  // workspace row slots
     // Where an item gets fewer parts than the cut into about split_target parts gives it (see
-    // split_items): the narrow kernel takes its probabilities in two 16-bit terms, items of the 128-row
-    // kernel renew their reference
+    // split_items): the narrow kernel takes its probabilities in two 16-bit terms, items of the
+    // 128-row kernel renew their reference
     bool narrow_two_terms, wide_renews;
     size_t workspace_bytes;
 

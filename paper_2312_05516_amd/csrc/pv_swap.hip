@@ -1,17 +1,18 @@
 // Page gather / scatter for tier swapping: whole pages leave the GPU pools for a staging buffer
-// (swap-out, paper Section 4.3.2) and come back into newly assigned pages (swap-in, Section 4.3.3).
-// The staging buffer may be device memory or pinned host memory that the GPU can address; with the
-// latter the copy crosses PCIe inside the kernel, with no intermediate device buffer.
+// (swap-out, paper Section 4.3.2) and come back into newly assigned pages (swap-in, Section
+// 4.3.3).  The staging buffer may be device memory or pinned host memory that the GPU can address;
+// with the latter the copy crosses PCIe inside the kernel, with no intermediate device buffer.
 //
 // Staging layout: for the i-th listed page, its K image (num_kv_heads * 16 * D elements, exactly
 // as in the pool) followed by its V image.  One workgroup moves one 4 KiB piece with 16 bytes per
-// lane; pure copies, bit-exact.  Bound: HBM.  What is read is read once and carries the streaming hint,
-// and so does what is stored in the staging buffer.  Pages that come in are read by that layer's
-// attention next: their stores do not.  Copy in and the attention behind it, K and V of 160 KiB each a
-// page, without and with the hint on those stores: 64 pages 19.1 / 20.2 us, 128 29.6 / 31.4, 256 48.7 /
-// 49.4, 512 83.4 / 88.5, 1024 157.3 / 167.2 (the copy alone 122.9 / 110.5: the hint only moves the cost
-// into the attention); 1024 pages of 2 x 32 KiB 41.8 / 43.2.  More bytes per workgroup are slower (1024
-// pages of 2 x 160 KiB out and as many in, 4 KiB 219 us, 8 KiB 234, 16 KiB 240, 32 KiB 326).
+// lane; pure copies, bit-exact.  Bound: HBM.  What is read is read once and carries the streaming
+// hint, and so does what is stored in the staging buffer.  Pages that come in are read by that
+// layer's attention next: their stores do not.  Copy in and the attention behind it, K and V of
+// 160 KiB each a page, without and with the hint on those stores: 64 pages 19.1 / 20.2 us, 128
+// 29.6 / 31.4, 256 48.7 / 49.4, 512 83.4 / 88.5, 1024 157.3 / 167.2 (the copy alone 122.9 / 110.5:
+// the hint only moves the cost into the attention); 1024 pages of 2 x 32 KiB 41.8 / 43.2.  More
+// bytes per workgroup are slower (1024 pages of 2 x 160 KiB out and as many in, 4 KiB 219 us, 8
+// KiB 234, 16 KiB 240, 32 KiB 326).
 #include "pv_device.h"
 
 namespace pv {
