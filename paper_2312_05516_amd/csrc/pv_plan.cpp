@@ -109,6 +109,7 @@ struct CutRule {
     bool always_stretch; // also where they do not run at once even so (else: target_cut)
     int32_t key_ns;      // what a key less in the longest item saves while the GPU is not full
     int32_t always_cut;  // up to this many items that is not weighed against the merge
+    bool level_lists;    // lists of nearly equal items go by how full their last round of CUs is
 };
 
 // Cut long items into parts of the KV range.  A cut is not free: every part pays the set-up of an
@@ -123,10 +124,15 @@ struct CutRule {
 //  * Otherwise the narrow kernel, which is bound by bandwidth, wants about 1024 parts, so that no
 //    workgroup walks a long item alone while the others have left: 62 requests over 500 keys and
 //    one over 32 K, 64/8 heads, 48.3 us (211 in parts that run at once: the short items take up
-//    their slots); 520 equal items 94.7 us (101 whole).  From 640 items on (head size 128) enough
-//    run behind one another for cutting outliers alone: 672 items over 0.1-8 K keys 83.3 us
-//    against 86.0, 720 equal ones 112 whole against 121 in two parts (800: 140 against 139).  Not
-//    so for head size 64, where an item takes half the time per key: 45.8 against 42.2.
+//    their slots).  From 640 items on (head size 128) enough run behind one another for cutting
+//    outliers alone: 672 items over 0.1-8 K keys 83.3 us against 86.0.  Not so for head size 64,
+//    where an item takes half the time per key: 45.8 against 42.2.
+//  * With 513 to 1023 items of nearly the same length (the longest a quarter over the average at
+//    most) what counts is how many CUs the last round of 256 items leaves idle: whole against two
+//    parts, 2.5 K keys on average and +-10 % of that, head size 128: 520 items 121 us / 109, 640 132
+//    / 129, 672 136 / 145, 768 146 / 157, 784 170 / 170 (6 K keys: 410 / 394), 896 179 / 184 (426 /
+//    421), 928 181 / 197, 1016 193 / 211; head size 64: 640 70 / 67, 672 72 / 75, 768 76 / 79, 800
+//    90 / 86, 896 94 / 92, 928 95 / 99.  So whole where it is at least six tenths full.
 //  * The 128-row kernel, bound by its arithmetic, with 16 times the rows to merge, takes as few
 //    parts as keep the longest within twice a slots-th of the keys: 11 requests of 100 tokens and
 //    one over 30 K, 40/40 heads, 163 us against 177 in about 1024 parts, 10 of 128 tokens over
@@ -156,11 +162,16 @@ static bool split_items(std::vector<WorkItem> &items, std::vector<CombineItem> &
     Cut cut = even;
     if (rule) {
         auto blocks = [](int64_t keys) { return (keys + kKvBlock - 1) / kKvBlock * kKvBlock; };
-        if (rule->long_list && (int64_t)items.size() >= rule->long_list) {
+        const int64_t n = (int64_t)items.size();
+        if (rule->level_lists && n > rule->slots && n < tune.split_target &&
+            longest * n * 4 <= total_keys * 5) {
+            const int64_t rest = n % kCUs;
+            if (rest == 0 || rest * 5 >= kCUs * 3) cut.longest_whole = longest;
+        } else if (rule->long_list && n >= rule->long_list) {
             const int64_t share = (total_keys + rule->long_share - 1) / rule->long_share;
             cut.chunk = blocks(std::max<int64_t>(share, tune.min_split_keys));
             cut.longest_whole = cut.chunk + cut.chunk / 4;
-        } else if (rule->always_stretch || (int64_t)items.size() <= rule->slots) {
+        } else if (rule->always_stretch || n <= rule->slots) {
             auto at_once = [&](int64_t chunk) {
                 const Cut c = {chunk, chunk, cut.min_keys};
                 int64_t parts = 0;
@@ -197,7 +208,7 @@ static bool split_items(std::vector<WorkItem> &items, std::vector<CombineItem> &
                 const int64_t after =
                     few || rule->always_stretch ? std::max(whole, part_len) : part_len;
                 if ((longest - after) * rule->key_ns >= 7000 + part_rows * head_dim * 8 / 4000 ||
-                    (int64_t)items.size() <= rule->always_cut)
+                    n <= rule->always_cut)
                     break;
             }
             cut.chunk = cut.longest_whole = 2 * cut.longest_whole;
@@ -553,9 +564,9 @@ pv_status build_plan(const pv_pool_desc *pool, int32_t num_q_heads, const int32_
     const bool wide_rows = pool->head_dim == 128;
     const CutRule narrow_rule = {
         kNarrowSlots, wide_rows ? kNarrowSlots * 5 / 4 : 0, kNarrowSlots, 25, false,
-        wide_rows ? 16 : (int64_t)plan->narrow.size() > kNarrowSlots ? 12 : 9, 0};
+        wide_rows ? 16 : (int64_t)plan->narrow.size() > kNarrowSlots ? 12 : 9, 0, true};
     const CutRule wide_rule = {kWideSlots, kFewWideItems, kFewWideItems, 100, true,
-                               wide_rows ? 31 : 16, wide_rows ? 128 : 0};
+                               wide_rows ? 31 : 16, wide_rows ? 128 : 0, false};
     plan->narrow_two_terms =
         split_items(plan->narrow, plan->combine, slots, tune, &narrow_rule, pool->head_dim);
     plan->wide_renews =

@@ -118,7 +118,8 @@ constexpr int64_t append_group_count(int64_t t_begin, int64_t count)
 constexpr int kNarrowRows = 16;  // rows per item of the bandwidth-oriented kernel
 constexpr int kWideRows = 128;   // rows per item of the matrix-core kernel (4 waves x 32 rows)
 constexpr int kTileRows = 256;   // rows per item of the 256-row matrix-core kernel (4 waves x 64)
-// Workgroups that run at once on the 256 CUs: two of the narrow kernel on each (212-216 registers
+constexpr int kCUs = 256;
+// Workgroups that run at once on the CUs: two of the narrow kernel on each (212-216 registers
 // a lane; head size 64 has room for three, but 512 parts are ahead of more: 4 generation steps,
 // 32/8 heads, 13.4 us with 512 parts, 14.2 with 656), three of the 128-row kernel (162-165
 // registers, 48 KiB of LDS).

@@ -253,11 +253,15 @@ def test_plan_cuts_the_long_prompts_of_a_short_skewed_list(pv, short, long_ctx, 
     assert longest <= 2 * share + 32
 
 
-@pytest.mark.parametrize("reqs,parts", [(47, 2), (52, 1), (60, 1), (64, 1), (65, 2), (70, 2), (80, 1)])
-def test_plan_cuts_equal_items_by_how_they_fill_the_gpu(pv, reqs, parts):
-    """Equal items over 2 K keys, head size 128: whole where they fill (nearly) all of the 512 slots,
-    cut where they do not, or where a few would be left for a second round."""
-    plan = pv.plan_create(pv.pool_desc(1 << 17, 8, 128, "f16"), 64, [1999] * reqs, [1] * reqs, 4096)
+@pytest.mark.parametrize("reqs,parts", [(47, 2), (52, 1), (60, 1), (64, 1), (65, 2), (70, 2), (80, 2),
+                                        (84, 1), (96, 1), (98, 2), (110, 2), (116, 1), (127, 1),
+                                        (128, 1), (129, 1)])
+@pytest.mark.parametrize("head_dim", [64, 128])
+def test_plan_cuts_equal_items_by_how_they_fill_the_gpu(pv, reqs, parts, head_dim):
+    """Equal items (8 a request) over 2 K keys: whole where they fill nearly all of the 512 slots or
+    the last round of 256, cut where they do not."""
+    plan = pv.plan_create(pv.pool_desc(1 << 17, 8, head_dim, "f16"), 64, [1999] * reqs, [1] * reqs,
+                          4096)
     items = _items(pv, plan, 0)
     counts = {int(it[7]) for it in items}
     assert (counts == {1}) == (parts == 1) and (parts == 1 or min(counts) >= 2)
