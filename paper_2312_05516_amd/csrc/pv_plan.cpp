@@ -108,7 +108,7 @@ struct CutRule {
     int32_t stretch_pct; // parts may be longer than a slots-th of the keys by so much, to run at once
     bool always_stretch; // also where they do not run at once even so (else: target_cut)
     int32_t key_ns;      // what a key less in the longest item saves while the GPU is not full
-    int32_t always_cut;  // up to this many items that is not weighed against the merge
+    int32_t always_cut;  // up to this many parts that is not weighed against the merge
     bool level_lists;    // lists of nearly equal items go by how full their last round of CUs is
 };
 
@@ -142,9 +142,9 @@ struct CutRule {
 //    520-640 keys are left whole (10.8-11.2 us; cut 11.7), over 900 cut (11.9; whole 14.9); head
 //    size 64 up to 1000 (9.0 against 11.7 at 640, 13.4 against 11.7 at 1400).  6 requests of 100
 //    tokens over 900 keys, 32/8 heads, 128-row kernel: 19.0 whole, 27.6 cut; over 2500 40.6 and
-//    38.8.  Where the cut of all long items does not pay, that of the longest few may.  Up to 128
-//    items of the 128-row kernel are cut in any case: 80 items 19.8 us, 21.9 whole; 20 items 18.2
-//    and 21.3; 120 items 22.1 and 22.7.
+//    38.8.  Where the cut of all long items does not pay, that of the longest few may.  The 128-row
+//    kernel's items (head size 128) are cut in any case while every part has a CU of its own: 80
+//    items in 240 parts 19.8 us, 21.9 whole; 130 in 202 22.1 and 23.9; 20 in 56 18.2 and 21.3.
 //  * Whatever the list, no part is longer than max_len keys (0 = no such limit).
 // No rule (the 256-row kernel), or a target set by hand: target_cut.
 static bool split_items(std::vector<WorkItem> &items, std::vector<CombineItem> &combine,
@@ -195,9 +195,10 @@ static bool split_items(std::vector<WorkItem> &items, std::vector<CombineItem> &
         }
         // the cut of all long items, or where that does not pay, of the longest few
         for (bool few = false; cut.longest_whole < longest; few = true) {
-            int64_t part_rows = 0, whole = 0;
+            int64_t part_rows = 0, whole = 0, all_parts = 0;
             for (const WorkItem &w : items) {
                 const int64_t len = w.kv_end - w.kv_begin, parts = cut.parts(len);
+                all_parts += parts;
                 if (parts > 1)
                     part_rows += w.row_count * parts;
                 else
@@ -208,7 +209,7 @@ static bool split_items(std::vector<WorkItem> &items, std::vector<CombineItem> &
                 const int64_t after =
                     few || rule->always_stretch ? std::max(whole, part_len) : part_len;
                 if ((longest - after) * rule->key_ns >= 7000 + part_rows * head_dim * 8 / 4000 ||
-                    n <= rule->always_cut)
+                    all_parts <= rule->always_cut)
                     break;
             }
             cut.chunk = cut.longest_whole = 2 * cut.longest_whole;
@@ -566,7 +567,7 @@ pv_status build_plan(const pv_pool_desc *pool, int32_t num_q_heads, const int32_
         kNarrowSlots, wide_rows ? kNarrowSlots * 5 / 4 : 0, kNarrowSlots, 25, false,
         wide_rows ? 16 : (int64_t)plan->narrow.size() > kNarrowSlots ? 12 : 9, 0, true};
     const CutRule wide_rule = {kWideSlots, kFewWideItems, kFewWideItems, 100, true,
-                               wide_rows ? 31 : 16, wide_rows ? 128 : 0, false};
+                               wide_rows ? 31 : 16, wide_rows ? kCUs : 0, false};
     plan->narrow_two_terms =
         split_items(plan->narrow, plan->combine, slots, tune, &narrow_rule, pool->head_dim);
     plan->wide_renews =
