@@ -133,7 +133,7 @@ void pv_plan_destroy(pv_plan *plan);
  * copy on `stream`, allocates nothing and does not wait; launches on the same stream may follow
  * at once.  The buffer must stay untouched until the last launch that uses the plan has finished,
  * and the plan (the copy reads its host memory) must not be destroyed before `stream` has passed
- * the copy.
+ * the copy; where the copy was captured into a graph, not before the graph's last replay.
  *
  * pv_plan_upload: convenience.  Allocates device memory that the plan then owns (freed by
  * pv_plan_destroy), copies, and waits for the copy.  Idempotent.
@@ -226,7 +226,8 @@ pv_status pv_multi_token_paged_attn_planned(pv_plan *plan, const void *q, const 
  * All calls on one GPU share that GPU's array: two calls whose execution may overlap (different
  * streams, or the same plan replayed while an earlier launch still runs) race on it.  Nothing in
  * the array needs clearing between calls.  The plan must not be destroyed before `stream` has
- * passed the call (the copy reads its host memory).
+ * passed the call (the copy reads its host memory); in a captured graph, where the copy is repeated,
+ * not before the graph's last replay has passed it.
  */
 size_t pv_static_scratch_bytes(void);
 pv_status pv_multi_token_paged_attn_noalloc(pv_plan *plan, const void *q, const void *k_pages,
