@@ -16,11 +16,16 @@
 // lanes read 256 consecutive bytes (no bank conflicts, no padding, no transposes).  Scores are
 // produced transposed, S^T = K Q^T (v_mfma_f32_32x32x16), so each lane owns one query row (softmax
 // without cross-lane traffic except one exchange for the maximum) and the probabilities are
-// already the B operand of O^T += V^T P^T.  About 165 VGPRs (147 for head size 64) and 48 KiB of
+// already the B operand of O^T += V^T P^T.  About 166 VGPRs (142 for head size 64) and 48 KiB of
 // LDS let three workgroups share a CU, whose wavefronts overlap each other's matrix-core,
 // vector-ALU and LDS phases.  One raw s_barrier per block, preceded by a wait that leaves only the
-// newest loads in flight.  Blocks that touch the causal boundary or the end of the sequence take a
-// separate, masked instantiation so the steady-state loop has no branches.  The running maximum is
+// newest loads in flight.  Blocks that touch the causal boundary or the end of the sequence run in a
+// second loop, masked, so the steady-state loop has no branches and the registers for one kind of
+// block at a time: room to request all V operands of a block while its scores are computed, into
+// the registers that its K operands leave (two at a time before, each pair waited for).  Block by
+// block 2427 -> 2281 cycles with three workgroups on a CU, 2105 -> 1745 with one or two; the clock
+// gives back half of that (1.85 -> 1.78 GHz: the chip's power limit): 64 mixed requests, 64/8
+// heads, whole step 262.7 -> 255.6 us, 48 of head size 64 102.7 -> 99.7.  The running maximum is
 // only moved when a new score exceeds it by more than 2^8 (softmax is shift-invariant), which
 // makes rescaling the accumulator rare.
 #include <type_traits>
@@ -74,11 +79,13 @@ __global__ __launch_bounds__(256, 3) void attn_wide_kernel(
     const int wave_rows = it.row_count - 32 * w;  // may be <= 0
     int unmasked_end = it.ctx + (it.row_begin + 32 * w) / group + 1;
     if (unmasked_end > it.kv_end) unmasked_end = it.kv_end;
+    unmasked_end = __builtin_amdgcn_readfirstlane(unmasked_end);
     int wave_end = 0;
     if (wave_rows > 0) {
         const int last = it.row_begin + 32 * w + (wave_rows < 32 ? wave_rows : 32) - 1;
         wave_end = it.ctx + last / group + 1;
         if (wave_end > it.kv_end) wave_end = it.kv_end;
+        wave_end = __builtin_amdgcn_readfirstlane(wave_end);
     }
 
     vec8 qf[KS];
@@ -108,9 +115,7 @@ __global__ __launch_bounds__(256, 3) void attn_wide_kernel(
     const int last_pg = (it.kv_end - 1) >> 4;
     const int pg0 = it.kv_begin >> 4;
     const int nblocks = (it.kv_end - it.kv_begin + BK - 1) / BK;
-    const int64_t head_off = (int64_t)it.kv_head * (16 * D);
-    const int64_t page_stride = (int64_t)num_kv_heads * (16 * D);
-
+    const uint32_t page_bytes = (uint32_t)num_kv_heads * TILE_BYTES;
     const uint32_t lane_bytes = (uint32_t)lane * 16u;
     // asynchronous copies move bytes [w*1024, w*1024+1024) of every 4 KiB pass over the K (V) part:
     // ids of the pages that this wavefront's pieces of a block lie in (a page past the end is never
@@ -121,18 +126,22 @@ __global__ __launch_bounds__(256, 3) void attn_wide_kernel(
         id0 = pt[pg <= last_pg ? pg : last_pg];
         id1 = pt[pg + PAGES / 2 <= last_pg ? pg + PAGES / 2 : last_pg];
     };
-    // block b into stage b % 3, lane l the 16 bytes at 16*l of a piece (scalar base + lane offset)
-    auto dma_block = [&](int b, int id0, int id1) {
-        unsigned char *stage = smem[b % STAGES];
+    // the wavefront's pieces of a block into the stage at `stage`, lane l the 16 bytes at 16*l of a
+    // piece (scalar base + lane offset); both pieces of K (V) lie at the same place of their page
+    const uint64_t piece_off =
+        (uint64_t)it.kv_head * TILE_BYTES + (uint32_t)(w * 1024 % TILE_BYTES);
+    const unsigned char *k_src = reinterpret_cast<const unsigned char *>(k_pages) + piece_off;
+    const unsigned char *v_src = reinterpret_cast<const unsigned char *>(v_pages) + piece_off;
+    auto dma_block = [&](unsigned char *stage, int id0, int id1) {
 #pragma unroll
         for (int p = 0; p < PASSES; ++p) {
             const int off = p * 4096 + w * 1024;  // wavefront-uniform
-            const int page = p ? id1 : id0;
-            const int64_t elem = (int64_t)page * page_stride + head_off + (off % TILE_BYTES) / 2;
-            lds_dma16(k_pages + elem, lane_bytes, stage + off);
-            lds_dma16(v_pages + elem, lane_bytes, stage + HALF_BYTES + off);
+            const uint64_t page_off = (uint64_t)(uint32_t)(p ? id1 : id0) * page_bytes;
+            lds_dma16(k_src + page_off, lane_bytes, stage + off);
+            lds_dma16(v_src + page_off, lane_bytes, stage + HALF_BYTES + off);
         }
     };
+    static_assert(4096 % TILE_BYTES == 0, "a pass covers whole pages");
 
     f32x16 o[NB];
 #pragma unroll
@@ -148,6 +157,11 @@ __global__ __launch_bounds__(256, 3) void attn_wide_kernel(
 
     auto compute_block = [&](const unsigned char *sb, int kb0, auto masked_tag) {
         constexpr bool MASKED = decltype(masked_tag)::value;
+        u32x4 kf[NT * KS];  // K operands, requested as soon as the block is published
+#pragma unroll
+        for (int i = 0; i < NT * KS; ++i)
+            kf[i] = *reinterpret_cast<const u32x4 *>(sb + k_lds + (i / KS) * 2 * TILE_BYTES +
+                                                     (i % KS) * 512);
         f32x16 s[NT];
 #pragma unroll
         for (int t = 0; t < NT; ++t)
@@ -156,11 +170,21 @@ __global__ __launch_bounds__(256, 3) void attn_wide_kernel(
 #pragma unroll
         for (int t = 0; t < NT; ++t)
 #pragma unroll
-            for (int ks = 0; ks < KS; ++ks) {
-                const u32x4 kf = *reinterpret_cast<const u32x4 *>(sb + k_lds + t * 2 * TILE_BYTES +
-                                                                  ks * 512);
-                s[t] = T::mfma32(as_vec8<T>(kf), qf[ks], s[t]);
-            }
+            for (int ks = 0; ks < KS; ++ks)
+                s[t] = T::mfma32(as_vec8<T>(kf[t * KS + ks]), qf[ks], s[t]);
+        // all V operands are requested while the matrix cores work on the scores, so that they have
+        // arrived when the first exponentials are done (the masked loop has no registers for that)
+        __builtin_amdgcn_sched_barrier(0);
+        auto read_v = [&](int i) {
+            return *reinterpret_cast<const u32x4 *>(sb + v_lds + (i / NB) * TILE_BYTES +
+                                                    (i % NB) * 512);
+        };
+        u32x4 vf[PAGES * NB];
+        if constexpr (!MASKED) {
+#pragma unroll
+            for (int i = 0; i < PAGES * NB; ++i) vf[i] = read_v(i);
+        }
+        __builtin_amdgcn_sched_barrier(0);
         // register v = 8*page + j of tile t  <->  key kb0 + 32*t + 16*page + 8*h + j
         bool vis[NT][16];
         if constexpr (MASKED) {
@@ -224,18 +248,18 @@ __global__ __launch_bounds__(256, 3) void attn_wide_kernel(
             const vec8 pf = as_vec8<T>(praw);
 #pragma unroll
             for (int blk = 0; blk < NB; ++blk) {
-                u32x4 vf = *reinterpret_cast<const u32x4 *>(sb + v_lds + pg * TILE_BYTES + blk * 512);
+                u32x4 v = MASKED ? read_v(pg * NB + blk) : vf[pg * NB + blk];
                 if constexpr (MASKED) {  // slots past the end may hold anything: zero those values
 #pragma unroll
                     for (int jj = 0; jj < 4; ++jj) {
                         const int kk = kb0 + 16 * pg + 8 * h + 2 * jj;
-                        uint32_t word = vf[jj];
+                        uint32_t word = v[jj];
                         if (kk >= it.kv_end) word &= 0xFFFF0000u;
                         if (kk + 1 >= it.kv_end) word &= 0x0000FFFFu;
-                        vf[jj] = word;
+                        v[jj] = word;
                     }
                 }
-                o[blk] = T::mfma32(as_vec8<T>(vf), pf, o[blk]);
+                o[blk] = T::mfma32(as_vec8<T>(v), pf, o[blk]);
             }
         }
         l_run += psum;
@@ -245,10 +269,10 @@ __global__ __launch_bounds__(256, 3) void attn_wide_kernel(
     // of the block after next are always fetched one iteration early
     int id0, id1;
     page_ids(0, id0, id1);
-    dma_block(0, id0, id1);
+    dma_block(smem[0], id0, id1);
     if (nblocks > 1) {
         page_ids(1, id0, id1);
-        dma_block(1, id0, id1);
+        dma_block(smem[1], id0, id1);
     }
     page_ids(2, id0, id1);
     asm volatile("" ::: "memory");
@@ -261,11 +285,12 @@ __global__ __launch_bounds__(256, 3) void attn_wide_kernel(
     asm volatile("" ::: "memory");
     const float renew_margin = (kLazyLog2 + kRenewLog2) / scale_log2e;  // zero scale: +inf, never
     int to_renewal = it.renew_blocks ? it.renew_blocks + 1 : 0;  // 0: counts down and never gets there
-    for (int b = 0; b < nblocks; ++b) {
+    int at = 0, at2 = 2;  // stages of blocks b and b + 2
+    // one block: `compute` works on its stage between the copy of the block after next and the
+    // barrier that publishes the next one
+    auto step = [&](int b, auto compute) {
         const bool more = b + 2 < nblocks;
-        if (more) dma_block(b + 2, id0, id1);  // its stage held block b-1: everyone is done with it
-        page_ids(b + 3, id0, id1);
-        const int kb0 = it.kv_begin + BK * b;
+        if (more) dma_block(smem[at2], id0, id1);  // it held block b-1: everyone is done with it
         if constexpr (RENEW) {
             // A renewal takes the block's own maximum as the reference also where it is lower, by
             // no more than 2^kRenewLog2 than any reference so far, so that nothing grows by more
@@ -276,12 +301,11 @@ __global__ __launch_bounds__(256, 3) void attn_wide_kernel(
                 m_cmp = m_top - renew_margin;
             }
         }
-        if (kb0 < wave_end) {
-            if (kb0 + BK <= unmasked_end)
-                compute_block(smem[b % STAGES], kb0, std::false_type{});
-            else
-                compute_block(smem[b % STAGES], kb0, std::true_type{});
-        }
+        compute(smem[at], it.kv_begin + BK * b);
+        __builtin_amdgcn_sched_barrier(0);
+        page_ids(b + 3, id0, id1);
+        at = at == STAGES - 1 ? 0 : at + 1;
+        at2 = at2 == STAGES - 1 ? 0 : at2 + 1;
         // block b+1 (issued one iteration ago) must have landed before the barrier publishes it;
         // this iteration's own copies may stay in flight.  This wavefront's LDS reads of block b
         // must have returned too: after the barrier the others refill that stage.  The scheduling
@@ -295,7 +319,17 @@ __global__ __launch_bounds__(256, 3) void attn_wide_kernel(
             __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, 0));
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
-    }
+    };
+    // Blocks that nothing is masked in for this wavefront's rows, then those that touch the causal
+    // boundary or the end of the sequence: loops of their own with the same barriers
+    const int unmasked = wave_end > 0 ? (unmasked_end - it.kv_begin) / BK : 0;
+    int b = 0;
+    for (; b < unmasked; ++b)
+        step(b, [&](const unsigned char *sb, int kb0) { compute_block(sb, kb0, std::false_type{}); });
+    for (; b < nblocks; ++b)
+        step(b, [&](const unsigned char *sb, int kb0) {
+            if (kb0 < wave_end) compute_block(sb, kb0, std::true_type{});
+        });
 
     // ---- finish: every lane owns one row; the two half-waves hold partial sums ----
     const float l_tot = l_run + __shfl_xor(l_run, 32);
