@@ -16,16 +16,19 @@
 // lanes read 256 consecutive bytes (no bank conflicts, no padding, no transposes).  Scores are
 // produced transposed, S^T = K Q^T (v_mfma_f32_32x32x16), so each lane owns one query row (softmax
 // without cross-lane traffic except one exchange for the maximum) and the probabilities are
-// already the B operand of O^T += V^T P^T.  About 166 VGPRs (142 for head size 64) and 48 KiB of
+// already the B operand of O^T += V^T P^T.  About 166 VGPRs (134 for head size 64) and 48 KiB of
 // LDS let three workgroups share a CU, whose wavefronts overlap each other's matrix-core,
 // vector-ALU and LDS phases.  One raw s_barrier per block, preceded by a wait that leaves only the
 // newest loads in flight.  Blocks that touch the causal boundary or the end of the sequence run in a
-// second loop, masked, so the steady-state loop has no branches and the registers for one kind of
-// block at a time: room to request all V operands of a block while its scores are computed, into
-// the registers that its K operands leave (two at a time before, each pair waited for).  Block by
-// block 2427 -> 2281 cycles with three workgroups on a CU, 2105 -> 1745 with one or two; the clock
-// gives back half of that (1.85 -> 1.78 GHz: the chip's power limit): 64 mixed requests, 64/8
-// heads, whole step 262.7 -> 255.6 us, 48 of head size 64 102.7 -> 99.7.  The running maximum is
+// second loop, which masks the scores, so the steady-state loop has no branches and the registers
+// for one kind of block at a time: room to request all V operands of a block while its scores are
+// computed, into the registers that its K operands leave (two at a time before, each pair waited
+// for).  Block by block 2427 -> 2281 cycles with three workgroups on a CU, 2105 -> 1745 with one or
+// two; the clock gives back half of that (1.85 -> 1.78 GHz: the chip's power limit): 64 mixed
+// requests, 64/8 heads, whole step 262.7 -> 255.6 us, 48 of head size 64 102.7 -> 99.7.  With the
+// values past the end zeroed once in LDS instead of by every reader, one division an item instead
+// of one a row, and every operand waited for by itself 253.7 and 97.1 us; 17 short prompts of head
+// size 64 22.9 -> 21.8, one prompt among few 21.3 -> 21.0.  The running maximum is
 // only moved when a new score exceeds it by more than 2^8 (softmax is shift-invariant), which
 // makes rescaling the accumulator rare.
 #include <type_traits>
@@ -41,7 +44,7 @@ __global__ __launch_bounds__(256, 3) void attn_wide_kernel(
     const WorkItem *__restrict__ items, const uint16_t *__restrict__ q,
     const uint16_t *__restrict__ k_pages, const uint16_t *__restrict__ v_pages,
     const int32_t *__restrict__ page_table, int32_t max_pages, int32_t num_q_heads,
-    int32_t num_kv_heads, int32_t group, float scale_log2e, uint32_t q_sign,
+    int32_t num_kv_heads, int32_t group, float scale_log2e, uint32_t q_keep, uint32_t q_sign,
     uint16_t *__restrict__ out, float *__restrict__ ws_o, float *__restrict__ ws_ml)
 {
     // Keys per block: 32 for head size 128; 64 for head size 64, where 32 keys are only 8
@@ -67,39 +70,36 @@ __global__ __launch_bounds__(256, 3) void attn_wide_kernel(
     const int q32 = lane & 31;
     const int h = lane >> 5;
 
-    const int row = it.row_begin + 32 * w + q32;
-    const bool valid = 32 * w + q32 < it.row_count;
-    const int tok = valid ? row / group : 0;
-    const int hq = it.kv_head * group + (valid ? row % group : 0);
-    // one past the last key of the item this row may see (a part of a KV range need not end at the
-    // end of a block)
-    const int vis_end = valid ? min(it.ctx + tok + 1, it.kv_end) : it.kv_end;
+    const RowMap rows(it.row_begin, group);
     // wavefront-uniform limits: below unmasked_end nothing is masked for this wavefront's rows
     // (and no slot is past the end); at or beyond wave_end nothing is visible to them
     const int wave_rows = it.row_count - 32 * w;  // may be <= 0
-    int unmasked_end = it.ctx + (it.row_begin + 32 * w) / group + 1;
+    int unmasked_end = it.ctx + rows.token(32 * w) + 1;
     if (unmasked_end > it.kv_end) unmasked_end = it.kv_end;
     unmasked_end = __builtin_amdgcn_readfirstlane(unmasked_end);
     int wave_end = 0;
     if (wave_rows > 0) {
-        const int last = it.row_begin + 32 * w + (wave_rows < 32 ? wave_rows : 32) - 1;
-        wave_end = it.ctx + last / group + 1;
+        wave_end = it.ctx + rows.token(32 * w + (wave_rows < 32 ? wave_rows : 32) - 1) + 1;
         if (wave_end > it.kv_end) wave_end = it.kv_end;
         wave_end = __builtin_amdgcn_readfirstlane(wave_end);
     }
 
     vec8 qf[KS];
     {
-        const uint16_t *qrow = q + ((int64_t)(it.q_row0 + tok) * num_q_heads + hq) * D;
+        const bool valid = 32 * w + q32 < it.row_count;
+        int tok, head;
+        rows.at(valid ? 32 * w + q32 : 0, tok, head);
+        const uint16_t *qrow =
+            q + ((int64_t)(it.q_row0 + tok) * num_q_heads + it.kv_head * group + head) * D;
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
-            // loaded without a condition (a lane without a row reads the request's first one):
+            // loaded without a condition (a lane without a row reads the item's first one):
             // eight branches less in front of the page ids; 19 first prompts, 64/8 heads 33.0 ->
             // 32.5 us, 8 longer ones, 40/40 heads 181.7 -> 179.6
             const u32x4 got = load16(qrow + 16 * ks + 8 * h);
             u32x4 raw = {0u, 0u, 0u, 0u};
             if (valid) raw = got;
-            raw ^= q_sign;  // a negative scale is applied as |scale| on negated queries
+            raw = (raw & q_keep) ^ q_sign;
             qf[ks] = as_vec8<T>(raw);
         }
     }
@@ -108,8 +108,9 @@ __global__ __launch_bounds__(256, 3) void attn_wide_kernel(
     // with key pi(i) (bits 2 and 3 of i swapped) so that the accumulator registers of S^T, taken in
     // order, are exactly the 8 consecutive keys the P^T operand of the second product needs.
     const int key = (q32 & 0x13) | ((q32 & 4) << 1) | ((q32 & 8) >> 1);
-    const int k_lds = (key >> 4) * TILE_BYTES + (h * 16 + (key & 15)) * 16;  // + ks * 512
-    const int v_lds = HALF_BYTES + (h * D + q32) * 16;  // + page * TILE_BYTES + blk * 512
+    int k_lds = (key >> 4) * TILE_BYTES + (h * 16 + (key & 15)) * 16;  // + ks * 512
+    int v_lds = HALF_BYTES + (h * D + q32) * 16;  // + page * TILE_BYTES + blk * 512
+    asm volatile("" : "+v"(k_lds), "+v"(v_lds));  // one register each, not their parts
 
     const int32_t *pt = page_table + (int64_t)it.req * max_pages;
     const int last_pg = (it.kv_end - 1) >> 4;
@@ -150,11 +151,16 @@ __global__ __launch_bounds__(256, 3) void attn_wide_kernel(
         for (int v = 0; v < 16; ++v) o[blk][v] = 0.f;
     float m_run = -INFINITY;  // reference maximum of the RAW scores (before scaling)
     float m_top = -INFINITY;  // the highest reference so far (RENEW)
-    float m_cmp = -INFINITY;  // what the test for a new reference compares with (RENEW): m_run, lower
-                              // for a renewal
     float l_run = 0.f;        // this lane's share of the running sum
     float mc = 0.f;           // m_run in the exp2 domain (0 while there is no reference yet)
 
+    // RENEW: a renewal takes the block's own maximum as the reference also where it is lower, by no
+    // more than 2^kRenewLog2 than any reference so far, so that nothing grows by more than that.
+    const float renew_margin = (kLazyLog2 + kRenewLog2) / scale_log2e;
+    int to_renewal = it.renew_blocks ? it.renew_blocks + 1 : 0;  // a renewal where it counts to 0
+    // one past the last key of the item that the lane's row may see (a part of a KV range need not
+    // end at the end of a block), less 8 * h; set in front of the masked loop
+    int vis_lane = 0;
     auto compute_block = [&](const unsigned char *sb, int kb0, auto masked_tag) {
         constexpr bool MASKED = decltype(masked_tag)::value;
         u32x4 kf[NT * KS];  // K operands, requested as soon as the block is published
@@ -173,28 +179,22 @@ __global__ __launch_bounds__(256, 3) void attn_wide_kernel(
             for (int ks = 0; ks < KS; ++ks)
                 s[t] = T::mfma32(as_vec8<T>(kf[t * KS + ks]), qf[ks], s[t]);
         // all V operands are requested while the matrix cores work on the scores, so that they have
-        // arrived when the first exponentials are done (the masked loop has no registers for that)
+        // arrived when the first exponentials are done
         __builtin_amdgcn_sched_barrier(0);
-        auto read_v = [&](int i) {
-            return *reinterpret_cast<const u32x4 *>(sb + v_lds + (i / NB) * TILE_BYTES +
-                                                    (i % NB) * 512);
-        };
         u32x4 vf[PAGES * NB];
-        if constexpr (!MASKED) {
 #pragma unroll
-            for (int i = 0; i < PAGES * NB; ++i) vf[i] = read_v(i);
-        }
+        for (int i = 0; i < PAGES * NB; ++i)
+            vf[i] = *reinterpret_cast<const u32x4 *>(sb + v_lds + (i / NB) * TILE_BYTES +
+                                                     (i % NB) * 512);
         __builtin_amdgcn_sched_barrier(0);
         // register v = 8*page + j of tile t  <->  key kb0 + 32*t + 16*page + 8*h + j
-        bool vis[NT][16];
         if constexpr (MASKED) {
+            const int seen = vis_lane - kb0;
 #pragma unroll
             for (int t = 0; t < NT; ++t)
 #pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    vis[t][v] = kb0 + 32 * t + 16 * (v >> 3) + 8 * h + (v & 7) < vis_end;
-                    if (!vis[t][v]) s[t][v] = -INFINITY;
-                }
+                for (int v = 0; v < 16; ++v)
+                    if (32 * t + 16 * (v >> 3) + (v & 7) >= seen) s[t][v] = -INFINITY;
         }
         float mx = s[0][0];
 #pragma unroll
@@ -206,15 +206,15 @@ __global__ __launch_bounds__(256, 3) void attn_wide_kernel(
         // probabilities just range up to 2^kLazyLog2 instead of 1).  Each lane tests the keys it
         // holds; only when some lane of the wavefront sees such a score (or has no reference yet)
         // do the two lanes of a row exchange their maxima and the accumulators get rescaled.
-        const float base = RENEW ? m_cmp : m_run;
+        float base = m_run;  // what the test for a new reference compares with: lower for a renewal
+        if constexpr (RENEW) base = to_renewal == 0 ? m_top - renew_margin : m_run;
         const bool grow = m_run == -INFINITY || (mx - base) * scale_log2e > kLazyLog2;
         if (__any(grow)) {
-            mx = fmaxf(mx, __shfl_xor(mx, 32));
+            mx = max_halves(mx);
             const float m_new =
                 (m_run == -INFINITY || (mx - base) * scale_log2e > kLazyLog2) ? mx : m_run;
             if constexpr (RENEW) {
                 m_top = fmaxf(m_top, m_new);
-                m_cmp = m_new;
             }
             const float m_safe = m_new == -INFINITY ? 0.f : m_new;
             const float alpha =
@@ -236,31 +236,15 @@ __global__ __launch_bounds__(256, 3) void attn_wide_kernel(
             u32x4 praw;
 #pragma unroll
             for (int jj = 0; jj < 4; ++jj) {
-                float p0 = fast_exp2(__builtin_fmaf(s[t][v0 + 2 * jj], scale_log2e, -mc));
-                float p1 = fast_exp2(__builtin_fmaf(s[t][v0 + 2 * jj + 1], scale_log2e, -mc));
-                if constexpr (MASKED) {
-                    p0 = vis[t][v0 + 2 * jj] ? p0 : 0.f;
-                    p1 = vis[t][v0 + 2 * jj + 1] ? p1 : 0.f;
-                }
+                const float p0 = fast_exp2(__builtin_fmaf(s[t][v0 + 2 * jj], scale_log2e, -mc));
+                const float p1 = fast_exp2(__builtin_fmaf(s[t][v0 + 2 * jj + 1], scale_log2e, -mc));
                 praw[jj] = T::pack2(p0, p1);
                 psum = T::add_pair(praw[jj], psum);  // the sum of what the matrix core will see
             }
             const vec8 pf = as_vec8<T>(praw);
 #pragma unroll
-            for (int blk = 0; blk < NB; ++blk) {
-                u32x4 v = MASKED ? read_v(pg * NB + blk) : vf[pg * NB + blk];
-                if constexpr (MASKED) {  // slots past the end may hold anything: zero those values
-#pragma unroll
-                    for (int jj = 0; jj < 4; ++jj) {
-                        const int kk = kb0 + 16 * pg + 8 * h + 2 * jj;
-                        uint32_t word = v[jj];
-                        if (kk >= it.kv_end) word &= 0xFFFF0000u;
-                        if (kk + 1 >= it.kv_end) word &= 0x0000FFFFu;
-                        v[jj] = word;
-                    }
-                }
-                o[blk] = T::mfma32(as_vec8<T>(v), pf, o[blk]);
-            }
+            for (int blk = 0; blk < NB; ++blk)
+                o[blk] = T::mfma32(as_vec8<T>(vf[pg * NB + blk]), pf, o[blk]);
         }
         l_run += psum;
     };
@@ -282,9 +266,8 @@ __global__ __launch_bounds__(256, 3) void attn_wide_kernel(
     else
         __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, 0));
     __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-    const float renew_margin = (kLazyLog2 + kRenewLog2) / scale_log2e;  // zero scale: +inf, never
-    int to_renewal = it.renew_blocks ? it.renew_blocks + 1 : 0;  // 0: counts down and never gets there
+    asm volatile("" : "+s"(id0), "+s"(id1)::"memory");
+    const int tail = it.kv_end - it.kv_begin - BK * (nblocks - 1);  // keys of the last block
     int at = 0, at2 = 2;  // stages of blocks b and b + 2
     // one block: `compute` works on its stage between the copy of the block after next and the
     // barrier that publishes the next one
@@ -292,14 +275,7 @@ __global__ __launch_bounds__(256, 3) void attn_wide_kernel(
         const bool more = b + 2 < nblocks;
         if (more) dma_block(smem[at2], id0, id1);  // it held block b-1: everyone is done with it
         if constexpr (RENEW) {
-            // A renewal takes the block's own maximum as the reference also where it is lower, by
-            // no more than 2^kRenewLog2 than any reference so far, so that nothing grows by more
-            // than that.
-            m_cmp = m_run;
-            if (--to_renewal == 0) {
-                to_renewal = it.renew_blocks;
-                m_cmp = m_top - renew_margin;
-            }
+            to_renewal = to_renewal == 0 ? it.renew_blocks - 1 : to_renewal - 1;
         }
         compute(smem[at], it.kv_begin + BK * b);
         __builtin_amdgcn_sched_barrier(0);
@@ -308,17 +284,19 @@ __global__ __launch_bounds__(256, 3) void attn_wide_kernel(
         at2 = at2 == STAGES - 1 ? 0 : at2 + 1;
         // block b+1 (issued one iteration ago) must have landed before the barrier publishes it;
         // this iteration's own copies may stay in flight.  This wavefront's LDS reads of block b
-        // must have returned too: after the barrier the others refill that stage.  The scheduling
-        // barrier keeps the block's last matrix-core instructions (which consume those reads) in
-        // front of the wait, so the wait itself costs nothing.
+        // must have returned too: after the barrier the others refill that stage.  They have: the
+        // scheduling barrier keeps the block's last matrix-core instructions, which wait for them,
+        // in front of this point.
         __builtin_amdgcn_sched_barrier(0);
         asm volatile("" ::: "memory");
         if (more)
-            __builtin_amdgcn_s_waitcnt(waitcnt_imm(2 * PASSES, 0));
+            __builtin_amdgcn_s_waitcnt(waitcnt_imm(2 * PASSES, 15));
         else
-            __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, 0));
+            __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, 15));
         __builtin_amdgcn_s_barrier();
-        asm volatile("" ::: "memory");
+        // the page ids have arrived, too: said here, or the first operand of the next block would be
+        // waited for together with them, which means with all other operands
+        asm volatile("" : "+s"(id0), "+s"(id1)::"memory");
     };
     // Blocks that nothing is masked in for this wavefront's rows, then those that touch the causal
     // boundary or the end of the sequence: loops of their own with the same barriers
@@ -326,13 +304,26 @@ __global__ __launch_bounds__(256, 3) void attn_wide_kernel(
     int b = 0;
     for (; b < unmasked; ++b)
         step(b, [&](const unsigned char *sb, int kb0) { compute_block(sb, kb0, std::false_type{}); });
-    for (; b < nblocks; ++b)
+    // the lane's row is worked out anew: the loop above has no register to keep it in
+    int lane_again = (int)(lane_bytes >> 4);
+    asm volatile("" : "+v"(lane_again));
+    const int own = 32 * w + (lane_again & 31), half = lane_again >> 5;
+    vis_lane =
+        (own < it.row_count ? min(it.ctx + rows.token(own) + 1, it.kv_end) : it.kv_end) - 8 * half;
+    for (; b < nblocks; ++b) {
+        if (b + 1 == nblocks && tail < BK) {
+            zero_past_end<D>(smem[at] + HALF_BYTES, tail, 64 * w + lane_again);
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
+        }
         step(b, [&](const unsigned char *sb, int kb0) {
             if (kb0 < wave_end) compute_block(sb, kb0, std::true_type{});
         });
+    }
 
     // ---- finish: every lane owns one row; the two half-waves hold partial sums ----
-    const float l_tot = l_run + __shfl_xor(l_run, 32);
+    const float l_tot = add_halves(l_run);
     if (it.split_count == 1) {
         // The accumulators hold 8 bytes of 32 different rows per register pair: stored from there,
         // every 16 bytes would be a request of their own to L2 (4 million of the 10 million requests
@@ -350,36 +341,41 @@ __global__ __launch_bounds__(256, 3) void attn_wide_kernel(
         for (int blk = 0; blk < NB; ++blk)
 #pragma unroll
             for (int a = 0; a < 4; ++a) {
-                const int d = 32 * blk + 8 * a + 4 * h;
-                *reinterpret_cast<u32x2 *>(part + q32 * ROW_BYTES + 2 * d) =
+                const int d = 32 * blk + 8 * a + 4 * half;
+                *reinterpret_cast<u32x2 *>(part + (own & 31) * ROW_BYTES + 2 * d) =
                     u32x2{T::pack2(o[blk][4 * a] * inv, o[blk][4 * a + 1] * inv),
                           T::pack2(o[blk][4 * a + 2] * inv, o[blk][4 * a + 3] * inv)};
             }
-        if (h == 0) row_off[q32] = ((int64_t)(it.q_row0 + tok) * num_q_heads + hq) * D;
+        int own_again = own < it.row_count ? own : 0, own_tok, own_head;
+        asm volatile("" : "+v"(own_again));
+        rows.at(own_again, own_tok, own_head);
+        if (half == 0)
+            row_off[own & 31] = ((int64_t)(it.q_row0 + own_tok) * num_q_heads +
+                                 it.kv_head * group + own_head) * D;
         // LDS operations of one wavefront complete in order; the statement keeps the compiler from
         // moving the reads in front of the other lanes' writes
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         constexpr int LPR = D / 8;  // lanes per row, 16 bytes each
-        const int c = lane % LPR;
+        const int c = lane_again % LPR;
 #pragma unroll
         for (int r0 = 0; r0 < 32; r0 += 64 / LPR) {
-            const int r = r0 + lane / LPR;
+            const int r = r0 + lane_again / LPR;
             if (r < wave_rows)
                 *reinterpret_cast<u32x4 *>(out + row_off[r] + 8 * c) =
                     *reinterpret_cast<const u32x4 *>(part + r * ROW_BYTES + 16 * c);
         }
-    } else if (valid) {
-        const int64_t slot = (int64_t)it.partial_base + 32 * w + q32;
+    } else if (own < it.row_count) {
+        const int64_t slot = (int64_t)it.partial_base + own;
         float *po = ws_o + slot * D;
 #pragma unroll
         for (int blk = 0; blk < NB; ++blk)
 #pragma unroll
             for (int a = 0; a < 4; ++a) {
-                const int d = 32 * blk + 8 * a + 4 * h;
+                const int d = 32 * blk + 8 * a + 4 * half;
                 *reinterpret_cast<f32x4 *>(po + d) = f32x4{o[blk][4 * a], o[blk][4 * a + 1],
                                                            o[blk][4 * a + 2], o[blk][4 * a + 3]};
             }
-        if (h == 0) {
+        if (half == 0) {
             // the merge works in the log2 domain of the scaled scores
             ws_ml[2 * slot] = m_run == -INFINITY ? -INFINITY : m_run * scale_log2e;
             ws_ml[2 * slot + 1] = l_tot;
@@ -393,14 +389,18 @@ static hipError_t launch_wide_t(const pv_plan *plan, const DeviceLists &dl, cons
                                 void *out, float *ws_o, float *ws_ml, hipStream_t stream)
 {
     const int n = (int)plan->wide.size();
-    const float c = (scale < 0.f ? -scale : scale) * kLog2e;
+    // A negative scale is applied as |scale| on negated queries, a zero scale as 1 on zeros: so
+    // that a masked score, minus infinity, is a probability of zero whatever the scale.
+    float c = (scale < 0.f ? -scale : scale) * kLog2e;
     const uint32_t q_sign = scale < 0.f ? 0x80008000u : 0u;
+    const uint32_t q_keep = c == 0.f ? 0u : 0xFFFFFFFFu;
+    if (c == 0.f) c = 1.f;
     auto kernel = plan->wide_renews ? attn_wide_kernel<T, D, true> : attn_wide_kernel<T, D, false>;
     hipLaunchKernelGGL(kernel, dim3(n), dim3(256), 0, stream, dl.wide, (const uint16_t *)q,
                        (const uint16_t *)k_pages, (const uint16_t *)v_pages,
                        page_table, plan->max_pages_per_req, plan->num_q_heads,
-                       plan->pool.num_kv_heads, plan->group, c, q_sign, (uint16_t *)out, ws_o,
-                       ws_ml);
+                       plan->pool.num_kv_heads, plan->group, c, q_keep, q_sign, (uint16_t *)out,
+                       ws_o, ws_ml);
     return hipGetLastError();
 }
 

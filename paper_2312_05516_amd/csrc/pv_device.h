@@ -180,6 +180,51 @@ __device__ __forceinline__ float max3_raw(float a, float b, float c)
     return r;
 }
 
+// The larger (the sum) of a lane's value and that of the lane 32 away: one lane exchange in the
+// vector ALU, without the LDS unit and the registers that a permute's lane addresses take.
+__device__ __forceinline__ float max_halves(float x)
+{
+    const uint32_t b = __builtin_bit_cast(uint32_t, x);
+    const auto r = __builtin_amdgcn_permlane32_swap(b, b, false, false);
+    return fmaxf(__builtin_bit_cast(float, (uint32_t)r[0]), __builtin_bit_cast(float, (uint32_t)r[1]));
+}
+__device__ __forceinline__ float add_halves(float x)
+{
+    const uint32_t b = __builtin_bit_cast(uint32_t, x);
+    const auto r = __builtin_amdgcn_permlane32_swap(b, b, false, false);
+    return __builtin_bit_cast(float, (uint32_t)r[0]) + __builtin_bit_cast(float, (uint32_t)r[1]);
+}
+
+// Token (of the request) and query head (of the group) of the rows of an item: row = token * group +
+// head.  One whole division for the item's first row; the others lie a few hundred further at most,
+// where a float quotient is off by one at the most.
+struct RowMap {
+    uint32_t tok0, head0, group;
+    float inv;
+    __device__ __forceinline__ RowMap(int row_begin, int group_) : group((uint32_t)group_)
+    {
+        tok0 = (uint32_t)row_begin / group;
+        head0 = (uint32_t)row_begin - tok0 * group;
+        inv = 1.f / (float)group;
+    }
+    // of the row `i` behind the first one
+    __device__ __forceinline__ void at(int i, int &tok, int &head) const
+    {
+        const uint32_t r = head0 + (uint32_t)i;
+        uint32_t n = (uint32_t)((float)r * inv);
+        if (n * group > r) --n;
+        if ((n + 1) * group <= r) ++n;
+        tok = (int)(tok0 + n);
+        head = (int)(r - n * group);
+    }
+    __device__ __forceinline__ int token(int i) const
+    {
+        int tok, head;
+        at(i, tok, head);
+        return tok;
+    }
+};
+
 // lane index of the calling thread within its wavefront, wave index made scalar
 __device__ __forceinline__ int lane_id() { return (int)(threadIdx.x & 63u); }
 __device__ __forceinline__ int wave_id()
@@ -261,6 +306,30 @@ __device__ __forceinline__ void scatter_v_group(const uint16_t *__restrict__ vsr
             for (int j = 0; j < 8; ++j)
                 if (j < count) vdst[s0 + j] = vals[i][j];
         }
+    }
+}
+
+// Zeroes the V values of the keys past the first `keys` of a block in LDS (V pages at `v`, whose
+// slots past the end of the sequence may hold anything, NaN included): 2 * D runs of 8 keys a page,
+// dealt to the 256 threads of the workgroup.  For the last block of an item only, in front of a
+// barrier, so that nobody has to mask values that they read.
+template <int D>
+__device__ __forceinline__ void zero_past_end(unsigned char *v, int keys, int thread)
+{
+    constexpr int RUNS = D == 128 ? 4 * D : 8 * D;  // 32 keys a block, 64 for head size 64
+#pragma unroll
+    for (int i = 0; i < RUNS; i += 256) {
+        const int run = i + thread;
+        const int first = run / D * 8;  // first key of the run
+        if (first + 8 <= keys) continue;
+        u32x4 *at = reinterpret_cast<u32x4 *>(v + run * 16);
+        u32x4 word = *at;
+#pragma unroll
+        for (int jj = 0; jj < 4; ++jj) {
+            if (first + 2 * jj >= keys) word[jj] &= 0xFFFF0000u;
+            if (first + 2 * jj + 1 >= keys) word[jj] &= 0x0000FFFFu;
+        }
+        *at = word;
     }
 }
 

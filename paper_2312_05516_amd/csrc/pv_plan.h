@@ -121,7 +121,7 @@ constexpr int kTileRows = 256;   // rows per item of the 256-row matrix-core ker
 constexpr int kCUs = 256;
 // Workgroups that run at once on the CUs: two of the narrow kernel on each (212-216 registers
 // a lane; head size 64 has room for three, but 512 parts are ahead of more: 4 generation steps,
-// 32/8 heads, 13.4 us with 512 parts, 14.2 with 656), three of the 128-row kernel (166-168
+// 32/8 heads, 13.4 us with 512 parts, 14.2 with 656), three of the 128-row kernel (165-167
 // registers, 48 KiB of LDS).
 constexpr int kNarrowSlots = 512;
 constexpr int kWideSlots = 768;
