@@ -37,9 +37,10 @@
 
 namespace pv {
 
+// STREAMS: items that are `alone` copy with the streaming hint (see kStreamKvBytes).
 // RENEW: some item has renew_blocks.  Lists without any keep an instantiation of their own (with the
 // test for it in the loop they take 1 % longer: 64 mixed requests, 64/8 heads, 270.5 -> 273.1 us)
-template <typename T, int D, bool RENEW>
+template <typename T, int D, bool RENEW, bool STREAMS>
 __global__ __launch_bounds__(256, 3) void attn_wide_kernel(
     const WorkItem *__restrict__ items, const uint16_t *__restrict__ q,
     const uint16_t *__restrict__ k_pages, const uint16_t *__restrict__ v_pages,
@@ -133,13 +134,14 @@ __global__ __launch_bounds__(256, 3) void attn_wide_kernel(
         (uint64_t)it.kv_head * TILE_BYTES + (uint32_t)(w * 1024 % TILE_BYTES);
     const unsigned char *k_src = reinterpret_cast<const unsigned char *>(k_pages) + piece_off;
     const unsigned char *v_src = reinterpret_cast<const unsigned char *>(v_pages) + piece_off;
-    auto dma_block = [&](unsigned char *stage, int id0, int id1) {
+    auto dma_block = [&](unsigned char *stage, int id0, int id1, auto stream_tag) {
+        constexpr bool STREAM = decltype(stream_tag)::value;
 #pragma unroll
         for (int p = 0; p < PASSES; ++p) {
             const int off = p * 4096 + w * 1024;  // wavefront-uniform
             const uint64_t page_off = (uint64_t)(uint32_t)(p ? id1 : id0) * page_bytes;
-            lds_dma16(k_src + page_off, lane_bytes, stage + off);
-            lds_dma16(v_src + page_off, lane_bytes, stage + HALF_BYTES + off);
+            lds_dma16<STREAM>(k_src + page_off, lane_bytes, stage + off);
+            lds_dma16<STREAM>(v_src + page_off, lane_bytes, stage + HALF_BYTES + off);
         }
     };
     static_assert(4096 % TILE_BYTES == 0, "a pass covers whole pages");
@@ -157,7 +159,8 @@ __global__ __launch_bounds__(256, 3) void attn_wide_kernel(
     // RENEW: a renewal takes the block's own maximum as the reference also where it is lower, by no
     // more than 2^kRenewLog2 than any reference so far, so that nothing grows by more than that.
     const float renew_margin = (kLazyLog2 + kRenewLog2) / scale_log2e;
-    int to_renewal = it.renew_blocks ? it.renew_blocks + 1 : 0;  // a renewal where it counts to 0
+    const int renew_blocks = (int)it.renew_blocks;
+    int to_renewal = renew_blocks ? renew_blocks + 1 : 0;  // a renewal where it counts to 0
     // one past the last key of the item that the lane's row may see (a part of a KV range need not
     // end at the end of a block), less 8 * h; set in front of the masked loop
     int vis_lane = 0;
@@ -249,80 +252,93 @@ __global__ __launch_bounds__(256, 3) void attn_wide_kernel(
         l_run += psum;
     };
 
-    // prologue: blocks 0 and 1 on their way, block 0 landed and visible to everyone; the page ids
-    // of the block after next are always fetched one iteration early
-    int id0, id1;
-    page_ids(0, id0, id1);
-    dma_block(smem[0], id0, id1);
-    if (nblocks > 1) {
-        page_ids(1, id0, id1);
-        dma_block(smem[1], id0, id1);
-    }
-    page_ids(2, id0, id1);
-    asm volatile("" ::: "memory");
-    // the queries (loaded first) and block 0 must be there; block 1 may still be on its way
-    if (nblocks > 1)
-        __builtin_amdgcn_s_waitcnt(waitcnt_imm(2 * PASSES, 0));
-    else
-        __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, 0));
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" : "+s"(id0), "+s"(id1)::"memory");
-    const int tail = it.kv_end - it.kv_begin - BK * (nblocks - 1);  // keys of the last block
-    int at = 0, at2 = 2;  // stages of blocks b and b + 2
-    // one block: `compute` works on its stage between the copy of the block after next and the
-    // barrier that publishes the next one
-    auto step = [&](int b, auto compute) {
-        const bool more = b + 2 < nblocks;
-        if (more) dma_block(smem[at2], id0, id1);  // it held block b-1: everyone is done with it
-        if constexpr (RENEW) {
-            to_renewal = to_renewal == 0 ? it.renew_blocks - 1 : to_renewal - 1;
+    // The item from its first copy to its last block; `stream`: with the streaming hint on its
+    // copies.  A flow of its own for either: with both kinds of copies in one loop and a branch
+    // between them batches that stream nothing are 2-4 % slower.
+    auto run = [&](auto stream) {
+        // prologue: blocks 0 and 1 on their way, block 0 landed and visible to everyone; the page
+        // ids of the block after next are always fetched one iteration early
+        int id0, id1;
+        page_ids(0, id0, id1);
+        dma_block(smem[0], id0, id1, stream);
+        if (nblocks > 1) {
+            page_ids(1, id0, id1);
+            dma_block(smem[1], id0, id1, stream);
         }
-        compute(smem[at], it.kv_begin + BK * b);
-        __builtin_amdgcn_sched_barrier(0);
-        page_ids(b + 3, id0, id1);
-        at = at == STAGES - 1 ? 0 : at + 1;
-        at2 = at2 == STAGES - 1 ? 0 : at2 + 1;
-        // block b+1 (issued one iteration ago) must have landed before the barrier publishes it;
-        // this iteration's own copies may stay in flight.  This wavefront's LDS reads of block b
-        // must have returned too: after the barrier the others refill that stage.  They have: the
-        // scheduling barrier keeps the block's last matrix-core instructions, which wait for them,
-        // in front of this point.
-        __builtin_amdgcn_sched_barrier(0);
+        page_ids(2, id0, id1);
         asm volatile("" ::: "memory");
-        if (more)
-            __builtin_amdgcn_s_waitcnt(waitcnt_imm(2 * PASSES, 15));
+        // the queries (loaded first) and block 0 must be there; block 1 may still be on its way
+        if (nblocks > 1)
+            __builtin_amdgcn_s_waitcnt(waitcnt_imm(2 * PASSES, 0));
         else
-            __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, 15));
+            __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, 0));
         __builtin_amdgcn_s_barrier();
-        // the page ids have arrived, too: said here, or the first operand of the next block would be
-        // waited for together with them, which means with all other operands
         asm volatile("" : "+s"(id0), "+s"(id1)::"memory");
+        const int tail = it.kv_end - it.kv_begin - BK * (nblocks - 1);  // keys of the last block
+        int at = 0, at2 = 2;  // stages of blocks b and b + 2
+        // one block: `compute` works on its stage between the copy of the block after next and the
+        // barrier that publishes the next one
+        auto step = [&](int b, auto compute) {
+            const bool more = b + 2 < nblocks;
+            if (more) dma_block(smem[at2], id0, id1, stream);  // everyone is done with block b-1
+            if constexpr (RENEW) to_renewal = (to_renewal == 0 ? renew_blocks : to_renewal) - 1;
+            compute(smem[at], it.kv_begin + BK * b);
+            __builtin_amdgcn_sched_barrier(0);
+            page_ids(b + 3, id0, id1);
+            at = at == STAGES - 1 ? 0 : at + 1;
+            at2 = at2 == STAGES - 1 ? 0 : at2 + 1;
+            // block b+1 (issued one iteration ago) must have landed before the barrier publishes
+            // it; this iteration's own copies may stay in flight.  This wavefront's LDS reads of
+            // block b must have returned too: after the barrier the others refill that stage.  They
+            // have: the scheduling barrier keeps the block's last matrix-core instructions, which
+            // wait for them, in front of this point.
+            __builtin_amdgcn_sched_barrier(0);
+            asm volatile("" ::: "memory");
+            if (more)
+                __builtin_amdgcn_s_waitcnt(waitcnt_imm(2 * PASSES, 15));
+            else
+                __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, 15));
+            __builtin_amdgcn_s_barrier();
+            // the page ids have arrived, too: said here, or the first operand of the next block would
+            // be waited for together with them, which means with all other operands
+            asm volatile("" : "+s"(id0), "+s"(id1)::"memory");
+        };
+        // Blocks that nothing is masked in for this wavefront's rows, then those that touch the
+        // causal boundary or the end of the sequence: loops of their own with the same barriers
+        const int unmasked = wave_end > 0 ? (unmasked_end - it.kv_begin) / BK : 0;
+        int b = 0;
+        for (; b < unmasked; ++b)
+            step(b, [&](const unsigned char *sb, int kb0) {
+                compute_block(sb, kb0, std::false_type{});
+            });
+        // the lane's row is worked out anew: the loop above has no register to keep it in
+        int lane_again = (int)(lane_bytes >> 4);
+        asm volatile("" : "+v"(lane_again));
+        const int own = 32 * w + (lane_again & 31), half = lane_again >> 5;
+        vis_lane = it.kv_end - 8 * half;
+        if (own < it.row_count)
+            vis_lane = min(it.ctx + rows.token(own) + 1, it.kv_end) - 8 * half;
+        for (; b < nblocks; ++b) {
+            if (b + 1 == nblocks && tail < BK) {
+                zero_past_end<D>(smem[at] + HALF_BYTES, tail, 64 * w + lane_again);
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+                __builtin_amdgcn_s_barrier();
+                asm volatile("" ::: "memory");
+            }
+            step(b, [&](const unsigned char *sb, int kb0) {
+                if (kb0 < wave_end) compute_block(sb, kb0, std::true_type{});
+            });
+        }
     };
-    // Blocks that nothing is masked in for this wavefront's rows, then those that touch the causal
-    // boundary or the end of the sequence: loops of their own with the same barriers
-    const int unmasked = wave_end > 0 ? (unmasked_end - it.kv_begin) / BK : 0;
-    int b = 0;
-    for (; b < unmasked; ++b)
-        step(b, [&](const unsigned char *sb, int kb0) { compute_block(sb, kb0, std::false_type{}); });
-    // the lane's row is worked out anew: the loop above has no register to keep it in
+    if (STREAMS && it.alone)
+        run(std::bool_constant<STREAMS>{});
+    else
+        run(std::false_type{});
+
+    // ---- finish: every lane owns one row; the two half-waves hold partial sums ----
     int lane_again = (int)(lane_bytes >> 4);
     asm volatile("" : "+v"(lane_again));
     const int own = 32 * w + (lane_again & 31), half = lane_again >> 5;
-    vis_lane =
-        (own < it.row_count ? min(it.ctx + rows.token(own) + 1, it.kv_end) : it.kv_end) - 8 * half;
-    for (; b < nblocks; ++b) {
-        if (b + 1 == nblocks && tail < BK) {
-            zero_past_end<D>(smem[at] + HALF_BYTES, tail, 64 * w + lane_again);
-            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-            __builtin_amdgcn_s_barrier();
-            asm volatile("" ::: "memory");
-        }
-        step(b, [&](const unsigned char *sb, int kb0) {
-            if (kb0 < wave_end) compute_block(sb, kb0, std::true_type{});
-        });
-    }
-
-    // ---- finish: every lane owns one row; the two half-waves hold partial sums ----
     const float l_tot = add_halves(l_run);
     if (it.split_count == 1) {
         // The accumulators hold 8 bytes of 32 different rows per register pair: stored from there,
@@ -395,7 +411,10 @@ static hipError_t launch_wide_t(const pv_plan *plan, const DeviceLists &dl, cons
     const uint32_t q_sign = scale < 0.f ? 0x80008000u : 0u;
     const uint32_t q_keep = c == 0.f ? 0u : 0xFFFFFFFFu;
     if (c == 0.f) c = 1.f;
-    auto kernel = plan->wide_renews ? attn_wide_kernel<T, D, true> : attn_wide_kernel<T, D, false>;
+    auto kernel = plan->wide_streams ? (plan->wide_renews ? attn_wide_kernel<T, D, true, true>
+                                                          : attn_wide_kernel<T, D, false, true>)
+                                     : (plan->wide_renews ? attn_wide_kernel<T, D, true, false>
+                                                          : attn_wide_kernel<T, D, false, false>);
     hipLaunchKernelGGL(kernel, dim3(n), dim3(256), 0, stream, dl.wide, (const uint16_t *)q,
                        (const uint16_t *)k_pages, (const uint16_t *)v_pages,
                        page_table, plan->max_pages_per_req, plan->num_q_heads,

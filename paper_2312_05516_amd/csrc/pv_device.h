@@ -241,15 +241,23 @@ typedef __attribute__((address_space(3))) void *lds_void_ptr;
 // M0.  M0 is a reserved register for this compiler: it never carries a value from one instruction
 // to a later one (every instruction that needs M0 gets its own s_mov in front), and it rejects M0
 // in a clobber list for that reason, so none is given.
+// STREAM: with the streaming hint, for data that nobody reads again.
+template <bool STREAM = false>
 __device__ __forceinline__ void lds_dma16(const void *uniform_base, uint32_t lane_offset,
                                           void *lds_base)
 {
     // address = wavefront-uniform 64-bit base (scalar registers) + per-lane 32-bit byte offset
     const uint32_t lds_addr = (uint32_t)(uintptr_t)(lds_void_ptr)lds_base;
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-                 :
-                 : "s"(lds_addr), "v"(lane_offset), "s"(uniform_base)
-                 : "memory");
+    if constexpr (STREAM)
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt"
+                     :
+                     : "s"(lds_addr), "v"(lane_offset), "s"(uniform_base)
+                     : "memory");
+    else
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+                     :
+                     : "s"(lds_addr), "v"(lane_offset), "s"(uniform_base)
+                     : "memory");
 }
 
 // V part of the KV append, shared by the plain and the rotary-fused append kernels so that the

@@ -224,7 +224,8 @@ static bool split_items(std::vector<WorkItem> &items, std::vector<CombineItem> &
             const int64_t len = w.kv_end - w.kv_begin;
             if (even.parts(len) <= cut.parts(len)) continue;
             fewer = true;
-            w.renew_blocks = std::max(even.part_len(len) / (head_dim == 128 ? 32 : 64), 1);
+            w.renew_blocks =
+                (uint32_t)std::max(even.part_len(len) / (head_dim == 128 ? 32 : 64), 1);
         }
     if (longest <= cut.longest_whole && !too_long(longest))
         return fewer;  // the common case of a long list: nothing is copied
@@ -525,10 +526,14 @@ pv_status build_plan(const pv_pool_desc *pool, int32_t num_q_heads, const int32_
         plan->narrow.reserve(n_narrow);
         plan->wide.reserve(n_wide);
     }
+    int64_t kv_bytes = 0, alone_bytes = 0;  // K/V read by all units, by those of one 128-row tile
     for (int32_t r = 0; r < num_reqs; ++r) {
         const int32_t n = q_lens[r], c = ctx_lens[r];
         if (n == 0) continue;
         const int32_t rows_total = n * G;
+        const int64_t unit_bytes = 4 * ((int64_t)c + n) * pool->num_kv_heads * pool->head_dim;
+        kv_bytes += unit_bytes;
+        if (rows_total <= kWideRows) alone_bytes += unit_bytes;
         for (int32_t hk = 0; hk < pool->num_kv_heads; ++hk) {
             WorkItem w;
             std::memset(&w, 0, sizeof w);
@@ -542,6 +547,7 @@ pv_status build_plan(const pv_pool_desc *pool, int32_t num_q_heads, const int32_
             w.ctx = c;
             const bool use_wide = rows_total >= tune.wide_min_rows || all_wide;
             const int32_t tile = use_wide ? kWideRows : kNarrowRows;
+            w.alone = rows_total <= kWideRows;
             // long units: their full 256-row tiles go to the 256-row kernel, the rest as usual
             int32_t rb = 0;
             if (use_tile256(pool, tune_batch, rows_total, (int64_t)c + n)) {
@@ -572,6 +578,7 @@ pv_status build_plan(const pv_pool_desc *pool, int32_t num_q_heads, const int32_
         split_items(plan->narrow, plan->combine, slots, tune, &narrow_rule, pool->head_dim);
     plan->wide_renews =
         split_items(plan->wide, plan->combine, slots, tune, &wide_rule, pool->head_dim);
+    plan->wide_streams = kv_bytes > kStreamKvBytes && alone_bytes * 4 >= kv_bytes;
     split_items(plan->tile256, plan->combine, slots, tune, nullptr, pool->head_dim,
                 kTileMaxKeys);
     if (slots > INT32_MAX / 2) {

@@ -31,7 +31,9 @@ struct WorkItem {
     // heads, bf16, whole instead of in three parts +0.77 % / 0.00 %, 51.1 / 51.0 us (the three
     // parts take 85); 6 of 50 tokens over 900, 64/8 heads, whole instead of in four +1.32 % / 0.00
     // %, 28.5 / 30.0 us.
-    int32_t renew_blocks;
+    uint32_t renew_blocks : 31;
+    // 128-row kernel: nobody else reads this item's K/V (its rows are all of the unit's)
+    uint32_t alone : 1;
 };
 static_assert(sizeof(WorkItem) == 48, "WorkItem is read by the kernels as 12 int32");
 
@@ -115,6 +117,18 @@ constexpr int64_t append_group_count(int64_t t_begin, int64_t count)
     return count > 0 ? (t_begin + count + 7) / 8 - t_begin / 8 : 0;
 }
 
+// 128-row kernel: the K/V of a unit whose rows fit one item is read once.  With the streaming hint
+// it does not push out of the L2 caches what the row tiles of larger units read together: 0.4 * n
+// prompts of 40-128 tokens and 0.6 * n generation steps over 500-1500, 40/40 heads, whole step
+// without and with it 70.2 / 62.5 us (11 requests, 230 MB of K/V), 86.8 / 75.4 (17), 140.4 / 117.8
+// (27), 219 / 189 (46); 119 requests, 32/8 heads, head size 64, 61.9 / 56.1.  Not for small batches,
+// whose K/V may still be in the last-level cache (256 MB) from the kernels before: of three batches
+// in turn 45.1 / 43.3 us at 107 MB each, 20.2 / 20.4 at 43, 23.9 / 26.1 at 58 (40/10 heads).  Not for
+// units of more tiles (the hint costs them 17 % at two tiles over 300-900 keys, 10-13 % at four to
+// eight), and not where less than a quarter of the bytes is read once: an instance of the kernel
+// with both kinds of copies is up to 2 % slower on the others.
+constexpr int64_t kStreamKvBytes = 96 << 20;
+
 constexpr int kNarrowRows = 16;  // rows per item of the bandwidth-oriented kernel
 constexpr int kWideRows = 128;   // rows per item of the matrix-core kernel (4 waves x 32 rows)
 constexpr int kTileRows = 256;   // rows per item of the 256-row matrix-core kernel (4 waves x 64)
@@ -197,6 +211,7 @@ struct pv_plan {
     // split_items): the narrow kernel takes its probabilities in two 16-bit terms, items of the
     // 128-row kernel renew their reference
     bool narrow_two_terms, wide_renews;
+    bool wide_streams;  // items of the 128-row kernel that are `alone` read K/V with the streaming hint
     size_t workspace_bytes;
 
     // Host image of everything the kernels read from the plan: the nine arrays above, each at a

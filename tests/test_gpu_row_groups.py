@@ -1,9 +1,11 @@
-"""Matrix-core kernel, on a real MI355X: which token and head a row is, for groups that do not divide
-a tile of rows, and the last block of an item, whose V slots past the end are zeroed in LDS."""
+"""Matrix-core kernel, on a real MI355X: which token and head a row is, for groups that do not divide a
+tile of rows; the last block of an item, whose V slots past the end are zeroed in LDS; items that read
+their K/V with the streaming hint."""
 import numpy as np
 import pytest
 
 import helpers as H
+from test_gpu_parity import _full_size_parity
 from paper_2312_05516_amd import workloads as wl
 
 pytestmark = pytest.mark.gpu
@@ -39,3 +41,20 @@ def test_last_block(oracle, head_dim, last, scale):
                           b.page_table, b.ctx_lens, b.q_lens, b.q_start, scale)
     err = np.abs(H.bits_to_f64(got, b.dtype) - want).max()
     assert err <= H.TOL[b.dtype], err
+
+
+@pytest.mark.parametrize("heads,dtype,ctx,reqs", [
+    ((10, 10, 128), "f16", 1100, 24), ((40, 10, 128), "bf16", 1100, 24),
+    ((32, 8, 64), "bf16", 1100, 60), ((12, 12, 64), "f16", 1100, 40),
+    ((10, 10, 128), "bf16", 7000, 6),    # KV ranges in parts
+    ((20, 20, 128), "f16", 1200, 20)])   # renewed references
+def test_units_of_one_tile_in_a_large_batch(oracle, heads, dtype, ctx, reqs):
+    """More K/V than the limit from which units of one 128-row tile read theirs with the streaming
+    hint, beside units of several tiles and generation steps, which end anywhere in a block."""
+    rng = np.random.default_rng(reqs)
+    g = heads[0] // heads[1]
+    new = np.array([(1, 128 // g, 40 // g, 150 // g)[i % 4] for i in range(reqs)])
+    b = wl.custom(rng.integers(ctx - 100, ctx + 100, size=reqs), new, num_q_heads=heads[0],
+                  num_kv_heads=heads[1], head_dim=heads[2], dtype=dtype, seed=reqs)
+    assert 4 * int(b.kv_lens.sum()) * heads[1] * heads[2] > 96 << 20
+    _full_size_parity(oracle, b, [0, 1, 2, 3], [0, heads[1] - 1])
