@@ -475,6 +475,7 @@ pv_status build_plan(const pv_pool_desc *pool, int32_t num_q_heads, const int32_
     if (tune.tile_batch_min_keys > 0 && tune.tile_min_keys > tune.tile_batch_min_keys &&
         pool->head_dim == 128) {
         int64_t pairs_all = 0, pairs_tile = 0, items = 0, keys = 0, longest = 0;
+        int64_t pairs_long = 0, long_items = 0;  // of units that qualify under the usual limit
         for (int32_t r = 0; r < num_reqs; ++r) {
             const int64_t n = q_lens[r], c = ctx_lens[r];
             if (n == 0) continue;
@@ -484,6 +485,10 @@ pv_status build_plan(const pv_pool_desc *pool, int32_t num_q_heads, const int32_
                 const int64_t tiles = rows_total / kTileRows;
                 pairs_tile += tiles * kTileRows * kv;
                 items += tiles * pool->num_kv_heads;
+                if (kv >= tune.tile_min_keys) {
+                    long_items += tiles * pool->num_kv_heads;
+                    pairs_long += rows_total * kv;
+                }
                 keys += tiles * pool->num_kv_heads * kv;
                 longest = std::max(longest, kv);
             }
@@ -492,6 +497,8 @@ pv_status build_plan(const pv_pool_desc *pool, int32_t num_q_heads, const int32_
         chunk = std::max<int64_t>(chunk, tune.min_split_keys);
         if (items >= tune.split_target && pairs_tile * 10 >= pairs_all * 9 && longest <= 2 * chunk)
             tune_batch.tile_min_keys = tune.tile_batch_min_keys;
+        else if (long_items < (pairs_long * 2 >= pairs_all ? kTileMinItems : kTileMinItemsBeside))
+            tune_batch.tile_min_keys = 0;
     }
     bool all_wide = false;
     if (tune.unify) {

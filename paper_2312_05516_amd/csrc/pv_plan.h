@@ -132,6 +132,18 @@ constexpr int64_t kStreamKvBytes = 96 << 20;
 constexpr int kNarrowRows = 16;  // rows per item of the bandwidth-oriented kernel
 constexpr int kWideRows = 128;   // rows per item of the matrix-core kernel (4 waves x 32 rows)
 constexpr int kTileRows = 256;   // rows per item of the 256-row matrix-core kernel (4 waves x 64)
+// The 256-row kernel takes a batch's long units only if they have this many tiles.  Fewer leave
+// CUs idle, or are cut into parts (about 1024) whose rows, twice as many as the 128-row kernel's,
+// the merge has to read, and their remaining rows are a launch of their own that does not fill the
+// GPU either.  Whole step with the 256-row kernel and without it, prompts over 8-28 K keys: 10 tiles
+// (1 x 365 tokens, 10/10 heads) 121.6 / 59.2 us, 16 (1 x 70, 64/8) 151 / 77, 40 (4 x 85, 40/10) 218 /
+// 114, 80 (2 x 188, 64/8) 355 / 282, 112 402 / 310, 158 436 / 381, 170 (17 x 278, 10/10) 523 / 373; 186
+// 528 / 536, 192 485 / 543, 288 844 / 949.  (Of 186 to 300 tiles those with many remaining rows would
+// still gain, 230 with a fifth of them 1004 / 856, others lose: 216 with as many 668 / 696.)  Where
+// the long units are less than half of a batch's pairs: 40 tiles beside 48 prompts, 40/40 heads, 563 /
+// 463, 96 beside 20, 64/8 heads, 470 / 389; 128 beside 15 699 / 635, which stay with both kernels.
+constexpr int kTileMinItems = 180;
+constexpr int kTileMinItemsBeside = 112;
 constexpr int kCUs = 256;
 // Workgroups that run at once on the CUs: two of the narrow kernel on each (212-216 registers
 // a lane; head size 64 has room for three, but 512 parts are ahead of more: 4 generation steps,
