@@ -10,7 +10,7 @@
 // blocks (two pages) of the item's KV range round-robin; nothing is shared between them, so K and
 // V go straight from HBM into registers in the lane order the matrix cores consume (the pool
 // stores runs of 8 elements along the contracted dimension, 16 bytes = one lane's operand), with
-// streaming (non-temporal) loads, since every byte is used once, and with the next block's loads in
+// streaming (non-temporal) loads where every byte is used once, and with the next block's loads in
 // flight while the current one is processed.  Scores are produced
 // transposed, S^T = K Q^T (16 keys x 16 rows per v_mfma_f32_16x16x32), so that every lane owns one
 // query row: the softmax needs no cross-lane traffic beyond two exchanges for the running
@@ -35,7 +35,15 @@ struct NarrowFrag {
 // (pv_plan::narrow_two_terms) take it: 8 more matrix-core instructions and about 40 of the vector
 // ALU per block, 4 generation steps over 0.7-9 K keys 23.6 -> 23.9 us.  Both terms of a positive
 // probability are positive, so that an infinite V gives infinity and not infinity minus infinity.
-template <typename T, int D, bool TWO>
+//
+// STREAM: K/V are read with the streaming hint, unless a fifth of their bytes belongs to units of
+// more than 16 rows, whose two items share them: with the hint the second finds little of them in
+// L2.  113 requests x 4 tokens over 1-2 K, 64/8 heads, whole step 210.6 -> 153.5 us without the
+// hint, 11 28.9 -> 21.7, 151 x 24 tokens, 12/12 heads, head size 64, 229.8 -> 166.1.  Units of one
+// item lose 8-14 % without it (113 generation steps 119.3 -> 132.2; below 100 MB of K/V +-3 %).  100
+// requests of which a fifth (30 %, half) bring 4 tokens: 116.5 / 118.8 us with and without the hint
+// (131.0 / 122.9, 141.2 / 122.6).
+template <typename T, int D, bool TWO, bool STREAM>
 __global__ __launch_bounds__(256, 2) void attn_narrow_kernel(
     const WorkItem *__restrict__ items, const uint16_t *__restrict__ q,
     const uint16_t *__restrict__ k_pages, const uint16_t *__restrict__ v_pages,
@@ -121,11 +129,11 @@ __global__ __launch_bounds__(256, 2) void attn_narrow_kernel(
         for (int t = 0; t < 2; ++t) {
             const uint16_t *kb = k_pages + (ksel[t] ? base1 : base0) + koff[t];
 #pragma unroll
-            for (int ks = 0; ks < KS; ++ks) f.k[t][ks] = load16_stream(kb + ks * (4 * 16 * 8));
+            for (int ks = 0; ks < KS; ++ks) f.k[t][ks] = load16_as<STREAM>(kb + ks * (4 * 16 * 8));
         }
         const uint16_t *vb = v_pages + (vsel ? base1 : base0) + voff;
 #pragma unroll
-        for (int blk = 0; blk < NB; ++blk) f.v[blk] = load16_stream(vb + blk * (16 * 8));
+        for (int blk = 0; blk < NB; ++blk) f.v[blk] = load16_as<STREAM>(vb + blk * (16 * 8));
     };
 
     f32x4 o[NB];
@@ -373,8 +381,11 @@ static hipError_t launch_narrow_t(const pv_plan *plan, const DeviceLists &dl, co
 {
     const int n = (int)plan->narrow.size();
     if (n == 0) return hipSuccess;
-    auto kernel = plan->narrow_two_terms ? attn_narrow_kernel<T, D, true>
-                                         : attn_narrow_kernel<T, D, false>;
+    auto kernel = plan->narrow_streams
+                      ? (plan->narrow_two_terms ? attn_narrow_kernel<T, D, true, true>
+                                                : attn_narrow_kernel<T, D, false, true>)
+                      : (plan->narrow_two_terms ? attn_narrow_kernel<T, D, true, false>
+                                                : attn_narrow_kernel<T, D, false, false>);
     hipLaunchKernelGGL(kernel, dim3(n), dim3(256), 0, stream, dl.narrow, (const uint16_t *)q,
                        (const uint16_t *)k_pages, (const uint16_t *)v_pages, page_table,
                        plan->max_pages_per_req, plan->num_q_heads, plan->pool.num_kv_heads,

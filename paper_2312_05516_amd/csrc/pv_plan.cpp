@@ -533,14 +533,19 @@ pv_status build_plan(const pv_pool_desc *pool, int32_t num_q_heads, const int32_
         plan->narrow.reserve(n_narrow);
         plan->wide.reserve(n_wide);
     }
-    int64_t kv_bytes = 0, alone_bytes = 0;  // K/V read by all units, by those of one 128-row tile
+    // K/V of all units, and of the units of a kernel that read theirs once or, in several items,
+    // more than once
+    int64_t kv_bytes = 0, wide_once = 0, wide_shared = 0, narrow_once = 0, narrow_shared = 0;
     for (int32_t r = 0; r < num_reqs; ++r) {
         const int32_t n = q_lens[r], c = ctx_lens[r];
         if (n == 0) continue;
         const int32_t rows_total = n * G;
         const int64_t unit_bytes = 4 * ((int64_t)c + n) * pool->num_kv_heads * pool->head_dim;
         kv_bytes += unit_bytes;
-        if (rows_total <= kWideRows) alone_bytes += unit_bytes;
+        if (rows_total >= tune.wide_min_rows || all_wide)
+            (rows_total <= kWideRows ? wide_once : wide_shared) += unit_bytes;
+        else
+            (rows_total <= kNarrowRows ? narrow_once : narrow_shared) += unit_bytes;
         for (int32_t hk = 0; hk < pool->num_kv_heads; ++hk) {
             WorkItem w;
             std::memset(&w, 0, sizeof w);
@@ -585,7 +590,8 @@ pv_status build_plan(const pv_pool_desc *pool, int32_t num_q_heads, const int32_
         split_items(plan->narrow, plan->combine, slots, tune, &narrow_rule, pool->head_dim);
     plan->wide_renews =
         split_items(plan->wide, plan->combine, slots, tune, &wide_rule, pool->head_dim);
-    plan->wide_streams = kv_bytes > kStreamKvBytes && alone_bytes * 4 >= kv_bytes;
+    plan->wide_streams = kv_bytes > kStreamKvBytes && wide_once * 3 >= wide_shared;
+    plan->narrow_streams = narrow_once > narrow_shared * 4;
     split_items(plan->tile256, plan->combine, slots, tune, nullptr, pool->head_dim,
                 kTileMaxKeys);
     if (slots > INT32_MAX / 2) {

@@ -223,7 +223,9 @@ struct pv_plan {
     // split_items): the narrow kernel takes its probabilities in two 16-bit terms, items of the
     // 128-row kernel renew their reference
     bool narrow_two_terms, wide_renews;
-    bool wide_streams;  // items of the 128-row kernel that are `alone` read K/V with the streaming hint
+    // K/V with the streaming hint: items of the 128-row kernel that are `alone`; all of the narrow
+    // kernel's
+    bool wide_streams, narrow_streams;
     size_t workspace_bytes;
 
     // Host image of everything the kernels read from the plan: the nine arrays above, each at a

@@ -1,6 +1,6 @@
 """Matrix-core kernel, on a real MI355X: which token and head a row is, for groups that do not divide a
 tile of rows; the last block of an item, whose V slots past the end are zeroed in LDS; items that read
-their K/V with the streaming hint."""
+their K/V with the streaming hint, and items of the narrow kernel that share theirs."""
 import numpy as np
 import pytest
 
@@ -40,6 +40,26 @@ def test_last_block(oracle, head_dim, last, scale):
     want, _ = oracle.attn(H.pool_tuple(b), b.num_q_heads, case.q, case.k_pool1, case.v_pool1,
                           b.page_table, b.ctx_lens, b.q_lens, b.q_start, scale)
     err = np.abs(H.bits_to_f64(got, b.dtype) - want).max()
+    assert err <= H.TOL[b.dtype], err
+
+
+@pytest.mark.parametrize("heads,new,reqs", [((8, 1, 128), 4, 5), ((8, 1, 128), 3, 600),
+                                            ((2, 2, 128), 24, 300), ((4, 1, 64), 8, 5),
+                                            ((1, 1, 64), 32, 600), ((16, 1, 64), 2, 300)])
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+def test_units_of_two_narrow_items(oracle, heads, new, reqs, dtype):
+    """17 to 32 rows a unit, so that two items read the same K/V, beside units of one; short lists
+    are cut (with probabilities in two terms) and merged, long ones are not."""
+    rng = np.random.default_rng(new)
+    ctx = rng.integers(0, 1500 if reqs == 5 else 90, size=reqs)
+    b = wl.custom(ctx, np.where(np.arange(reqs) % 3 == 1, 1, new), num_q_heads=heads[0],
+                  num_kv_heads=heads[1], head_dim=heads[2], dtype=dtype, seed=reqs)
+    case = H.make_case(b, fill="nan")
+    got, _, _ = H.gpu_run(case)
+    want, _ = oracle.attn(H.pool_tuple(b), b.num_q_heads, case.q, case.k_pool1, case.v_pool1,
+                          b.page_table, b.ctx_lens, b.q_lens, b.q_start, b.scale)
+    err = np.abs(H.bits_to_f64(got, b.dtype) - want).max()
+    print(f"{heads}, {reqs} x {new} tokens {dtype}: {err:.3e}", flush=True)
     assert err <= H.TOL[b.dtype], err
 
 
