@@ -445,7 +445,9 @@ pv_status pv_multi_token_paged_attn(const pv_pool_desc *pool, int32_t num_q_head
     pv_status s = check_prefix(q_lens, q_start, num_reqs, total_q);
     if (s != PV_OK) return s;
     pv_plan *plan = nullptr;
-    s = pv_plan_create(pool, num_q_heads, ctx_lens, q_lens, num_reqs, max_pages_per_req, &plan);
+    pv::Tuning tune = pv::default_tuning();
+    tune.even_cus = false;
+    s = pv::build_plan(pool, num_q_heads, ctx_lens, q_lens, num_reqs, max_pages_per_req, tune, &plan);
     if (s != PV_OK) return s;
     if (plan->total_q == 0) {
         pv_plan_destroy(plan);

@@ -49,6 +49,7 @@ Tuning default_tuning()
     t.xcds = env_int("PV_XCDS", 8);
     t.unify = env_int("PV_UNIFY", 1) == 1 ? 1 : 0;  // any other positive value switches it off
     t.unify_max_steps = env_int("PV_UNIFY_MAX_STEPS", 90000);
+    t.even_cus = true;
     {
         const char *v = std::getenv("PV_TILE_MIN_KEYS");
         t.tile_min_keys = (v && *v == '0' && !v[1]) ? 0 : env_int("PV_TILE_MIN_KEYS", 8192);
@@ -281,13 +282,83 @@ static bool split_items(std::vector<WorkItem> &items, std::vector<CombineItem> &
     return fewer;
 }
 
+// Order of the XCDs' items where all of them run at once: workgroup k of an XCD goes to CU k % cus, so
+// that round after round every CU gets one more.  The longest items are dealt first, each to the CU
+// with the least to do, and every CU takes as many as the rounds give it.  In the order of the list
+// below some CUs get several long items and others short ones only.  The 128-row kernel over that
+// order and over this one, in microseconds: 64 / 8 heads, 2 first prompts of 68-1291 tokens 49.0 /
+// 44.1; 32 / 8 heads of size 64, 4 of 392-955 32.1 / 26.9; 11 prompts of 113-459 on contexts of
+// 175-923 51.9 / 46.5; geometric mean of 50 batches with 257-1000 tiles 3.1 % less, all but one within
+// 0.5 % of the old order or ahead (1 % behind: 5 of 68-223, 40 / 40 heads, 18.4 / 18.5).
+// Among CUs with equal loads the last one is taken: dealt from the first CU up, the longest items
+// went to the CUs that get one item more, and lists a little over one round (276-352 items) lost
+// 2-4 %.  The 16-row kernel reads its items at the rate of memory whatever shares a CU: no difference.
+// Lengths are told apart to 1/128 of the longest one, so that one counting pass sorts them:
+// 612-760 items take 6-9 us of the host on top of 13-20 for the whole plan, 25-45 with a comparison
+// sort for each XCD and a branch for each CU.  That is for a plan that several layers use.
+static void pair_up(const std::vector<WorkItem> &items, std::vector<std::vector<uint32_t>> &queues)
+{
+    const size_t cus = kCUs / queues.size();  // a power of two
+    int64_t longest = 1;
+    for (const WorkItem &w : items) longest = std::max(longest, item_cost(w));
+    int shift = 0;
+    while ((longest >> shift) > 255) ++shift;
+
+    const uint32_t set_up = kItemSetUp >> shift;
+
+    struct Dealt { uint32_t pos; uint16_t queue, steps; };
+    uint32_t begin[257] = {};
+    size_t n = 0, most = 0;
+    for (const std::vector<uint32_t> &q : queues)
+        if (q.size() > cus) {
+            for (uint32_t pos : q) ++begin[256 - (item_cost(items[pos]) >> shift)];
+            n += q.size();
+            most = std::max(most, q.size());
+        }
+    for (int b = 0; b < 256; ++b) begin[b + 1] += begin[b];
+    std::vector<Dealt> dealt(n);
+    for (size_t k = 0; k < most; ++k)  // the XCDs in turn, whose dealing does not depend on each other
+        for (size_t q = 0; q < queues.size(); ++q)
+            if (k < queues[q].size() && queues[q].size() > cus) {
+                const uint32_t pos = queues[q][k];
+                const uint16_t steps = (uint16_t)(item_cost(items[pos]) >> shift);
+                dealt[begin[255 - steps]++] = Dealt{pos, (uint16_t)q, steps};
+            }
+
+    // load * cus + (cus - 1 - CU): the least of them names the CU too, the last one of equals.  Loads
+    // are counted in the sorted steps, so that a float (which has a minimum of four in one
+    // instruction) holds every key: at most (n + cus) * 351 < 2^24.
+    constexpr float kFull = 3e38f;
+    const size_t stride = std::max<size_t>(cus, 16);
+    std::vector<float> keys(queues.size() * stride, kFull);
+    std::vector<uint32_t> taken(queues.size() * cus, 0);
+    for (size_t q = 0; q < queues.size(); ++q)
+        for (size_t c = 0; c < cus; ++c) keys[q * stride + c] = (float)(cus - 1 - c);
+    for (const Dealt &it : dealt) {
+        float *key = &keys[it.queue * stride], least[16];
+        for (size_t l = 0; l < 16; ++l) least[l] = key[l];
+        for (size_t c = 16; c < stride; c += 16)
+            for (size_t l = 0; l < 16; ++l) least[l] = key[c + l] < least[l] ? key[c + l] : least[l];
+        for (size_t w = 8; w > 0; w /= 2)
+            for (size_t l = 0; l < w; ++l) least[l] = least[l + w] < least[l] ? least[l + w] : least[l];
+        const uint32_t best = (uint32_t)least[0];
+        const size_t c = cus - 1 - (best & (cus - 1));
+        std::vector<uint32_t> &queue = queues[it.queue];
+        const size_t k = taken[it.queue * cus + c]++ * cus + c;
+        queue[k] = it.pos;
+        key[c] = k + cus < queue.size() ? (float)(best + (it.steps + set_up) * cus) : kFull;
+    }
+}
+
 // Order of the work list = order of workgroup dispatch.  Two goals:
 //  * longest first, so that in-order dispatch approximates longest-processing-time scheduling;
 //  * items that stream the same K/V (the row tiles of one (request, KV head, KV part)) should run
 //    at the same time on the same XCD, so that the second and later tiles hit in that XCD's L2.
 //    Workgroup i of a launch goes to XCD i % xcds, so a group's items are placed `xcds` positions
 //    apart.  Groups are dealt to the XCDs greedily by accumulated cost (longest group first).
-static void order_items(std::vector<WorkItem> &items, int xcds)
+// A list of at most `slots` items runs at once, and which items share a CU is all that its order
+// decides: see pair_up (0: keep the order of the list).
+static void order_items(std::vector<WorkItem> &items, int xcds, size_t slots)
 {
     if (items.empty()) return;
     if (xcds < 1) xcds = 1;
@@ -346,6 +417,8 @@ static void order_items(std::vector<WorkItem> &items, int xcds)
         for (uint32_t i = g.begin; i < g.end; ++i) queue[best].push_back(order[i]);
         load[best] += g.cost;
     }
+    if (n > (size_t)kCUs && n <= slots && kCUs % xcds == 0) pair_up(items, queue);
+
     // 3. interleave: position k*xcds + x takes the k-th item of XCD x's queue; once a queue is
     //    empty its positions are filled from the queues that still have items
     std::vector<WorkItem> out;
@@ -613,9 +686,9 @@ pv_status build_plan(const pv_pool_desc *pool, int32_t num_q_heads, const int32_
         delete plan;
         return PV_ERR_OUT_OF_RANGE;
     }
-    order_items(plan->narrow, tune.xcds);
-    order_items(plan->wide, tune.xcds);
-    order_items(plan->tile256, tune.xcds);
+    order_items(plan->narrow, tune.xcds, 0);
+    order_items(plan->wide, tune.xcds, tune.even_cus ? kWideSlots : 0);
+    order_items(plan->tile256, tune.xcds, 0);
     plan->partial_slots = slots;
     int64_t merge_rows = 0;
     for (const CombineItem &c : plan->combine) merge_rows += c.row_count;

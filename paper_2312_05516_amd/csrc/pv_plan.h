@@ -147,10 +147,11 @@ constexpr int kTileMinItemsBeside = 112;
 constexpr int kCUs = 256;
 // Workgroups that run at once on the CUs: two of the narrow kernel on each (212-216 registers
 // a lane; head size 64 has room for three, but 512 parts are ahead of more: 4 generation steps,
-// 32/8 heads, 13.4 us with 512 parts, 14.2 with 656), three of the 128-row kernel (165-167
+// 32/8 heads, 13.4 us with 512 parts, 14.2 with 656), three of the 128-row kernel (161-163
 // registers, 48 KiB of LDS).
 constexpr int kNarrowSlots = 512;
 constexpr int kWideSlots = 768;
+constexpr int kItemSetUp = 96;  // keys that take an item as long as its set-up and its result
 constexpr int kSplitTarget = 1024;
 constexpr int kFewWideItems = 512;  // shorter lists of the 128-row kernel are cut to fill the GPU
 constexpr int kKvBlock = 32;     // keys per inner step (two pages)
@@ -202,6 +203,8 @@ struct Tuning {
     int32_t tile_batch_min_keys;  // the lower limit that applies instead when nearly all of a
                              // batch's work qualifies under it and its items need no splitting
                              // (0: no such rule; it is off when tile_min_keys is set by hand)
+    bool even_cus;           // order lists that run at once by what shares a CU (see pair_up); a plan
+                             // for one launch alone does not: 6-9 us of host time for 1-5 us of it
 };
 
 }  // namespace pv

@@ -33,3 +33,48 @@ def test_few_tiles_beside_other_work(monkeypatch, new, reqs, tiles):
     assert len({(int(i[0]), int(i[1]), int(i[2])) for i in items}) == tiles
     assert pv.plan_num_work_items(plan, 1) > 0
     plan.destroy()
+
+
+@pytest.mark.parametrize("heads,new,reqs", [
+    ((8, 8, 64), 128, 32),                  # 256 items: a CU each
+    ((8, 8, 64), 128 * 2 + 1, 11),          # 264
+    ((64, 8, 128), 88, 8),                  # 352
+    ((40, 40, 128), 700, 2), ((12, 12, 64), 500, 13),
+    ((64, 8, 128), 330, 4),                 # 672
+    ((64, 8, 128), 16 * 24, 4),             # 768: the last that runs at once
+    ((8, 8, 64), 128, 97), ((5, 5, 64), 300, 20), ((1, 1, 128), 128, 300)])
+@pytest.mark.parametrize("uneven", [False, True])
+def test_items_that_run_at_once_share_the_cus_evenly(monkeypatch, heads, new, reqs, uneven):
+    """Workgroup i goes to XCD i % 8, and workgroup k of an XCD to its CU k % 32."""
+    for name in ("PV_XCDS", "PV_TILE_MIN_KEYS", "PV_SPLIT_TARGET"):
+        monkeypatch.delenv(name, raising=False)
+    group = heads[0] // heads[1]
+    desc = pv.pool_desc(1 << 17, heads[1], heads[2], "f16")
+    ctx = [(97 * r * r) % 1400 if uneven else 0 for r in range(reqs)]
+    q = [new - (29 * r) % (new // 3) if uneven else new for r in range(reqs)]
+    plan = pv.plan_create(desc, heads[0], ctx, q, 1024)
+    items = [pv.plan_work_item(plan, 1, i) for i in range(pv.plan_num_work_items(plan, 1))]
+    n = len(items)
+    # every row of every (request, KV head) once, over all keys that it sees
+    rows = [0] * reqs
+    for req, _, begin, count, kv_begin, kv_end, _, parts in (map(int, i) for i in items):
+        if parts == 1:
+            assert kv_begin == 0 and kv_end == ctx[req] + (begin + count - 1) // group + 1
+        rows[req] += (kv_end - kv_begin) * count
+    for r in range(reqs):
+        tiles = [(b, min(128, q[r] * group - b)) for b in range(0, q[r] * group, 128)]
+        assert rows[r] == heads[1] * sum(c * (ctx[r] + (b + c - 1) // group + 1) for b, c in tiles)
+    if not 256 < n <= 768 or any(int(i[7]) > 1 for i in items):
+        plan.destroy()
+        return
+    # No CU has much more to do than one that takes as many items, beyond its longest item: the
+    # longest are dealt first, each to the CU with the least.
+    cost = [int(i[5] - i[4]) + 96 for i in items]
+    for x in range(8):
+        mine = [cost[i] for i in range(x, n, 8)]
+        per_cu = [mine[c::32] for c in range(32)]
+        for a in per_cu:
+            for b in per_cu:
+                if len(a) == len(b):
+                    assert sum(a) - sum(b) <= max(a) + max(b) // 16, (x, a, b)
+    plan.destroy()
