@@ -16,7 +16,7 @@
 // lanes read 256 consecutive bytes (no bank conflicts, no padding, no transposes).  Scores are
 // produced transposed, S^T = K Q^T (v_mfma_f32_32x32x16), so each lane owns one query row (softmax
 // without cross-lane traffic except one exchange for the maximum) and the probabilities are
-// already the B operand of O^T += V^T P^T.  About 166 VGPRs (134 for head size 64) and 48 KiB of
+// already the B operand of O^T += V^T P^T.  161-163 VGPRs (127-130 for head size 64) and 48 KiB of
 // LDS let three workgroups share a CU, whose wavefronts overlap each other's matrix-core,
 // vector-ALU and LDS phases.  One raw s_barrier per block, preceded by a wait that leaves only the
 // newest loads in flight.  Blocks that touch the causal boundary or the end of the sequence run in a
