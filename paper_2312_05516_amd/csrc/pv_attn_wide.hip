@@ -117,7 +117,6 @@ __global__ __launch_bounds__(256, 3) void attn_wide_kernel(
     const int last_pg = (it.kv_end - 1) >> 4;
     const int pg0 = it.kv_begin >> 4;
     const int nblocks = (it.kv_end - it.kv_begin + BK - 1) / BK;
-    const uint32_t page_bytes = (uint32_t)num_kv_heads * TILE_BYTES;
     const uint32_t lane_bytes = (uint32_t)lane * 16u;
     // asynchronous copies move bytes [w*1024, w*1024+1024) of every 4 KiB pass over the K (V) part:
     // ids of the pages that this wavefront's pieces of a block lie in (a page past the end is never
@@ -139,7 +138,9 @@ __global__ __launch_bounds__(256, 3) void attn_wide_kernel(
 #pragma unroll
         for (int p = 0; p < PASSES; ++p) {
             const int off = p * 4096 + w * 1024;  // wavefront-uniform
-            const uint64_t page_off = (uint64_t)(uint32_t)(p ? id1 : id0) * page_bytes;
+            // (a page may be larger than 4 GiB)
+            const uint64_t page_off =
+                (uint64_t)(uint32_t)(p ? id1 : id0) * (uint32_t)num_kv_heads * TILE_BYTES;
             lds_dma16<STREAM>(k_src + page_off, lane_bytes, stage + off);
             lds_dma16<STREAM>(v_src + page_off, lane_bytes, stage + HALF_BYTES + off);
         }
