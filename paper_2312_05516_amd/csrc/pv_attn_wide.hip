@@ -340,6 +340,15 @@ __global__ __launch_bounds__(256, 3) void attn_wide_kernel(
     int lane_again = (int)(lane_bytes >> 4);
     asm volatile("" : "+v"(lane_again));
     const int own = 32 * w + (lane_again & 31), half = lane_again >> 5;
+    if (q_keep == 0) {  // a scale of zero: an infinity or a NaN among the row's queries makes it NaN
+        int tok, head;
+        rows.at(own < it.row_count ? own : 0, tok, head);
+        const uint16_t *qrow =
+            q + ((int64_t)(it.q_row0 + tok) * num_q_heads + it.kv_head * group + head) * D;
+#pragma unroll 1
+        for (int ks = 0; ks < KS; ++ks)
+            if (any_not_finite<T>(load16(qrow + 16 * ks + 8 * half))) l_run = NAN;
+    }
     const float l_tot = add_halves(l_run);
     if (it.split_count == 1) {
         // The accumulators hold 8 bytes of 32 different rows per register pair: stored from there,
@@ -407,7 +416,8 @@ static hipError_t launch_wide_t(const pv_plan *plan, const DeviceLists &dl, cons
 {
     const int n = (int)plan->wide.size();
     // A negative scale is applied as |scale| on negated queries, a zero scale as 1 on zeros: so
-    // that a masked score, minus infinity, is a probability of zero whatever the scale.
+    // that a masked score, minus infinity, is a probability of zero whatever the scale.  (Zero times
+    // an infinity or a NaN among the queries is NaN: the kernel looks for these at its end.)
     float c = (scale < 0.f ? -scale : scale) * kLog2e;
     const uint32_t q_sign = scale < 0.f ? 0x80008000u : 0u;
     const uint32_t q_keep = c == 0.f ? 0u : 0xFFFFFFFFu;

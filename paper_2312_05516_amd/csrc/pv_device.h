@@ -21,6 +21,7 @@ constexpr float kRenewLog2 = 4.f;  // how far below the highest one a renewed re
 
 struct F16 {
     typedef f16x8 vec8;
+    static constexpr uint32_t kExponent = 0x7C00u;  // all ones: infinity or NaN
     static __device__ __forceinline__ f32x4 mfma16(vec8 a, vec8 b, f32x4 c)
     {
         return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0);
@@ -88,6 +89,7 @@ struct F16 {
 
 struct BF16 {
     typedef bf16x8 vec8;
+    static constexpr uint32_t kExponent = 0x7F80u;
     static __device__ __forceinline__ f32x4 mfma16(vec8 a, vec8 b, f32x4 c)
     {
         return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
@@ -145,6 +147,17 @@ template <typename T>
 __device__ __forceinline__ typename T::vec8 as_vec8(u32x4 raw)
 {
     return __builtin_bit_cast(typename T::vec8, raw);
+}
+
+// whether one of eight 16-bit values is an infinity or a NaN
+template <typename T>
+__device__ __forceinline__ bool any_not_finite(u32x4 raw)
+{
+    constexpr uint32_t LO = T::kExponent, HI = T::kExponent << 16;
+    bool any = false;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) any |= (raw[i] & LO) == LO || (raw[i] & HI) == HI;
+    return any;
 }
 
 __device__ __forceinline__ u32x4 load16(const void *p)

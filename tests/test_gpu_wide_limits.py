@@ -45,3 +45,35 @@ def test_pages_of_4_gib(monkeypatch, head_dim, hkv):
         err = float((w @ vv.double() - out[0, hd].double()).abs().max())
         print(f"head {hd} of {hkv}: {err:.2e}", flush=True)
         assert err <= H.TOL["f16"], hd
+
+
+@pytest.mark.parametrize("head_dim,dtype", [(64, "f16"), (128, "f16"), (128, "bf16")])
+@pytest.mark.parametrize("scale", [0.0, -0.0])
+def test_zero_scale_does_not_hide_infinite_queries(head_dim, dtype, scale):
+    """A scale of zero weighs all visible keys alike.  An infinity or a NaN in a query is still NaN
+    (0 * inf), in its own row and no other; the same in the keys, for the rows that see them."""
+    b = wl.custom([50, 0], [60, 40], num_q_heads=2, num_kv_heads=2, head_dim=head_dim, dtype=dtype,
+                  seed=5)
+    case = H.make_case(b, fill="nan")
+    inf, nan = (0x7C00, 0x7E00) if dtype == "f16" else (0x7F80, 0x7FC0)
+    case.q[3, 0, 7] = inf
+    case.q[17, 1, head_dim - 1] = 0x8000 | inf
+    case.q[59, 0, 0] = nan
+    case.q[99, 1, 1] = 0x8000 | nan
+    hidden = [(3, 0), (17, 1), (59, 0), (99, 1)]
+    got, _, _ = H.gpu_run(case, scale=scale)
+    got = H.bits_to_f64(got, dtype)
+    case.q[:] = 0
+    want = H.dense_causal_attention(case, scale=0.0)
+    for row, head in hidden:
+        assert np.isnan(got[row, head]).all(), (row, head)
+        got[row, head] = want[row, head]
+    assert np.isfinite(got).all()
+    assert np.abs(got - want).max() <= H.TOL[dtype]
+    # an infinite key at position 80 of the first request: token 30 of the new ones and later see it
+    case.k_new[30, 0, 5] = inf
+    got, _, _ = H.gpu_run(case, scale=scale)
+    got = H.bits_to_f64(got, dtype)
+    assert np.isnan(got[30:60, 0]).all()
+    got[30:60, 0] = want[30:60, 0]
+    assert np.abs(got - want).max() <= H.TOL[dtype]
