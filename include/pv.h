@@ -155,7 +155,9 @@ size_t pv_plan_workspace_bytes(const pv_plan *plan);
 /* Work-item introspection (for tests and reports).  kind: 0 = items of the bandwidth-oriented
  * kernel (at most 16 query rows per item), 1 = items of the matrix-core kernel (at most 128
  * rows), 2 = split-KV combine items, 3 = items of the 256-row matrix-core kernel (exactly 256
- * rows; the full 256-row tiles of units with at least 256 rows and 8192 keys, head size 128).
+ * rows: full 256-row tiles of units of head size 128 with at least 256 rows and 8192 keys, or 1536
+ * where nearly the whole batch is such units; only where a batch has enough of them, in tiles or in
+ * tiles times keys, for one more launch to pay).
  * pv_plan_work_item fills eight int32 fields:
  *   req, kv_head, row_begin, row_count, kv_begin, kv_end, split_index, split_count
  * where a "row" is a (new token, query head of the group) pair, row = token*G + g.  Which kernel

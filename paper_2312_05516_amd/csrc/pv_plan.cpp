@@ -563,7 +563,8 @@ pv_status build_plan(const pv_pool_desc *pool, int32_t num_q_heads, const int32_
     if (tune.tile_batch_min_keys > 0 && tune.tile_min_keys > tune.tile_batch_min_keys &&
         pool->head_dim == 128) {
         int64_t pairs_all = 0, pairs_tile = 0, items = 0, keys = 0, longest = 0;
-        int64_t pairs_long = 0, long_items = 0;  // of units that qualify under the usual limit
+        // of units that qualify under the usual limit, and of their full tiles
+        int64_t pairs_long = 0, pairs_long_tiles = 0, long_items = 0, long_keys = 0;
         for (int32_t r = 0; r < num_reqs; ++r) {
             const int64_t n = q_lens[r], c = ctx_lens[r];
             if (n == 0) continue;
@@ -575,7 +576,9 @@ pv_status build_plan(const pv_pool_desc *pool, int32_t num_q_heads, const int32_
                 items += tiles * pool->num_kv_heads;
                 if (kv >= tune.tile_min_keys) {
                     long_items += tiles * pool->num_kv_heads;
+                    long_keys += tiles * pool->num_kv_heads * kv;
                     pairs_long += rows_total * kv;
+                    pairs_long_tiles += tiles * kTileRows * kv;
                 }
                 keys += tiles * pool->num_kv_heads * kv;
                 longest = std::max(longest, kv);
@@ -585,8 +588,16 @@ pv_status build_plan(const pv_pool_desc *pool, int32_t num_q_heads, const int32_
         chunk = std::max<int64_t>(chunk, tune.min_split_keys);
         if (items >= tune.split_target && pairs_tile * 10 >= pairs_all * 9 && longest <= 2 * chunk)
             tune_batch.tile_min_keys = tune.tile_batch_min_keys;
-        else if (long_items < (pairs_long * 2 >= pairs_all ? kTileMinItems : kTileMinItemsBeside))
-            tune_batch.tile_min_keys = 0;
+        else if (long_items > 0 && long_items < kTileMinItems) {
+            // slots that the 128-row kernel's list of the same tiles fills, cut to run at once
+            const int64_t wide_parts = kWideSlots / (2 * long_items) * (2 * long_items);
+            int64_t limit = kTileKeysMixed;
+            if (pairs_long < pairs_all - pairs_long)
+                limit = kTileKeysMinority;
+            else if (pairs_long_tiles >= pairs_all - pairs_all / 50)
+                limit = wide_parts * 8 <= kWideSlots * 7 ? kTileKeysIdle : kTileKeysAlone;
+            if (long_keys < limit) tune_batch.tile_min_keys = 0;
+        }
     }
     bool all_wide = false;
     if (tune.unify) {

@@ -132,18 +132,32 @@ constexpr int64_t kStreamKvBytes = 96 << 20;
 constexpr int kNarrowRows = 16;  // rows per item of the bandwidth-oriented kernel
 constexpr int kWideRows = 128;   // rows per item of the matrix-core kernel (4 waves x 32 rows)
 constexpr int kTileRows = 256;   // rows per item of the 256-row matrix-core kernel (4 waves x 64)
-// The 256-row kernel takes a batch's long units only if they have this many tiles.  Fewer leave
-// CUs idle, or are cut into parts (about 1024) whose rows, twice as many as the 128-row kernel's,
-// the merge has to read, and their remaining rows are a launch of their own that does not fill the
-// GPU either.  Whole step with the 256-row kernel and without it, prompts over 8-28 K keys: 10 tiles
-// (1 x 365 tokens, 10/10 heads) 121.6 / 59.2 us, 16 (1 x 70, 64/8) 151 / 77, 40 (4 x 85, 40/10) 218 /
-// 114, 80 (2 x 188, 64/8) 355 / 282, 112 402 / 310, 158 436 / 381, 170 (17 x 278, 10/10) 523 / 373; 186
-// 528 / 536, 192 485 / 543, 288 844 / 949.  (Of 186 to 300 tiles those with many remaining rows would
-// still gain, 230 with a fifth of them 1004 / 856, others lose: 216 with as many 668 / 696.)  Where
-// the long units are less than half of a batch's pairs: 40 tiles beside 48 prompts, 40/40 heads, 563 /
-// 463, 96 beside 20, 64/8 heads, 470 / 389; 128 beside 15 699 / 635, which stay with both kernels.
+// The 256-row kernel takes a batch's long units only if they have this many tiles, or fewer with this
+// many keys over all tiles.  Few tiles are cut into about 1024 parts, whose rows, twice as many as
+// the 128-row kernel's, the merge has to read: 60-80 us more, whatever the number of keys; in return a
+// million tile keys take 95-110 us in place of 120-140.  So what counts is their product, and how well
+// the other kernel's list fills its slots.  Whole step with the 128-row kernel and with the 256-row
+// kernel, in microseconds, by million tile keys:
+//  * nothing but these tiles: 0.84 (20 tiles) 130 / 160, 1.66 (112) 240 / 260, 2.66 (176) 351 / 367,
+//    2.99 (96) 381 / 397, 3.40 (150) 460 / 462, 5.19 (176) 672 / 645, 5.9 (96) 733 / 699, 6.9 (112)
+//    859 / 763, 17.9 (160) 2442 / 1945.  Where the 128-row kernel's list leaves an eighth of the slots
+//    idle the 256-row kernel is ahead sooner: 2.41 (160) 342 / 331, 3.28 (150) 514 / 474, 3.45 (80)
+//    490 / 472; 2.13 (80) 314 / 326.
+//  * remaining rows or other requests beside them, which with the 256-row kernel are a launch of their
+//    own: 2.77 (170) 600 / 693, 3.79 (150) 571 / 593, 4.66 (80) 668 / 689, 4.90 (90) 659 / 694, 5.2 (60)
+//    889 / 801, 5.7 (152) 837 / 797, 7.3 (160) 1146 / 1082, 9.0 (90) 1537 / 1332, 13.2 (150) 2975 / 2440.
+//  * the long units less than half of the batch's pairs: 1.4 (112) 509 / 582, 1.6 (160) 486 / 560, 2.4
+//    (144) 828 / 881, 2.6 (128) 687 / 757, 3.6 (176) 1417 / 1464, 5.3 (120) 1585 / 1540.  The limit is
+//    lower than that asks for: one prompt of 512 tokens over 20 K keys among shorter ones (the 2.6)
+//    has always gone to the kernel for long units.
+// From kTileMinItems tiles on the 256-row kernel's list is hardly cut (186 tiles 528 / 536, 192 485 /
+// 543, 288 844 / 949, here with the 256-row kernel first); those with many remaining rows would still
+// gain by the other kernel (230 with a fifth of them 1004 / 856; 216 with as many 668 / 696 would not).
 constexpr int kTileMinItems = 180;
-constexpr int kTileMinItemsBeside = 112;
+constexpr int64_t kTileKeysAlone = 4000000;
+constexpr int64_t kTileKeysIdle = 2500000;
+constexpr int64_t kTileKeysMixed = 5000000;
+constexpr int64_t kTileKeysMinority = 2500000;
 constexpr int kCUs = 256;
 // Workgroups that run at once on the CUs: two of the narrow kernel on each (212-216 registers
 // a lane; head size 64 has room for three, but 512 parts are ahead of more: 4 generation steps,

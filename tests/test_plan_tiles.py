@@ -23,12 +23,34 @@ def test_few_tiles_go_to_the_128_row_kernel(monkeypatch, heads, new, reqs, tiles
     plan.destroy()
 
 
-@pytest.mark.parametrize("new,reqs,tiles", [(32 * 13, 20, 0), (32 * 14, 20, 112), (32 * 13, 2, 0)])
-def test_few_tiles_beside_other_work(monkeypatch, new, reqs, tiles):
-    """One long prompt beside `reqs` short ones, 64/8 heads: 104 and 112 tiles."""
+@pytest.mark.parametrize("heads,new,ctx,tiles", [
+    ((64, 8), 640, 14000, 0), ((64, 8), 640, 17000, 160),     # 2.3 and 2.8 M tile keys, 640 slots
+    ((64, 8), 704, 22000, 0), ((64, 8), 704, 23000, 176),     # 4.0 and 4.2 M, 704 slots
+    ((64, 8), 448, 32000, 112), ((16, 2), 64 * 8, 128000, 32), ((40, 40), 768, 60000, 120),
+    ((40, 10), 64 * 6 + 20, 70000, 0),                        # 60 tiles and a rest: 4.2 M
+    ((40, 10), 64 * 6 + 20, 90000, 60),                       # 5.4 M
+    ((10, 10), 365, 120000, 0)])                              # 1.2 M
+def test_few_tiles_over_many_keys_go_to_the_256_row_kernel(monkeypatch, heads, new, ctx, tiles):
+    """Below 180 tiles what counts is tiles times keys: the merge of the 256-row kernel's parts costs
+    the same over 16 K and over 120 K keys."""
+    monkeypatch.delenv("PV_TILE_MIN_KEYS", raising=False)
+    desc = pv.pool_desc(1 << 20, heads[1], 128, "bf16")
+    plan = pv.plan_create(desc, heads[0], [ctx], [new], 1 << 14)
+    items = [pv.plan_work_item(plan, 3, i) for i in range(pv.plan_num_work_items(plan, 3))]
+    assert len({(int(i[0]), int(i[1]), int(i[2])) for i in items}) == tiles
+    plan.destroy()
+
+
+@pytest.mark.parametrize("new,ctx,reqs,tiles", [
+    (32 * 13, 12000, 20, 0), (32 * 14, 12000, 20, 0), (32 * 13, 12000, 2, 0),
+    (32 * 20, 12000, 20, 0),                                  # 160 tiles, 2.0 M tile keys
+    (32 * 16, 20000, 20, 128),                                # 2.6 M
+    (32 * 8, 40000, 10, 0), (32 * 8, 80000, 10, 64)])         # more than half: 2.6 and 5.1 M
+def test_few_tiles_beside_other_work(monkeypatch, new, ctx, reqs, tiles):
+    """One long prompt beside `reqs` short ones, 64/8 heads."""
     monkeypatch.delenv("PV_TILE_MIN_KEYS", raising=False)
     desc = pv.pool_desc(1 << 17, 8, 128, "f16")
-    plan = pv.plan_create(desc, 64, [1000] * reqs + [12000], [400] * reqs + [new], 1024)
+    plan = pv.plan_create(desc, 64, [1000] * reqs + [ctx], [400] * reqs + [new], 8192)
     items = [pv.plan_work_item(plan, 3, i) for i in range(pv.plan_num_work_items(plan, 3))]
     assert len({(int(i[0]), int(i[1]), int(i[2])) for i in items}) == tiles
     assert pv.plan_num_work_items(plan, 1) > 0
