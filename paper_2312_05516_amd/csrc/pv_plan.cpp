@@ -288,14 +288,18 @@ static bool split_items(std::vector<WorkItem> &items, std::vector<CombineItem> &
 // below some CUs get several long items and others short ones only.  The 128-row kernel over that
 // order and over this one, in microseconds: 64 / 8 heads, 2 first prompts of 68-1291 tokens 49.0 /
 // 44.1; 32 / 8 heads of size 64, 4 of 392-955 32.1 / 26.9; 11 prompts of 113-459 on contexts of
-// 175-923 51.9 / 46.5; geometric mean of 50 batches with 257-1000 tiles 3.1 % less, all but one within
-// 0.5 % of the old order or ahead (1 % behind: 5 of 68-223, 40 / 40 heads, 18.4 / 18.5).
+// 175-923 51.9 / 46.5; geometric mean of 50 batches with 257-1000 tiles 3.1 % less.  Of whole items
+// no list was more than 1 % behind.  Parts of cut items are alike already: 272 such lists 1.6 % less
+// in the mean, 9 more than 2 % behind (11 requests, half of 35 tokens and half of one over 0.05-1.5
+// K, 40/10 heads, 26.4 / 28.1 the worst) and 29 more than 5 % ahead (21 % the best), without a property
+// that tells the ones from the others.
 // Among CUs with equal loads the last one is taken: dealt from the first CU up, the longest items
 // went to the CUs that get one item more, and lists a little over one round (276-352 items) lost
 // 2-4 %.  The 16-row kernel reads its items at the rate of memory whatever shares a CU: no difference.
 // Lengths are told apart to 1/128 of the longest one, so that one counting pass sorts them:
 // 612-760 items take 6-9 us of the host on top of 13-20 for the whole plan, 25-45 with a comparison
-// sort for each XCD and a branch for each CU.  That is for a plan that several layers use.
+// sort for each XCD and a branch for each CU.  That is for a plan that several layers use, and for
+// items whose lengths differ (see worth_pairing).
 static void pair_up(const std::vector<WorkItem> &items, std::vector<std::vector<uint32_t>> &queues)
 {
     const size_t cus = kCUs / queues.size();  // a power of two
@@ -348,6 +352,18 @@ static void pair_up(const std::vector<WorkItem> &items, std::vector<std::vector<
         queue[k] = it.pos;
         key[c] = k + cus < queue.size() ? (float)(best + (it.steps + set_up) * cus) : kFull;
     }
+}
+
+// Items within a 32nd of the longest one's length: any dealing leaves the CUs with as many of them, and
+// so as much to do to 3 %.  Five such lists: 0.997-1.004 times the time of the list's own order.
+static bool worth_pairing(const std::vector<WorkItem> &items)
+{
+    int64_t longest = 0, shortest = INT64_MAX;
+    for (const WorkItem &w : items) {
+        longest = std::max(longest, item_cost(w));
+        shortest = std::min(shortest, item_cost(w));
+    }
+    return (longest - shortest) * 32 > longest;
 }
 
 // Order of the work list = order of workgroup dispatch.  Two goals:
@@ -417,7 +433,8 @@ static void order_items(std::vector<WorkItem> &items, int xcds, size_t slots)
         for (uint32_t i = g.begin; i < g.end; ++i) queue[best].push_back(order[i]);
         load[best] += g.cost;
     }
-    if (n > (size_t)kCUs && n <= slots && kCUs % xcds == 0) pair_up(items, queue);
+    if (n > (size_t)kCUs && n <= slots && kCUs % xcds == 0 && worth_pairing(items))
+        pair_up(items, queue);
 
     // 3. interleave: position k*xcds + x takes the k-th item of XCD x's queue; once a queue is
     //    empty its positions are filled from the queues that still have items

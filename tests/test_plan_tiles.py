@@ -1,4 +1,6 @@
 """Which kernel a batch's long multi-token units go to (host only)."""
+from fractions import Fraction
+
 import pytest
 
 from paper_2312_05516_amd import binding as pv
@@ -86,7 +88,12 @@ def test_items_that_run_at_once_share_the_cus_evenly(monkeypatch, heads, new, re
     for r in range(reqs):
         tiles = [(b, min(128, q[r] * group - b)) for b in range(0, q[r] * group, 128)]
         assert rows[r] == heads[1] * sum(c * (ctx[r] + (b + c - 1) // group + 1) for b, c in tiles)
-    if not 256 < n <= 768 or any(int(i[7]) > 1 for i in items):
+    cut = any(int(i[7]) > 1 for i in items)
+    # lists of an item for each CU, of more than run at once, or with cut items: nothing more to hold
+    exempt = reqs == 97 or (heads, new) == ((8, 8, 64), 128) or uneven and heads in (
+        (8, 8, 64), (5, 5, 64), (1, 1, 128))
+    assert exempt == (cut or not 256 < n <= 768), (n, cut)
+    if exempt:
         plan.destroy()
         return
     # No CU has much more to do than one that takes as many items, beyond its longest item: the
@@ -100,3 +107,78 @@ def test_items_that_run_at_once_share_the_cus_evenly(monkeypatch, heads, new, re
                 if len(a) == len(b):
                     assert sum(a) - sum(b) <= max(a) + max(b) // 16, (x, a, b)
     plan.destroy()
+
+
+def _items(pv, plan):
+    """(req, KV head, first row, rows, first key, end, part, parts) in the order of dispatch."""
+    return [tuple(map(int, pv.plan_work_item(plan, 1, i)))
+            for i in range(pv.plan_num_work_items(plan, 1))]
+
+
+def _list_order(items):
+    """The order that groups (the row tiles of one request, KV head and part) have by themselves: by
+    length, each to the XCD with the least to do, the XCDs' queues in turn."""
+    groups = {}
+    for i in sorted(items, key=lambda i: (i[0], i[1], i[6], i[2])):
+        groups.setdefault((i[0], i[1], i[6]), []).append(i)
+    keys = {g: sum(i[5] - i[4] for i in v) for g, v in groups.items()}
+    queues, load = [[] for _ in range(8)], [0] * 8
+    for g in sorted(groups, key=lambda g: (-Fraction(keys[g], len(groups[g])), g)):
+        x = load.index(min(load))
+        queues[x] += groups[g]
+        load[x] += keys[g]
+    out, x = [], 0
+    while any(queues):
+        while not queues[x]:
+            x = (x + 1) % 8
+        out.append((x, queues[x].pop(0)))
+        x = (x + 1) % 8
+    return out
+
+
+def _fullest(items):
+    """Keys of the CU that has most to do, a set-up of 96 for each item: workgroup i goes to XCD
+    i % 8, workgroup k of an XCD to its CU k % 32."""
+    load = [0] * 256
+    for i, it in enumerate(items):
+        load[i % 8 * 32 + i // 8 % 32] += it[5] - it[4] + 96
+    return max(load)
+
+
+@pytest.mark.parametrize("heads,new,reqs,gain", [
+    # `gain`: what dealing must take off the fullest CU at least (0: the list keeps its own order)
+    ((8, 8, 64), (128, 128), 32, 0),          # 256 items: a CU each
+    ((8, 8, 64), (128, 128), 97, 0),          # 776: more than run at once
+    ((5, 5, 64), (80, 80), 60, 0),            # 300 of one length
+    ((8, 8, 64), (1, 257), 24, 0.10), ((64, 8, 128), (60, 90), 8, 0.03),
+    ((40, 40, 128), (300, 700), 2, 0.20), ((12, 12, 64), (200, 500), 13, 0.08),
+    ((10, 10, 128), (30, 120), 45, 0.10), ((64, 8, 128), (16, 380), 5, 0.15),
+    ((12, 12, 64), (60, 256), 35, 0.05)])
+@pytest.mark.parametrize("ctx", [0, 1400])
+def test_items_that_run_at_once_are_dealt_to_the_cus(monkeypatch, heads, new, reqs, gain, ctx):
+    """Lists that gain nothing keep the order of the groups; in the others the fullest CU has less to
+    do than in that order."""
+    for name in ("PV_XCDS", "PV_TILE_MIN_KEYS", "PV_SPLIT_TARGET"):
+        monkeypatch.delenv(name, raising=False)
+    group = heads[0] // heads[1]
+    desc = pv.pool_desc(1 << 17, heads[1], heads[2], "f16")
+    # cutting is another matter: a target set by hand, which no list here is short of
+    monkeypatch.setenv("PV_SPLIT_TARGET", "1")
+    same = new[0] == new[1]
+    c = [ctx if same else (97 * r * r) % (ctx + 1) for r in range(reqs)]
+    q = [new[1] - (29 * r * r) % (new[1] - new[0] + 1) for r in range(reqs)]
+    plan = pv.plan_create(desc, heads[0], c, q, 1024)
+    items = _items(pv, plan)
+    plan.destroy()
+    want = sorted((r, h, b, min(128, q[r] * group - b), 0,
+                   c[r] + (min(b + 128, q[r] * group) - 1) // group + 1, 0, 1)
+                  for r in range(reqs) for h in range(heads[1])
+                  for b in range(0, q[r] * group, 128))
+    assert sorted(items) == want
+    own = [i for _, i in _list_order(items)]
+    print(f"{len(items)} items, fullest CU {_fullest(own)} -> {_fullest(items)}")
+    if gain == 0:
+        assert items == own
+    else:
+        assert 256 < len(items) <= 768
+        assert _fullest(items) <= (1 - gain) * _fullest(own)
