@@ -167,6 +167,11 @@ size_t pv_plan_workspace_bytes(const pv_plan *plan);
  * instead of two), otherwise they are cut into items of the bandwidth-oriented kernel. */
 int32_t pv_plan_num_work_items(const pv_plan *plan, int32_t kind);
 pv_status pv_plan_work_item(const pv_plan *plan, int32_t kind, int32_t index, int32_t out[8]);
+/* Which variants of the attention kernels the plan launches (for tests and reports), a sum of: 1 = the
+ * bandwidth-oriented kernel takes its probabilities in two 16-bit terms, 2 = it reads K/V with the
+ * streaming hint, 4 = items of the matrix-core kernel (128 rows) renew their reference maximum, 8 =
+ * items of it that alone read their K/V do so with the streaming hint.  -1 for NULL. */
+int32_t pv_plan_kernel_variants(const pv_plan *plan);
 
 /* Host-side check of a page table against the plan (host copy of the table, row stride
  * max_pages_per_req): every page a request needs must be in [0, num_pages); and, if

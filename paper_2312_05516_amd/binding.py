@@ -32,6 +32,7 @@ EXPORTS = [
     "pv_plan_create", "pv_plan_destroy", "pv_plan_upload", "pv_plan_upload_to",
     "pv_plan_device_bytes", "pv_plan_owns_device_memory", "pv_plan_total_q", "pv_plan_q_start",
     "pv_plan_workspace_bytes", "pv_plan_num_work_items", "pv_plan_work_item",
+    "pv_plan_kernel_variants",
     "pv_plan_check_page_table", "pv_plan_enable_timing", "pv_plan_kernel_ms",
     "pv_kv_append_planned", "pv_multi_token_paged_attn_planned",
     "pv_kv_append", "pv_multi_token_paged_attn", "pv_attn_workspace_bytes",
@@ -94,6 +95,8 @@ _lib.pv_plan_num_work_items.restype = ctypes.c_int32
 _lib.pv_plan_num_work_items.argtypes = [_vp, ctypes.c_int32]
 _lib.pv_plan_work_item.restype = ctypes.c_int
 _lib.pv_plan_work_item.argtypes = [_vp, ctypes.c_int32, ctypes.c_int32, _i32p]
+_lib.pv_plan_kernel_variants.restype = ctypes.c_int32
+_lib.pv_plan_kernel_variants.argtypes = [_vp]
 _lib.pv_plan_check_page_table.restype = ctypes.c_int
 _lib.pv_plan_check_page_table.argtypes = [_vp, _i32p, ctypes.c_int32]
 _lib.pv_plan_enable_timing.restype = ctypes.c_int
@@ -290,6 +293,12 @@ def plan_work_item(plan: Plan, kind: int, index: int) -> np.ndarray:
     _check(_lib.pv_plan_work_item(plan.handle, int(kind), int(index), _i32(out)),
            "pv_plan_work_item")
     return out
+
+
+def plan_kernel_variants(plan: Plan) -> int:
+    """Sum of 1 (narrow kernel: probabilities in two terms), 2 (it streams K/V), 4 (128-row kernel:
+    references are renewed) and 8 (items that alone read their K/V stream them)."""
+    return int(_lib.pv_plan_kernel_variants(plan.handle))
 
 
 def plan_check_page_table(plan: Plan, page_table_host, check_append_unique: bool = True) -> int:

@@ -658,10 +658,14 @@ pv_status build_plan(const pv_pool_desc *pool, int32_t num_q_heads, const int32_
         const int32_t rows_total = n * G;
         const int64_t unit_bytes = 4 * ((int64_t)c + n) * pool->num_kv_heads * pool->head_dim;
         kv_bytes += unit_bytes;
-        if (rows_total >= tune.wide_min_rows || all_wide)
-            (rows_total <= kWideRows ? wide_once : wide_shared) += unit_bytes;
-        else
-            (rows_total <= kNarrowRows ? narrow_once : narrow_shared) += unit_bytes;
+        // a unit whose rows are all in full tiles of the 256-row kernel has none left for the others
+        const bool tiled = use_tile256(pool, tune_batch, rows_total, (int64_t)c + n);
+        if (!tiled || rows_total % kTileRows != 0) {
+            if (rows_total >= tune.wide_min_rows || all_wide)
+                (rows_total <= kWideRows ? wide_once : wide_shared) += unit_bytes;
+            else
+                (rows_total <= kNarrowRows ? narrow_once : narrow_shared) += unit_bytes;
+        }
         for (int32_t hk = 0; hk < pool->num_kv_heads; ++hk) {
             WorkItem w;
             std::memset(&w, 0, sizeof w);
@@ -678,7 +682,7 @@ pv_status build_plan(const pv_pool_desc *pool, int32_t num_q_heads, const int32_
             w.alone = rows_total <= kWideRows;
             // long units: their full 256-row tiles go to the 256-row kernel, the rest as usual
             int32_t rb = 0;
-            if (use_tile256(pool, tune_batch, rows_total, (int64_t)c + n)) {
+            if (tiled) {
                 for (; rb + kTileRows <= rows_total; rb += kTileRows) {
                     w.row_begin = rb;
                     w.row_count = kTileRows;
@@ -839,6 +843,13 @@ int32_t pv_plan_num_work_items(const pv_plan *plan, int32_t kind)
     case 3: return (int32_t)plan->tile256.size();
     }
     return -1;
+}
+
+int32_t pv_plan_kernel_variants(const pv_plan *plan)
+{
+    if (!plan) return -1;
+    return (plan->narrow_two_terms ? 1 : 0) | (plan->narrow_streams ? 2 : 0) |
+           (plan->wide_renews ? 4 : 0) | (plan->wide_streams ? 8 : 0);
 }
 
 pv_status pv_plan_work_item(const pv_plan *plan, int32_t kind, int32_t index, int32_t out[8])

@@ -182,3 +182,38 @@ def test_items_that_run_at_once_are_dealt_to_the_cus(monkeypatch, heads, new, re
     else:
         assert 256 < len(items) <= 768
         assert _fullest(items) <= (1 - gain) * _fullest(own)
+
+
+STREAMS = 8
+
+
+@pytest.mark.parametrize("long_new,long_reqs,short_reqs,streams", [
+    (512, 4, 30, True),     # 4096 rows: full tiles only, none of which the 128-row kernel reads
+    (512 + 16, 4, 30, False),  # 128 rows left of each: their K/V are read by tiles of both kernels
+    (512 + 17, 4, 30, False),  # 136 rows
+    (512 + 16, 4, 1, False), (512, 4, 1, True)])
+def test_units_of_the_256_row_kernel_do_not_count_for_the_hint(monkeypatch, long_new, long_reqs,
+                                                               short_reqs, streams):
+    """Whether the 128-row kernel's items of one-tile units read their K/V with the streaming hint goes
+    by the K/V that this kernel reads: 512 tiles over 30 K keys go to the other kernel."""
+    monkeypatch.delenv("PV_TILE_MIN_KEYS", raising=False)
+    desc = pv.pool_desc(1 << 17, 8, 128, "bf16")
+    plan = pv.plan_create(desc, 64, [30000] * long_reqs + [1000] * short_reqs,
+                          [long_new] * long_reqs + [16] * short_reqs, 2048)
+    tiles = {tuple(map(int, pv.plan_work_item(plan, 3, i)[:3]))
+             for i in range(pv.plan_num_work_items(plan, 3))}
+    assert len(tiles) == long_reqs * 8 * 16
+    assert (pv.plan_kernel_variants(plan) & STREAMS != 0) == streams
+    plan.destroy()
+
+
+@pytest.mark.parametrize("one_tile,three_tiles,streams", [(24, 0, True), (24, 12, True),
+                                                          (6, 24, False), (2, 0, False)])
+def test_units_of_one_tile_stream_in_large_batches(monkeypatch, one_tile, three_tiles, streams):
+    """At least a quarter of the K/V read once, and more than 96 MiB of it in all."""
+    monkeypatch.delenv("PV_TILE_MIN_KEYS", raising=False)
+    reqs = one_tile + three_tiles
+    plan = pv.plan_create(pv.pool_desc(1 << 14, 40, 128, "f16"), 40, [1000] * reqs,
+                          [100] * one_tile + [300] * three_tiles, 128)
+    assert (pv.plan_kernel_variants(plan) & STREAMS != 0) == streams
+    plan.destroy()
