@@ -170,7 +170,8 @@ pv_status pv_plan_work_item(const pv_plan *plan, int32_t kind, int32_t index, in
 /* Which variants of the attention kernels the plan launches (for tests and reports), a sum of: 1 = the
  * bandwidth-oriented kernel takes its probabilities in two 16-bit terms, 2 = it reads K/V with the
  * streaming hint, 4 = items of the matrix-core kernel (128 rows) renew their reference maximum, 8 =
- * items of it that alone read their K/V do so with the streaming hint.  -1 for NULL. */
+ * items of it that alone read their K/V do so with the streaming hint (the kernel still excepts pages
+ * that requests share).  -1 for NULL. */
 int32_t pv_plan_kernel_variants(const pv_plan *plan);
 
 /* Host-side check of a page table against the plan (host copy of the table, row stride

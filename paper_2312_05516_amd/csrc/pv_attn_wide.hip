@@ -37,15 +37,17 @@
 
 namespace pv {
 
-// STREAMS: items that are `alone` copy with the streaming hint (see kStreamKvBytes).
+// STREAMS: items that are `alone` and whose pages no other request shares copy with the streaming
+// hint (see kStreamKvBytes).
 // RENEW: some item has renew_blocks.  Lists without any keep an instantiation of their own (with the
 // test for it in the loop they take 1 % longer: 64 mixed requests, 64/8 heads, 270.5 -> 273.1 us)
 template <typename T, int D, bool RENEW, bool STREAMS>
 __global__ __launch_bounds__(256, 3) void attn_wide_kernel(
     const WorkItem *__restrict__ items, const uint16_t *__restrict__ q,
     const uint16_t *__restrict__ k_pages, const uint16_t *__restrict__ v_pages,
-    const int32_t *__restrict__ page_table, int32_t max_pages, int32_t num_q_heads,
-    int32_t num_kv_heads, int32_t group, float scale_log2e, uint32_t q_keep, uint32_t q_sign,
+    const int32_t *__restrict__ page_table, int32_t max_pages, int32_t num_reqs,
+    int32_t num_q_heads, int32_t num_kv_heads, int32_t group, float scale_log2e, uint32_t q_keep,
+    uint32_t q_sign,
     uint16_t *__restrict__ out, float *__restrict__ ws_o, float *__restrict__ ws_ml)
 {
     // Keys per block: 32 for head size 128; 64 for head size 64, where 32 keys are only 8
@@ -117,6 +119,16 @@ __global__ __launch_bounds__(256, 3) void attn_wide_kernel(
     const int last_pg = (it.kv_end - 1) >> 4;
     const int pg0 = it.kv_begin >> 4;
     const int nblocks = (it.kv_end - it.kv_begin + BK - 1) / BK;
+    // STREAMS: whether somebody else reads an `alone` item's pages.  Looked for where most of them
+    // are shared: the page in the middle of its range, in the table rows of the 64 requests around.
+    int own_page = 0, other_page = -1;
+    if (STREAMS && it.alone) {
+        const int mid = (pg0 + last_pg) >> 1;
+        const int other = max(min(it.req - 32, num_reqs - 64), 0) + lane;
+        own_page = pt[mid];
+        if (other < num_reqs && other != it.req)
+            other_page = page_table[(int64_t)other * max_pages + mid];
+    }
     const uint32_t lane_bytes = (uint32_t)lane * 16u;
     // asynchronous copies move bytes [w*1024, w*1024+1024) of every 4 KiB pass over the K (V) part:
     // ids of the pages that this wavefront's pieces of a block lie in (a page past the end is never
@@ -253,28 +265,35 @@ __global__ __launch_bounds__(256, 3) void attn_wide_kernel(
         l_run += psum;
     };
 
-    // The item from its first copy to its last block; `stream`: with the streaming hint on its
-    // copies.  A flow of its own for either: with both kinds of copies in one loop and a branch
-    // between them batches that stream nothing are 2-4 % slower.
-    auto run = [&](auto stream) {
-        // prologue: blocks 0 and 1 on their way, block 0 landed and visible to everyone; the page
-        // ids of the block after next are always fetched one iteration early
-        int id0, id1;
-        page_ids(0, id0, id1);
-        dma_block(smem[0], id0, id1, stream);
-        if (nblocks > 1) {
-            page_ids(1, id0, id1);
-            dma_block(smem[1], id0, id1, stream);
-        }
-        page_ids(2, id0, id1);
-        asm volatile("" ::: "memory");
-        // the queries (loaded first) and block 0 must be there; block 1 may still be on its way
-        if (nblocks > 1)
-            __builtin_amdgcn_s_waitcnt(waitcnt_imm(2 * PASSES, 0));
+    // prologue: blocks 0 and 1 on their way, block 0 landed and visible to everyone; the page ids of
+    // the block after next are always fetched one iteration early
+    int id0, id1;
+    auto dma_first = [&](unsigned char *stage) {  // nobody waits for the other requests' page ids here
+        if (STREAMS && it.alone)
+            dma_block(stage, id0, id1, std::bool_constant<STREAMS>{});
         else
-            __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, 0));
-        __builtin_amdgcn_s_barrier();
-        asm volatile("" : "+s"(id0), "+s"(id1)::"memory");
+            dma_block(stage, id0, id1, std::false_type{});
+    };
+    page_ids(0, id0, id1);
+    dma_first(smem[0]);
+    if (nblocks > 1) {
+        page_ids(1, id0, id1);
+        dma_first(smem[1]);
+    }
+    page_ids(2, id0, id1);
+    asm volatile("" ::: "memory");
+    // the queries (loaded first) and block 0 must be there; block 1 may still be on its way
+    if (nblocks > 1)
+        __builtin_amdgcn_s_waitcnt(waitcnt_imm(2 * PASSES, 0));
+    else
+        __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, 0));
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" : "+s"(id0), "+s"(id1)::"memory");
+
+    // The item's blocks; `stream`: with the streaming hint on its copies from the third block on.  A
+    // flow of its own for either: with both kinds of copies in one loop and a branch between them
+    // batches that stream nothing are 2-4 % slower.
+    auto run = [&](auto stream) {
         const int tail = it.kv_end - it.kv_begin - BK * (nblocks - 1);  // keys of the last block
         int at = 0, at2 = 2;  // stages of blocks b and b + 2
         // one block: `compute` works on its stage between the copy of the block after next and the
@@ -331,7 +350,7 @@ __global__ __launch_bounds__(256, 3) void attn_wide_kernel(
             });
         }
     };
-    if (STREAMS && it.alone)
+    if (STREAMS && it.alone && !__any(other_page == own_page))
         run(std::bool_constant<STREAMS>{});
     else
         run(std::false_type{});
@@ -428,7 +447,7 @@ static hipError_t launch_wide_t(const pv_plan *plan, const DeviceLists &dl, cons
                                                           : attn_wide_kernel<T, D, false, false>);
     hipLaunchKernelGGL(kernel, dim3(n), dim3(256), 0, stream, dl.wide, (const uint16_t *)q,
                        (const uint16_t *)k_pages, (const uint16_t *)v_pages,
-                       page_table, plan->max_pages_per_req, plan->num_q_heads,
+                       page_table, plan->max_pages_per_req, plan->num_reqs, plan->num_q_heads,
                        plan->pool.num_kv_heads, plan->group, c, q_keep, q_sign, (uint16_t *)out,
                        ws_o, ws_ml);
     return hipGetLastError();

@@ -94,6 +94,34 @@ def test_lists_cut_into_fewer_parts_are_no_further_from_64_bits(monkeypatch, ctx
     assert err <= even_err * 1.001
 
 
+@pytest.mark.parametrize("ctx,new,heads", [
+    ([16000], [365], (10, 10, 128)), ([14000], [70], GQA), ([20000, 9000], [188, 200], GQA),
+    ([28000], [128], (16, 2, 128))])
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+def test_few_long_prompts_are_no_further_from_64_bits(monkeypatch, ctx, new, heads, dtype):
+    """Too few 256-row tiles for a kernel of their own: the 128-row kernel takes them.  Against the
+    256-row kernel on the same values, whose queries are rounded once more: no further from 64 bits."""
+    from paper_2312_05516_amd import binding as pv
+    monkeypatch.delenv("PV_TILE_MIN_KEYS", raising=False)
+
+    def tiles():
+        plan = pv.plan_create(pv.pool_desc(b.num_pages, b.num_kv_heads, b.head_dim, b.dtype),
+                              b.num_q_heads, b.ctx_lens, b.q_lens, b.max_pages_per_req)
+        n = pv.plan_num_work_items(plan, 3)
+        plan.destroy()
+        return n
+    b, q, k, v = _state(ctx, new, heads, dtype, 91)
+    want = _in_64_bits(b, q, k, v)
+    assert tiles() == 0
+    err = _error(_run(b, q, k, v)[0], want)
+    monkeypatch.setenv("PV_TILE_MIN_KEYS", "8192")
+    assert tiles() > 0
+    other = _error(_run(b, q, k, v)[0], want)
+    print(f"{err:.4e}, with the 256-row kernel {other:.4e}", flush=True)
+    assert err <= other
+    assert err <= (1.2e-3 if dtype == "f16" else 1e-2)
+
+
 @pytest.mark.parametrize("bits", [-300.0, -30.0, -3.0, 3.0, 30.0, 300.0])
 @pytest.mark.parametrize("heads,dtype,reqs", [(MHA, "f16", 10), ((20, 20, 64), "bf16", 24)])
 def test_reference_is_renewed_under_falling_and_rising_scores(heads, dtype, reqs, bits):
