@@ -171,7 +171,7 @@ pv_status pv_plan_work_item(const pv_plan *plan, int32_t kind, int32_t index, in
  * bandwidth-oriented kernel takes its probabilities in two 16-bit terms, 2 = it reads K/V with the
  * streaming hint, 4 = items of the matrix-core kernel (128 rows) renew their reference maximum, 8 =
  * items of it that alone read their K/V do so with the streaming hint (the kernel still excepts pages
- * that requests share).  -1 for NULL. */
+ * that requests share), 16 = the 256-row kernel applies the scale to the scores, not the queries.  -1 for NULL. */
 int32_t pv_plan_kernel_variants(const pv_plan *plan);
 
 /* Host-side check of a page table against the plan (host copy of the table, row stride
@@ -206,7 +206,8 @@ pv_status pv_kv_append_planned(pv_plan *plan, const void *k_new, const void *v_n
  * weighted sum are accumulated in fp32; out is rounded to the 16-bit dtype.  For
  * |scale*log2(e)| <= 0.25 the 256-row kernel applies the scale to the queries (rounded back to
  * 16 bits) instead of the scores, a perturbation of the size of the rounding the probabilities
- * get; larger scales are applied to the scores in fp32 by every kernel.  Must run after the append of
+ * get, unless the plan has few items for it; larger scales are applied to the scores in fp32 by
+ * every kernel.  Must run after the append of
  * the same batch on the same stream.
  *   q, out     : device [total_q, Hq, D]
  * Launches at most four kernels (the two matrix-core attention kernels, bandwidth-oriented

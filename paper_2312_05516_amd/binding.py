@@ -297,7 +297,8 @@ def plan_work_item(plan: Plan, kind: int, index: int) -> np.ndarray:
 
 def plan_kernel_variants(plan: Plan) -> int:
     """Sum of 1 (narrow kernel: probabilities in two terms), 2 (it streams K/V), 4 (128-row kernel:
-    references are renewed) and 8 (items that alone read their K/V stream them)."""
+    references are renewed), 8 (items that alone read their K/V stream them) and 16 (256-row kernel:
+    scores are scaled, not queries)."""
     return int(_lib.pv_plan_kernel_variants(plan.handle))
 
 

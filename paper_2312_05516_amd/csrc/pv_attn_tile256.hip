@@ -37,7 +37,8 @@
 // back to 16 bits when they are loaded.  That rounding moves a score by at most 2^-9 (bf16) or
 // 2^-12 (fp16) of sum_d |q_d k_d| * scale*log2(e), the size of the rounding the probabilities get
 // anyway before the second product; the launch uses it only while |scale*log2(e)| <= 0.25 (1/sqrt(D)
-// for D >= 34), and the exact fp32 scaling otherwise.
+// for D >= 34), and the exact fp32 scaling otherwise and for plans with few items of this kernel
+// (pv_plan::tile_scales_scores).
 #include <type_traits>
 
 #include "pv_device.h"
@@ -590,7 +591,8 @@ static hipError_t launch_tile256_t(const pv_plan *plan, const DeviceLists &dl, c
     const int n = (int)plan->tile256.size();
     const float c_signed = scale * kLog2e;
     const float c_abs = c_signed < 0.f ? -c_signed : c_signed;
-    if (c_abs <= 0.25f) {
+    // (a zero scale in fp32 would make NaN of a masked score, minus infinity)
+    if (c_abs <= 0.25f && (!plan->tile_scales_scores || c_abs == 0.f)) {
         // queries pre-multiplied by scale*log2(e): the sign travels with them
         hipLaunchKernelGGL((attn_tile256_kernel<T, true>), dim3(n), dim3(256), 0, stream,
                            dl.tile256, (const uint16_t *)q, (const uint16_t *)k_pages,

@@ -536,6 +536,7 @@ pv_status build_plan(const pv_pool_desc *pool, int32_t num_q_heads, const int32_
     plan->d_owned = nullptr;
     std::memset(&plan->dev, 0, sizeof plan->dev);
     plan->timing = false;
+    plan->tile_scales_scores = false;
     for (void *&e : plan->events) e = nullptr;
     for (bool &u : plan->event_used) u = false;
     int32_t at = 0;
@@ -582,6 +583,7 @@ pv_status build_plan(const pv_pool_desc *pool, int32_t num_q_heads, const int32_
         int64_t pairs_all = 0, pairs_tile = 0, items = 0, keys = 0, longest = 0;
         // of units that qualify under the usual limit, and of their full tiles
         int64_t pairs_long = 0, pairs_long_tiles = 0, long_items = 0, long_keys = 0;
+        int64_t long_min = INT64_MAX, long_max = 0;
         for (int32_t r = 0; r < num_reqs; ++r) {
             const int64_t n = q_lens[r], c = ctx_lens[r];
             if (n == 0) continue;
@@ -594,6 +596,8 @@ pv_status build_plan(const pv_pool_desc *pool, int32_t num_q_heads, const int32_
                 if (kv >= tune.tile_min_keys) {
                     long_items += tiles * pool->num_kv_heads;
                     long_keys += tiles * pool->num_kv_heads * kv;
+                    long_min = std::min(long_min, kv);
+                    long_max = std::max(long_max, kv);
                     pairs_long += rows_total * kv;
                     pairs_long_tiles += tiles * kTileRows * kv;
                 }
@@ -606,14 +610,21 @@ pv_status build_plan(const pv_pool_desc *pool, int32_t num_q_heads, const int32_
         if (items >= tune.split_target && pairs_tile * 10 >= pairs_all * 9 && longest <= 2 * chunk)
             tune_batch.tile_min_keys = tune.tile_batch_min_keys;
         else if (long_items > 0 && long_items < kTileMinItems) {
-            // slots that the 128-row kernel's list of the same tiles fills, cut to run at once
-            const int64_t wide_parts = kWideSlots / (2 * long_items) * (2 * long_items);
-            int64_t limit = kTileKeysMixed;
-            if (pairs_long < pairs_all - pairs_long)
-                limit = kTileKeysMinority;
-            else if (pairs_long_tiles >= pairs_all - pairs_all / 50)
-                limit = wide_parts * 8 <= kWideSlots * 7 ? kTileKeysIdle : kTileKeysAlone;
-            if (long_keys < limit) tune_batch.tile_min_keys = 0;
+            const bool minority = pairs_long < pairs_all - pairs_long;
+            if (!minority || long_items < kTileMinItemsBeside || long_keys < kTileKeysBeside) {
+                // slots that the 128-row kernel's list of the same tiles fills, cut to run at once
+                // (where lengths differ the cut finds one that fills them)
+                const int64_t wide_parts = kWideSlots / (2 * long_items) * (2 * long_items);
+                const bool idle = wide_parts * 8 <= kWideSlots * 7 &&
+                                  (long_max - long_min) * 8 <= long_max;
+                int64_t limit = kTileKeysMixed;
+                if (pairs_long_tiles >= pairs_all - pairs_all / 50)
+                    limit = idle ? kTileKeysIdle : kTileKeysAlone;
+                if (long_keys < limit)
+                    tune_batch.tile_min_keys = 0;
+                else
+                    plan->tile_scales_scores = true;
+            }
         }
     }
     bool all_wide = false;
@@ -849,7 +860,8 @@ int32_t pv_plan_kernel_variants(const pv_plan *plan)
 {
     if (!plan) return -1;
     return (plan->narrow_two_terms ? 1 : 0) | (plan->narrow_streams ? 2 : 0) |
-           (plan->wide_renews ? 4 : 0) | (plan->wide_streams ? 8 : 0);
+           (plan->wide_renews ? 4 : 0) | (plan->wide_streams ? 8 : 0) |
+           (plan->tile_scales_scores ? 16 : 0);
 }
 
 pv_status pv_plan_work_item(const pv_plan *plan, int32_t kind, int32_t index, int32_t out[8])

@@ -142,29 +142,32 @@ constexpr int kTileRows = 256;   // rows per item of the 256-row matrix-core ker
 // The 256-row kernel takes a batch's long units only if they have this many tiles, or fewer with this
 // many keys over all tiles.  Few tiles are cut into about 1024 parts, whose rows, twice as many as
 // the 128-row kernel's, the merge has to read: 60-80 us more, whatever the number of keys; in return a
-// million tile keys take 95-110 us in place of 120-140.  So what counts is their product, and how well
-// the other kernel's list fills its slots.  Whole step with the 128-row kernel and with the 256-row
-// kernel, in microseconds, by million tile keys:
-//  * nothing but these tiles: 0.84 (20 tiles) 130 / 160, 1.66 (112) 240 / 260, 2.66 (176) 351 / 367,
-//    2.99 (96) 381 / 397, 3.40 (150) 460 / 462, 5.19 (176) 672 / 645, 5.9 (96) 733 / 699, 6.9 (112)
-//    859 / 763, 17.9 (160) 2442 / 1945.  Where the 128-row kernel's list leaves an eighth of the slots
-//    idle the 256-row kernel is ahead sooner: 2.41 (160) 342 / 331, 3.28 (150) 514 / 474, 3.45 (80)
-//    490 / 472; 2.13 (80) 314 / 326.
+// million tile keys take 100-115 us in place of 120-140.  So what counts is their product, and how well
+// the other kernel's list fills its slots.  The few tiles that do go there have their scores scaled in
+// fp32 (4 % more time than with scaled queries): 80 parts in 100 of the scaled queries' distance from
+// 64 bits, the same as the 128-row kernel's.  Whole step with the 128-row and with the 256-row kernel,
+// in microseconds, by million tile keys:
+//  * nothing but these tiles: 2.0 (96 tiles) 257 / 301, 2.5 (120) 368 / 384, 3.9 (120) 585 / 547, 5.9
+//    (96) 753 / 783, 11.5 (96) 1386 / 1407, 7.7 (120) 1092 / 993.  Where the 128-row kernel's list leaves
+//    an eighth of the slots idle the 256-row kernel is ahead sooner: 2.3 (112) 314 / 328, 3.3 (160) 453
+//    / 434, 3.6 (112) 483 / 472, 5.2 (160) 703 / 643, 10.3 (160) 1371 / 1200, 19 (160) 2643 / 2224.
 //  * remaining rows or other requests beside them, which with the 256-row kernel are a launch of their
-//    own: 2.77 (170) 600 / 693, 3.79 (150) 571 / 593, 4.66 (80) 668 / 689, 4.90 (90) 659 / 694, 5.2 (60)
-//    889 / 801, 5.7 (152) 837 / 797, 7.3 (160) 1146 / 1082, 9.0 (90) 1537 / 1332, 13.2 (150) 2975 / 2440.
-//  * the long units less than half of the batch's pairs: 1.4 (112) 509 / 582, 1.6 (160) 486 / 560, 2.4
-//    (144) 828 / 881, 2.6 (128) 687 / 757, 3.6 (176) 1417 / 1464, 5.3 (120) 1585 / 1540.  The limit is
-//    lower than that asks for: one prompt of 512 tokens over 20 K keys among shorter ones (the 2.6)
-//    has always gone to the kernel for long units.
+//    own: 2.4 (120) 428 / 440, 3.9 (120) 665 / 640, 7.7 (120) 1308 / 1154; with scaled queries 2.8 (170)
+//    600 / 693, 4.7 (80) 668 / 689, 4.9 (90) 659 / 694, 5.7 (152) 837 / 797, 7.3 (160) 1146 / 1082, 8.0
+//    (80) 1247 / 1274, 9.0 (90) 1537 / 1332, 11.4 (130) 1713 / 1730, 13.2 (150) 2975 / 2440.
+//  * at least kTileMinItemsBeside tiles of long units that are less than half of the batch's pairs:
+//    1.4 (112) 509 / 582, 1.6 (160) 486 / 560, 2.4 (144) 828 / 881, 2.6 (128) 687 / 757, 3.6 (176) 1417 /
+//    1464, 5.3 (120) 1585 / 1540.  The limit is lower than that asks for: one prompt of 512 tokens over
+//    20 K keys among shorter ones (the 2.6) has always gone to the kernel for long units.
 // From kTileMinItems tiles on the 256-row kernel's list is hardly cut (186 tiles 528 / 536, 192 485 /
 // 543, 288 844 / 949, here with the 256-row kernel first); those with many remaining rows would still
 // gain by the other kernel (230 with a fifth of them 1004 / 856; 216 with as many 668 / 696 would not).
 constexpr int kTileMinItems = 180;
-constexpr int64_t kTileKeysAlone = 4000000;
-constexpr int64_t kTileKeysIdle = 2500000;
-constexpr int64_t kTileKeysMixed = 5000000;
-constexpr int64_t kTileKeysMinority = 2500000;
+constexpr int64_t kTileKeysAlone = 6000000;
+constexpr int64_t kTileKeysIdle = 3500000;
+constexpr int64_t kTileKeysMixed = 7000000;
+constexpr int kTileMinItemsBeside = 112;
+constexpr int64_t kTileKeysBeside = 2500000;
 constexpr int kCUs = 256;
 // Workgroups that run at once on the CUs: two of the narrow kernel on each (212-216 registers
 // a lane; head size 64 has room for three, but 512 parts are ahead of more: 4 generation steps,
@@ -250,6 +253,8 @@ struct pv_plan {
     // K/V with the streaming hint: items of the 128-row kernel that are `alone` and share no pages;
     // all of the narrow kernel's
     bool wide_streams, narrow_streams;
+    // 256-row kernel: no scaled queries (see kTileMinItems)
+    bool tile_scales_scores;
     size_t workspace_bytes;
 
     // Host image of everything the kernels read from the plan: the nine arrays above, each at a

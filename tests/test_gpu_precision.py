@@ -27,7 +27,7 @@ def _state(ctx, new, heads, dtype, seed):
     return b, draw(b.total_q, b.num_q_heads, b.head_dim), draw(*pool), draw(*pool)
 
 
-def _run(b, q, k, v):
+def _run(b, q, k, v, scale=None):
     import torch
     from paper_2312_05516_amd import binding as pv
     desc = pv.pool_desc(b.num_pages, b.num_kv_heads, b.head_dim, b.dtype)
@@ -35,15 +35,15 @@ def _run(b, q, k, v):
     pv.plan_upload(plan)
     ws = torch.empty(max(pv.plan_workspace_bytes(plan), 256), dtype=torch.uint8, device="cuda")
     out = torch.full_like(q, float("nan"))
-    pv.multi_token_paged_attn_planned(plan, q, k, v, torch.from_numpy(b.page_table).cuda(), b.scale,
-                                      out, ws)
+    pv.multi_token_paged_attn_planned(plan, q, k, v, torch.from_numpy(b.page_table).cuda(),
+                                      b.scale if scale is None else scale, out, ws)
     torch.cuda.synchronize()
     items = [pv.plan_num_work_items(plan, kind) for kind in (0, 1)]
     plan.destroy()
     return out, items
 
 
-def _in_64_bits(b, q, k, v):
+def _in_64_bits(b, q, k, v, scale=None):
     import torch
     hkv, d, g = b.num_kv_heads, b.head_dim, b.num_q_heads // b.num_kv_heads
     kv_, vv = k.view(b.num_pages, hkv, d // 8, 16, 8), v.view(b.num_pages, hkv, 2, d, 8)
@@ -57,7 +57,8 @@ def _in_64_bits(b, q, k, v):
         qq = q[s0:s0 + n].double().view(n, hkv, g, d).permute(1, 2, 0, 3).reshape(hkv, g * n, d)
         hidden = (torch.arange(kv, device="cuda")[None, :] >
                   (c + torch.arange(n, device="cuda"))[:, None]).repeat(g, 1)
-        s = torch.bmm(qq.contiguous(), kk.transpose(1, 2).contiguous()) * b.scale
+        s = torch.bmm(qq.contiguous(), kk.transpose(1, 2).contiguous())
+        s *= b.scale if scale is None else scale
         o = torch.bmm(torch.softmax(s.masked_fill_(hidden[None], -math.inf), -1), vd.contiguous())
         want[s0:s0 + n] = o.view(hkv, g, n, d).permute(2, 0, 1, 3).reshape(n, hkv * g, d)
     return want
@@ -120,6 +121,41 @@ def test_few_long_prompts_are_no_further_from_64_bits(monkeypatch, ctx, new, hea
     print(f"{err:.4e}, with the 256-row kernel {other:.4e}", flush=True)
     assert err <= other
     assert err <= (1.2e-3 if dtype == "f16" else 1e-2)
+
+
+@pytest.mark.parametrize("ctx,new,heads", [([22000], [640], GQA), ([48000], [2048], (10, 10, 128)),
+                                           ([150000, 120000], [560, 300], (16, 2, 128))])
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+def test_few_tiles_over_many_keys_are_no_further_from_64_bits(monkeypatch, ctx, new, heads, dtype):
+    """Few 256-row tiles over so many keys that they go to the 256-row kernel all the same: with scores
+    scaled in fp32, no further from 64 bits than in the 128-row kernel, which rounds nothing that this
+    one does not (0.1 % for the parts, which begin at other keys).  Negative, small and zero scales."""
+    from paper_2312_05516_amd import binding as pv
+    monkeypatch.delenv("PV_TILE_MIN_KEYS", raising=False)
+    b, q, k, v = _state(ctx, new, heads, dtype, 93)
+    want = _in_64_bits(b, q, k, v)
+
+    def run(scale=None):
+        plan = pv.plan_create(pv.pool_desc(b.num_pages, b.num_kv_heads, b.head_dim, b.dtype),
+                              b.num_q_heads, b.ctx_lens, b.q_lens, b.max_pages_per_req)
+        variants, items = pv.plan_kernel_variants(plan), pv.plan_num_work_items(plan, 3)
+        plan.destroy()
+        return _run(b, q, k, v, scale)[0], variants & 16, items
+    out, scaled, items = run()
+    assert scaled and items > 0
+    err = _error(out, want)
+    for scale in (-b.scale, 1e-30, -1e-30, 0.0):
+        exact = _in_64_bits(b, q, k, v, scale)
+        # nearly equal weights: an average of 20 K values or more, small against their rounding
+        d = float((run(scale)[0].double() - exact).abs().max() / exact.abs().max())
+        print(f"scale {scale:.2g}: {d:.2e} of the largest result", flush=True)
+        assert d <= (2e-3 if dtype == "f16" else 1.6e-2)
+    monkeypatch.setenv("PV_TILE_MIN_KEYS", "0")
+    out, _, items = run()
+    assert items == 0
+    other = _error(out, want)
+    print(f"{err:.4e}, with the 128-row kernel {other:.4e}", flush=True)
+    assert err <= other * 1.001
 
 
 @pytest.mark.parametrize("bits", [-300.0, -30.0, -3.0, 3.0, 30.0, 300.0])

@@ -5,6 +5,8 @@ import pytest
 
 from paper_2312_05516_amd import binding as pv
 
+STREAMS, SCALES_SCORES = 8, 16  # of pv_plan_kernel_variants
+
 
 @pytest.mark.parametrize("heads,new,reqs,tiles", [
     ((10, 10), 365, 1, 0), ((64, 8), 188, 2, 0), ((40, 40), 700, 1, 0),
@@ -26,11 +28,11 @@ def test_few_tiles_go_to_the_128_row_kernel(monkeypatch, heads, new, reqs, tiles
 
 
 @pytest.mark.parametrize("heads,new,ctx,tiles", [
-    ((64, 8), 640, 14000, 0), ((64, 8), 640, 17000, 160),     # 2.3 and 2.8 M tile keys, 640 slots
-    ((64, 8), 704, 22000, 0), ((64, 8), 704, 23000, 176),     # 4.0 and 4.2 M, 704 slots
-    ((64, 8), 448, 32000, 112), ((16, 2), 64 * 8, 128000, 32), ((40, 40), 768, 60000, 120),
-    ((40, 10), 64 * 6 + 20, 70000, 0),                        # 60 tiles and a rest: 4.2 M
-    ((40, 10), 64 * 6 + 20, 90000, 60),                       # 5.4 M
+    ((64, 8), 640, 20000, 0), ((64, 8), 640, 22000, 160),     # 3.3 and 3.6 M tile keys, 640 slots
+    ((64, 8), 704, 32000, 0), ((64, 8), 704, 35000, 176),     # 5.8 and 6.3 M, 704 slots
+    ((64, 8), 448, 32000, 112), ((16, 2), 64 * 8, 190000, 32), ((40, 40), 768, 60000, 120),
+    ((40, 10), 64 * 6 + 20, 90000, 0),                        # 60 tiles and a rest: 5.4 M
+    ((40, 10), 64 * 6 + 20, 120000, 60),                      # 7.2 M
     ((10, 10), 365, 120000, 0)])                              # 1.2 M
 def test_few_tiles_over_many_keys_go_to_the_256_row_kernel(monkeypatch, heads, new, ctx, tiles):
     """Below 180 tiles what counts is tiles times keys: the merge of the 256-row kernel's parts costs
@@ -40,6 +42,7 @@ def test_few_tiles_over_many_keys_go_to_the_256_row_kernel(monkeypatch, heads, n
     plan = pv.plan_create(desc, heads[0], [ctx], [new], 1 << 14)
     items = [pv.plan_work_item(plan, 3, i) for i in range(pv.plan_num_work_items(plan, 3))]
     assert len({(int(i[0]), int(i[1]), int(i[2])) for i in items}) == tiles
+    assert (pv.plan_kernel_variants(plan) & SCALES_SCORES != 0) == (tiles > 0)
     plan.destroy()
 
 
@@ -47,7 +50,7 @@ def test_few_tiles_over_many_keys_go_to_the_256_row_kernel(monkeypatch, heads, n
     (32 * 13, 12000, 20, 0), (32 * 14, 12000, 20, 0), (32 * 13, 12000, 2, 0),
     (32 * 20, 12000, 20, 0),                                  # 160 tiles, 2.0 M tile keys
     (32 * 16, 20000, 20, 128),                                # 2.6 M
-    (32 * 8, 40000, 10, 0), (32 * 8, 80000, 10, 64)])         # more than half: 2.6 and 5.1 M
+    (32 * 8, 80000, 10, 0), (32 * 8, 112000, 10, 64)])        # more than half: 5.1 and 7.2 M
 def test_few_tiles_beside_other_work(monkeypatch, new, ctx, reqs, tiles):
     """One long prompt beside `reqs` short ones, 64/8 heads."""
     monkeypatch.delenv("PV_TILE_MIN_KEYS", raising=False)
@@ -182,9 +185,6 @@ def test_items_that_run_at_once_are_dealt_to_the_cus(monkeypatch, heads, new, re
     else:
         assert 256 < len(items) <= 768
         assert _fullest(items) <= (1 - gain) * _fullest(own)
-
-
-STREAMS = 8
 
 
 @pytest.mark.parametrize("long_new,long_reqs,short_reqs,streams", [
