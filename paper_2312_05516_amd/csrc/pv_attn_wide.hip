@@ -45,10 +45,10 @@ template <typename T, int D, bool RENEW, bool STREAMS>
 __global__ __launch_bounds__(256, 3) void attn_wide_kernel(
     const WorkItem *__restrict__ items, const uint16_t *__restrict__ q,
     const uint16_t *__restrict__ k_pages, const uint16_t *__restrict__ v_pages,
-    const int32_t *__restrict__ page_table, int32_t max_pages, int32_t num_reqs,
-    int32_t num_q_heads, int32_t num_kv_heads, int32_t group, float scale_log2e, uint32_t q_keep,
-    uint32_t q_sign,
-    uint16_t *__restrict__ out, float *__restrict__ ws_o, float *__restrict__ ws_ml)
+    const int32_t *__restrict__ page_table, int32_t max_pages, int32_t num_q_heads,
+    int32_t num_kv_heads, int32_t group, float scale_log2e, uint32_t q_keep, uint32_t q_sign,
+    uint16_t *__restrict__ out, float *__restrict__ ws_o, float *__restrict__ ws_ml,
+    int32_t num_reqs)
 {
     // Keys per block: 32 for head size 128; 64 for head size 64, where 32 keys are only 8
     // matrix-core instructions of a wavefront against about 70 of the vector ALU, a barrier, a
@@ -447,9 +447,9 @@ static hipError_t launch_wide_t(const pv_plan *plan, const DeviceLists &dl, cons
                                                           : attn_wide_kernel<T, D, false, false>);
     hipLaunchKernelGGL(kernel, dim3(n), dim3(256), 0, stream, dl.wide, (const uint16_t *)q,
                        (const uint16_t *)k_pages, (const uint16_t *)v_pages,
-                       page_table, plan->max_pages_per_req, plan->num_reqs, plan->num_q_heads,
+                       page_table, plan->max_pages_per_req, plan->num_q_heads,
                        plan->pool.num_kv_heads, plan->group, c, q_keep, q_sign, (uint16_t *)out,
-                       ws_o, ws_ml);
+                       ws_o, ws_ml, plan->num_reqs);
     return hipGetLastError();
 }
 
