@@ -22,15 +22,16 @@
 // newest loads in flight.  Blocks that touch the causal boundary or the end of the sequence run in a
 // second loop, which masks the scores, so the steady-state loop has no branches and the registers
 // for one kind of block at a time: room to request all V operands of a block while its scores are
-// computed, into the registers that its K operands leave (two at a time before, each pair waited
-// for).  Block by block 2427 -> 2281 cycles with three workgroups on a CU, 2105 -> 1745 with one or
-// two; the clock gives back half of that (1.85 -> 1.78 GHz: the chip's power limit): 64 mixed
-// requests, 64/8 heads, whole step 262.7 -> 255.6 us, 48 of head size 64 102.7 -> 99.7.  With the
-// values past the end zeroed once in LDS instead of by every reader, one division an item instead
-// of one a row, and every operand waited for by itself 253.7 and 97.1 us; 17 short prompts of head
-// size 64 22.9 -> 21.8, one prompt among few 21.3 -> 21.0.  The running maximum is
-// only moved when a new score exceeds it by more than 2^8 (softmax is shift-invariant), which
-// makes rescaling the accumulator rare.
+// computed, into the registers that its K operands leave.  Values past the end of the sequence are
+// zeroed once in LDS, not by every reader, and a row's token takes one division an item.  The running
+// maximum is only moved when a new score exceeds it by more than 2^8 (softmax is shift-invariant),
+// which makes rescaling the accumulator rare.
+//
+// What bounds it: a 32-key block of head size 128 takes 2281 cycles with three workgroups on a CU (1745
+// with one or two), of which the matrix cores need 1536 and the LDS reads, by count, 1920; on random
+// data the clock is at 1.78 GHz, the chip's power limit.  64 mixed requests, 64/8 heads, whole step
+// 254 us, 48 of head size 64 97 us (vector ALU busy half of the time, matrix cores a third); before the
+// loops were split and the operands requested ahead 262.7 and 102.7.
 #include <type_traits>
 
 #include "pv_device.h"
@@ -39,8 +40,8 @@ namespace pv {
 
 // STREAMS: items that are `alone` and whose pages no other request shares copy with the streaming
 // hint (see kStreamKvBytes).
-// RENEW: some item has renew_blocks.  Lists without any keep an instantiation of their own (with the
-// test for it in the loop they take 1 % longer: 64 mixed requests, 64/8 heads, 270.5 -> 273.1 us)
+// RENEW: some item has renew_blocks.  Lists without any keep an instantiation of their own: with the
+// test for it in the loop they take 1 % longer.
 template <typename T, int D, bool RENEW, bool STREAMS>
 __global__ __launch_bounds__(256, 3) void attn_wide_kernel(
     const WorkItem *__restrict__ items, const uint16_t *__restrict__ q,
@@ -119,15 +120,15 @@ __global__ __launch_bounds__(256, 3) void attn_wide_kernel(
     const int last_pg = (it.kv_end - 1) >> 4;
     const int pg0 = it.kv_begin >> 4;
     const int nblocks = (it.kv_end - it.kv_begin + BK - 1) / BK;
-    // STREAMS: whether somebody else reads an `alone` item's pages.  Looked for where most of them
-    // are shared: the page in the middle of its range, in the table rows of the 64 requests around.
+    // STREAMS: whether somebody else reads an `alone` item's pages.  Looked for where three quarters of
+    // them are shared: the page there, in the table rows of the 64 requests around.
     int own_page = 0, other_page = -1;
-    if (STREAMS && it.alone) {
-        const int mid = (pg0 + last_pg) >> 1;
+    if (STREAMS && it.alone && it.ctx >= kSharedMinCtx) {
+        const int at = pg0 + (last_pg - pg0) * 3 / 4;
         const int other = max(min(it.req - 32, num_reqs - 64), 0) + lane;
-        own_page = pt[mid];
+        own_page = pt[at];
         if (other < num_reqs && other != it.req)
-            other_page = page_table[(int64_t)other * max_pages + mid];
+            other_page = page_table[(int64_t)other * max_pages + at];
     }
     const uint32_t lane_bytes = (uint32_t)lane * 16u;
     // asynchronous copies move bytes [w*1024, w*1024+1024) of every 4 KiB pass over the K (V) part:
@@ -376,7 +377,9 @@ __global__ __launch_bounds__(256, 3) void attn_wide_kernel(
         // its quarter of the ring, which nobody reads any more (last barrier above), and stores
         // whole rows: 120 -> 112 us for that batch, 258 -> 252 us for a mixed batch of 64
         // requests, 64/8 heads.
-        constexpr int ROW_BYTES = 2 * D + 16;  // 16 bytes of padding: no bank conflicts either way
+        // 16 bytes of padding: the 16-byte reads have no bank conflicts; of the 8-byte writes those of
+        // rows r and r + 16 meet in the same banks, about 90 cycles a wavefront and item
+        constexpr int ROW_BYTES = 2 * D + 16;
         constexpr int PART = STAGES * 2 * HALF_BYTES / 4;
         static_assert(32 * ROW_BYTES + 32 * 8 <= PART, "a wavefront's rows fit its part of the ring");
         unsigned char *part = &smem[0][0] + w * PART;

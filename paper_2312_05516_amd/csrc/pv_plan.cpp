@@ -135,14 +135,15 @@ struct CutRule {
 //    parts as keep the longest within twice a slots-th of the keys: 11 requests of 100 tokens and
 //    one over 30 K, 40/40 heads, 163 us against 177 in about 1024 parts, 10 of 128 tokens over
 //    1000 whole 53 against 90, 19 (760 items, one over 30 K) 170 against 188.
-//  * Nothing is cut where the merge costs more than the shorter longest item gives: a launch of
-//    about 7 us, and 8 bytes per partial row element at about 4 TB/s.  16 generation steps over
-//    520-640 keys are left whole (10.8-11.2 us; cut 11.7), over 900 cut (11.9; whole 14.9); head
-//    size 64 up to 1000 (9.0 against 11.7 at 640, 13.4 against 11.7 at 1400).  6 requests of 100
-//    tokens over 900 keys, 32/8 heads, 128-row kernel: 19.0 whole, 27.6 cut; over 2500 40.6 and
-//    38.8.  Where the cut of all long items does not pay, that of the longest few may.  The 128-row
-//    kernel's items (head size 128) are cut in any case while every part has a CU of its own: 80
-//    items in 240 parts 19.8 us, 21.9 whole; 130 in 202 22.1 and 23.9; 20 in 56 18.2 and 21.3.
+//  * Nothing is cut where the merge costs more than the shorter longest item gives: about 7 us for
+//    one more kernel behind the slowest part (4-5 of its own), and 8 bytes per partial row element
+//    at about 4 TB/s.  16 generation steps over 520-640 keys are left whole (10.8-11.2 us; cut
+//    11.7), over 900 cut (11.9; whole 14.9); head size 64 up to 1000 (9.0 against 11.7 at 640, 13.4
+//    against 11.7 at 1400).  6 requests of 100 tokens over 900 keys, 32/8 heads, 128-row kernel: 19.0
+//    whole, 27.6 cut; over 2500 40.6 and 38.8.  Where the cut of all long items does not pay, that
+//    of the longest few may.  The 128-row kernel's items (head size 128) are cut in any case while
+//    every part has a CU of its own: 80 items in 240 parts 19.8 us, 21.9 whole; 130 in 202 22.1 and
+//    23.9; 20 in 56 18.2 and 21.3.
 //  * Whatever the list, no part is longer than max_len keys (0 = no such limit).
 // No rule (the 256-row kernel), or a target set by hand: target_cut.
 static bool split_items(std::vector<WorkItem> &items, std::vector<CombineItem> &combine,
@@ -561,11 +562,11 @@ pv_status build_plan(const pv_pool_desc *pool, int32_t num_q_heads, const int32_
         }
     }
 
-    // One attention launch instead of two for a mixed batch.  Every launch has a fixed cost, the
-    // two kernels cannot share a CU, and a short bandwidth-oriented launch never gets the GPU up to
-    // speed, while its units fit well into the slots the long matrix-core items leave.  But an item
-    // of the matrix-core kernel holds a workgroup slot for one step per 32 keys whatever its row
-    // count, so when the small units (generation steps) are a large amount of work, the
+    // One attention launch instead of two for a mixed batch.  A launch takes at least 2 us of the
+    // stream, the two kernels cannot share a CU, and a short bandwidth-oriented launch never gets
+    // the GPU up to speed, while its units fit well into the slots the long matrix-core items leave.
+    // But an item of the matrix-core kernel holds a workgroup slot for one step per 32 keys whatever
+    // its row count, so when the small units (generation steps) are a large amount of work, the
     // bandwidth-oriented kernel is the better place for them.  Measured crossover on mixes of
     // 256-token prompts and generation steps over 2000-token contexts, MHA 40/40 and GQA 64/8 alike:
     // 80-100 K steps of 32 keys summed over the small units and KV heads (~1.5 GB of K/V).

@@ -129,12 +129,15 @@ constexpr int64_t append_group_count(int64_t t_begin, int64_t count)
 // eight), and not where less than a quarter of the bytes is read once: an instance of the kernel
 // with both kinds of copies is up to 2 % slower on the others.
 // Requests may share pages, whose K/V the hint pushes out between their readers: the kernel looks at
-// the page table for that (see attn_wide_kernel).  Always with the hint, never, and by the table: 24
-// prompts of 100 tokens over a common prefix of 3 K, 40/40 heads, 218.0 / 204.1 / 203.4 us, over two
-// prefixes in turn 235.3 / 210.0 / 207.6; 8 such prompts and 20 generation steps 177.2 / 148.5 /
-// 149.7; 40 of 30 over 3 K, 40/10 heads, 102.7 / 93.7 / 94.7; the same batches over K/V of their own
-// 304.3 / 328.6 / 303.5, 316.8 / 333.0 / 317.1, 121.9 / 130.8 / 122.0.
+// the page table for that (see attn_wide_kernel), where three quarters of an item's range are shared
+// and contexts are long.  Always with the hint, never, and by the table: 24 prompts of 100 tokens over
+// a common prefix of 3 K, 40/40 heads, 221.5 / 204.1 / 204.5 us, over two prefixes in turn 236.4 /
+// 210.0 / 206.6; 8 such prompts and 20 generation steps 181.5 / 148.5 / 150.8; 40 of 30 over 3 K, 40/10
+// heads, 101.3 / 93.7 / 94.1; the same batches over K/V of their own 307.3 / 328.6 / 307.6, 318.6 / 333.0
+// / 318.8, 121.1 / 130.8 / 121.4.  Twelve prompts of 100 tokens, always and never: of 3 K keys 60 % shared
+// 116.2 / 125.2 us, 75 % 111.3 / 110.4, 85 % 104.4 / 102.5; of 500 keys 83 % 34.3 / 35.4, 93 % 33.4 / 35.4.
 constexpr int64_t kStreamKvBytes = 96 << 20;
+constexpr int kSharedMinCtx = 640;  // cached tokens from which the kernel looks for shared pages
 
 constexpr int kNarrowRows = 16;  // rows per item of the bandwidth-oriented kernel
 constexpr int kWideRows = 128;   // rows per item of the matrix-core kernel (4 waves x 32 rows)
